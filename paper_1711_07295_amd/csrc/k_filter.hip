@@ -43,6 +43,24 @@ __device__ __forceinline__ unsigned long long rfl64(unsigned long long v) {
   return ((unsigned long long)hi << 32) | lo;
 }
 
+// The launch's arguments, read from the kernel argument segment where they
+// are used: the pointer is made opaque, so that no argument is kept in
+// scalar registers across the sweeps (kept ones filled all 106 and spilled
+// into vector registers, which set the waves per SIMD).
+typedef const __attribute__((address_space(4))) FilterArgs *ArgPtr;
+
+__device__ __forceinline__ ArgPtr args() {
+  ArgPtr a = (ArgPtr)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(a));
+  return a;
+}
+
+// Index of this wave in the launch: workgroups of four waves, or of one in a
+// direct launch.
+__device__ __forceinline__ uint32_t wave_index() {
+  return rfl(blockIdx.x * args()->cfg.block_waves + (threadIdx.x >> 6));
+}
+
 template <int W, int R>
 struct Rows {
   uint32_t bits[R][2 * W];
@@ -63,53 +81,68 @@ struct Rows {
 constexpr uint32_t kStage = kFilterStage;
 
 struct Sink {
-  uint2 *queue;
-  JoinCounters *ctr;
-  unsigned long long cap;
-  uint32_t chunk;              // slots per reservation (>= kStage)
   uint2 *stage;                // this wave's kStage LDS entries
   uint32_t fill;               // entries staged (wave-uniform)
   uint32_t first_col;          // (column, row slab) of the first staged entry
   uint32_t first_slab;
   uint32_t fail_col;           // resume point, set when the queue fills
   uint32_t fail_slab;
-  unsigned long long pos, end; // the wave's reserved slots [pos, end), end <= cap
+  uint32_t stripe;             // the wave's stripe of the queue
+  uint32_t pos, end;           // the wave's reserved slots [pos, end) of that stripe
 };
 
 // Sentinels into the rest of the wave's chunk.
 __device__ __forceinline__ void sink_pad(Sink &s) {
+  const ArgPtr a = args();
   const uint32_t lane = threadIdx.x & 63;
-  for (unsigned long long x = s.pos + lane; x < s.end; x += 64)
-    s.queue[x] = make_uint2(kSentinel, kSentinel);
+  uint2 *q = a->queue + (unsigned long long)s.stripe * a->cfg.cap;
+  for (uint32_t x = s.pos + lane; x < s.end; x += 64) q[x] = make_uint2(kSentinel, kSentinel);
   s.pos = s.end;
 }
 
+// `want` slots of the wave's stripe, or of the first stripe after it that
+// holds `need` of them; what a full stripe had left becomes sentinels.
+// False when no stripe has room.
+__device__ __forceinline__ bool reserve(Sink &s, uint32_t want, uint32_t need) {
+  const ArgPtr a = args();
+  const uint32_t lane = threadIdx.x & 63, stripes = a->cfg.stripes, cap = a->cfg.cap;
+  JoinCounters *ctr = a->ctr;
+  for (uint32_t k = 0; k < stripes; ++k) {
+    unsigned long long base = 0;
+    if (lane == 0) base = atomicAdd(&ctr->queue_next[s.stripe][0], (unsigned long long)want);
+    base = rfl64(base);
+    s.pos = base < cap ? (uint32_t)base : cap;
+    s.end = base + want < cap ? (uint32_t)base + want : cap;
+    if (s.pos + need <= s.end) return true;
+    sink_pad(s);
+    s.stripe = (s.stripe + 1) & (stripes - 1);
+  }
+  return false;
+}
+
 // Copy the staged entries into the wave's chunk, reserving a new chunk
-// when they do not fit in the current one.  When the queue has no room
-// for them, the reserved slots become sentinels, the first staged entry's
-// point is left as the resume point and false is returned: every pair
-// before that point is in the queue, none after it.
-__device__ __forceinline__ bool flush(Sink &s) {
+// when they do not fit in the current one (in a direct launch the tile's
+// last run, which ends the wave, reserves only the slots it takes).  When
+// the queue has no room for them, the reserved slots become sentinels, the
+// first staged entry's point is left as the resume point and false is
+// returned: every pair before that point is in the queue, none after it.
+__device__ __forceinline__ bool flush(Sink &s, bool last = false) {
   const uint32_t n = rfl(s.fill);
   if (n == 0) return true;
+  const ArgPtr a = args();
   const uint32_t lane = threadIdx.x & 63;
   if (s.pos + n > s.end) {
     sink_pad(s);
-    unsigned long long base = 0;
-    if (lane == 0) base = atomicAdd(&s.ctr->queue_count, (unsigned long long)s.chunk);
-    base = rfl64(base);
-    s.pos = base < s.cap ? base : s.cap;
-    s.end = base + s.chunk < s.cap ? base + s.chunk : s.cap;
-    if (s.pos + n > s.end) {
-      sink_pad(s);
+    if (!reserve(s, last && a->cfg.direct ? n : a->cfg.chunk, n)) {
       s.fill = 0;
       s.fail_col = s.first_col;
       s.fail_slab = s.first_slab;
       return false;
     }
   }
+  uint2 *q = a->queue + (unsigned long long)s.stripe * a->cfg.cap;
   __builtin_amdgcn_wave_barrier();
-  for (uint32_t x = lane; x < n; x += 64) s.queue[s.pos + x] = s.stage[x];
+  for (uint32_t x = lane; x < n; x += 64) q[s.pos + x] = s.stage[x];
   __builtin_amdgcn_wave_barrier();
   s.pos += n;
   s.fill = 0;
@@ -261,17 +294,33 @@ __device__ __forceinline__ bool sweep(const uint64_t *__restrict__ bm_cols, cons
   return true;
 }
 
+// What a wave needs to run one tile.
+struct TileJob {
+  uint32_t row0, row_end, c0, c1;
+  bool diag;
+  uint32_t first;  // resumed inside the tile: first slab (vector ALU) or pairs to skip (MFMA)
+  const int32_t *slack;
+  const uint32_t *cmin, *cmax, *sstart;
+  uint32_t col_base;
+  bool cosine;
+  uint32_t p, q;
+};
+
 // One tile: rows [row0, row_end) of a row block (at most 64*R of them, R per
 // lane, interleaved by 64), columns [c0, c1).  Returns false when the queue
 // filled (a resume point has been recorded).
 template <int W, int R, int U, bool COS>
-__device__ __forceinline__ bool run_tile(
-    const uint64_t *__restrict__ bm_rows, const uint64_t *__restrict__ bm_cols,
-    const uint32_t *__restrict__ size_rows, const uint32_t *__restrict__ size_cols,
-    const uint32_t *__restrict__ sstart_cols, uint32_t col_base,
-    const int32_t *__restrict__ slack, const uint32_t *__restrict__ cmin,
-    const uint32_t *__restrict__ cmax, bool cosine, uint32_t p, uint32_t q, uint32_t row0,
-    uint32_t row_end, uint32_t c0, uint32_t c1, bool diag, uint32_t first_slab, Sink &sink) {
+__device__ __forceinline__ bool run_tile(const TileJob &jb, Sink &sink) {
+  const ArgPtr ka = args();
+  const uint64_t *__restrict__ bm_rows = ka->bm_rows, *__restrict__ bm_cols = ka->bm_cols;
+  const uint32_t *__restrict__ size_rows = ka->size_rows, *__restrict__ size_cols = ka->size_cols;
+  const uint32_t *__restrict__ cmin = jb.cmin, *__restrict__ cmax = jb.cmax;
+  const uint32_t *__restrict__ sstart_cols = jb.sstart;
+  const int32_t *__restrict__ slack = jb.slack;
+  const uint32_t col_base = jb.col_base, row0 = jb.row0, row_end = jb.row_end, c0 = jb.c0,
+                 c1 = jb.c1;
+  const bool diag = jb.diag;
+  uint32_t first_slab = jb.first;
   const uint32_t lane = threadIdx.x & 63;
   Rows<W, R> rw;
 #pragma unroll
@@ -304,7 +353,7 @@ __device__ __forceinline__ bool run_tile(
     for (int r = 0; r < R; ++r) {
       const bool in_band = c >= rw.cmn[r] && c <= rw.cmx[r];
       if (!in_band) thr[r] = -1;
-      else if (COS && cosine) thr[r] = cosine_slack(rw.size[r], c, p, q);
+      else if (COS && jb.cosine) thr[r] = cosine_slack(rw.size[r], c, jb.p, jb.q);
       else thr[r] = slack[rw.size[r] + c];
       any_ok |= in_band;
     }
@@ -324,49 +373,49 @@ __device__ __forceinline__ bool run_tile(
     j = gend;
   }
   // the tile's staged pairs go out before the next tile
-  return flush(sink);
+  return flush(sink, true);
 }
 
-// What a wave needs to run one tile.
-struct TileJob {
-  uint32_t row0, row_end, c0, c1;
-  bool diag;
-  uint32_t first;  // resumed inside the tile: first slab (vector ALU) or pairs to skip (MFMA)
-  const int32_t *slack;
-  const uint32_t *cmin, *cmax, *sstart;
-  uint32_t col_base;
-  bool cosine;
-  uint32_t p, q;
-};
-
-// The persistent loop both kernels share, over the tiles [cfg.tile_lo,
+// The tile loop both kernels share, over the tiles [cfg.tile_lo,
 // cfg.tile_hi) of the plan.  Waves first take the resume entries of a
-// previous launch that fall in that range (entry k goes to wave k), then
-// tiles from the partitioned cursors, until the range is exhausted or the
-// queue has filled.  run(job) runs one tile and returns false when the
-// queue filled, with the resume point in the sink.
+// previous launch that fall in that range (entries k, k + waves, ... go to
+// wave k), then fresh tiles, until the range is exhausted or the queue has
+// filled.  run(job) runs one tile and returns false when the queue filled,
+// with the resume point in the sink.
+//
+// Fresh tiles come from the partitioned cursors (persistent waves), or, in a
+// direct launch (cfg.direct), each wave takes one tile and ends: no cursor
+// is read, and the workgroup dispatch balances the tiles of an XCD, which
+// gets every eighth run of kDirectDeal tiles (regions as the cursors have
+// them would leave XCDs idle: nobody takes their neighbours' tiles).  The cursors cost a launch about 45 us that does not grow with
+// its work: a wave that finds its own cursor dry reads the other 63 one
+// after the other, a memory round trip each.  In a direct launch every
+// tile a full queue keeps a wave from starting goes to the resume list (a
+// round that resumes has no fresh tiles there: the first round had them
+// all).
+constexpr uint32_t kDirectDeal = 8;
+
 template <class Run>
-__device__ __forceinline__ void persistent(const uint32_t *__restrict__ tables,
-                                           const TaskDesc *__restrict__ tasks,
-                                           const RowBlock *__restrict__ blocks,
-                                           const uint32_t *__restrict__ tile_block,
-                                           const uint32_t *__restrict__ sstart_cols,
-                                           JoinCounters *__restrict__ ctr,
-                                           const Resume *__restrict__ resume_in,
-                                           Resume *__restrict__ resume_out,
-                                           const FilterConfig &cfg, Sink &sink, Run &&run) {
+__device__ __forceinline__ void tile_loop(Sink &sink, Run &&run) {
   const uint32_t lane = threadIdx.x & 63;
-  const uint32_t wave = rfl(blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6));
-  bool resumed = false;
+  const uint32_t wave = wave_index();
   uint32_t t = 0, col = 0, slab = 0;
-  if (wave < cfg.n_resume_in && wave < cfg.resume_cap) {
-    t = rfl(resume_in[wave].tile);
-    col = rfl(resume_in[wave].col);
-    slab = rfl(resume_in[wave].slab);
-    resumed = t >= cfg.tile_lo && t < cfg.tile_hi;
-  }
-  const uint32_t n_tiles = cfg.tile_hi - cfg.tile_lo;
-  uint32_t *cursors = &ctr->tile_next[cfg.cls][0][0];
+  uint32_t entry = wave;
+  bool fresh = true;     // direct: the wave's tile is still to take
+  bool stopped = false;  // this wave found the queue full
+  // the tile stays to be done from (c, s) on
+  auto record = [&](uint32_t tile, uint32_t c, uint32_t s) {
+    const ArgPtr a = args();
+    if (lane == 0) {
+      const uint32_t q = atomicAdd(&a->ctr->n_resume, 1u);
+      Resume rs;
+      rs.tile = tile;
+      rs.col = c;
+      rs.slab = s;
+      rs.pad = 0;
+      if (q < a->cfg.resume_cap) a->resume_out[q] = rs;
+    }
+  };
   // Each XCD owns one contiguous region of the tile range, so that its
   // waves sweep neighbouring row blocks whose columns stay in its L2.
   // Inside a region the tiles are dealt to kSub sub-cursors in blocks of
@@ -379,8 +428,42 @@ __device__ __forceinline__ void persistent(const uint32_t *__restrict__ tables,
   const uint32_t xcd0 = blockIdx.x % kXcds, sub0 = (blockIdx.x / kXcds) % kSub;
   uint32_t visit = 0;
   for (;;) {
-    if (!resumed) {
-      if (__hip_atomic_load(&ctr->overflow, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) break;
+    const ArgPtr a = args();
+    JoinCounters *ctr = a->ctr;
+    const uint32_t tile_lo = a->cfg.tile_lo, tile_hi = a->cfg.tile_hi;
+    const uint32_t n_tiles = tile_hi - tile_lo;
+    const uint32_t n_resume = min(a->cfg.n_resume_in, a->cfg.resume_cap);
+    bool resumed = false;
+    while (entry < n_resume && !resumed) {
+      const Resume *in = a->resume_in + entry;
+      t = rfl(in->tile);
+      col = rfl(in->col);
+      slab = rfl(in->slab);
+      resumed = t >= tile_lo && t < tile_hi;
+      entry += a->cfg.waves;
+    }
+    const bool full =
+        stopped ||
+        rfl(__hip_atomic_load(&ctr->overflow, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) != 0;
+    if (resumed && full) {
+      record(t, col, slab);
+      continue;
+    }
+    if (!resumed && a->cfg.direct) {
+      if (!fresh || a->cfg.n_resume_in) break;
+      fresh = false;
+      const uint32_t i = blockIdx.x / kXcds;  // one wave per workgroup
+      const uint32_t k = ((i / kDirectDeal) * kXcds + blockIdx.x % kXcds) * kDirectDeal +
+                         i % kDirectDeal;
+      if (k >= n_tiles) break;
+      t = tile_lo + k;
+      if (full) {
+        record(t, kTileStart, 0);
+        break;
+      }
+    } else if (!resumed) {
+      if (full) break;
+      uint32_t *cursors = &ctr->tile_next[a->cfg.cls][0][0];
       bool got = false;
       while (visit < kParts) {
         const uint32_t x = (xcd0 + visit / kSub) % kXcds, k = (sub0 + visit) % kSub;
@@ -398,7 +481,7 @@ __device__ __forceinline__ void persistent(const uint32_t *__restrict__ tables,
           c = atomicAdd(cur, 1u);
         c = rfl(c);
         if (c < owned) {
-          t = cfg.tile_lo + r0 + ((c / kDeal) * kSub + k) * kDeal + c % kDeal;
+          t = tile_lo + r0 + ((c / kDeal) * kSub + k) * kDeal + c % kDeal;
           got = true;
           break;
         }
@@ -407,21 +490,24 @@ __device__ __forceinline__ void persistent(const uint32_t *__restrict__ tables,
       if (!got) break;
     }
     // decode the tile
-    const uint32_t b = rfl(tile_block[t]);
-    if (b >= cfg.n_blocks) break;
+    const uint32_t b = rfl(a->tile_block[t]);
+    if (b >= a->cfg.n_blocks) break;
+    const RowBlock *blocks = a->blocks;
+    const uint32_t *tables = a->tables;
+    const uint32_t tile_cols = a->cfg.tile_cols;
     TileJob job;
     job.row0 = rfl(blocks[b].row0);
-    job.row_end = min(rfl(blocks[b].row_end), cfg.n_rows);
+    job.row_end = min(rfl(blocks[b].row_end), a->cfg.n_rows);
     const uint32_t cbeg = rfl(blocks[b].col_begin);
     const uint32_t cend = rfl(blocks[b].col_end);
     const uint32_t k = t - rfl(blocks[b].tile_begin);
     const uint32_t task = rfl(blocks[b].task);
     const bool self = rfl(blocks[b].self) != 0;
-    const TaskDesc *td = tasks + task;
+    const TaskDesc *td = a->tasks + task;
     job.slack = reinterpret_cast<const int32_t *>(tables + rfl(td->slack_off));
     job.cmin = tables + rfl(td->cmin_off);
     job.cmax = tables + rfl(td->cmax_off);
-    job.sstart = sstart_cols + rfl64(td->col_sstart_off);
+    job.sstart = a->sstart_cols + rfl64(td->col_sstart_off);
     job.col_base = rfl(td->col_base);
     job.cosine = rfl(td->sim) == SSJ_SIM_COSINE;
     job.p = rfl(td->p);
@@ -429,83 +515,57 @@ __device__ __forceinline__ void persistent(const uint32_t *__restrict__ tables,
     uint32_t c0, c1;
     job.diag = false;
     if (self) {
-      const uint32_t n_int = (job.row0 - cbeg + cfg.tile_cols - 1) / cfg.tile_cols;
+      const uint32_t n_int = (job.row0 - cbeg + tile_cols - 1) / tile_cols;
       if (k < n_int) {
-        c0 = cbeg + k * cfg.tile_cols;
-        c1 = min(c0 + cfg.tile_cols, job.row0);
+        c0 = cbeg + k * tile_cols;
+        c1 = min(c0 + tile_cols, job.row0);
       } else {
         c0 = job.row0;
         c1 = cend;
         job.diag = true;
       }
     } else {
-      c0 = cbeg + k * cfg.tile_cols;
-      c1 = min(c0 + cfg.tile_cols, cend);
+      c0 = cbeg + k * tile_cols;
+      c1 = min(c0 + tile_cols, cend);
     }
     job.first = 0;
-    if (resumed) {
+    if (resumed && col != kTileStart) {
       c0 = col;
       job.first = slab;
     }
-    resumed = false;
     job.c0 = c0;
-    job.c1 = min(c1, cfg.n_cols);
+    job.c1 = min(c1, a->cfg.n_cols);
     if (!run(job)) {
-      // the queue is full: record where this tile resumes, and stop
-      const uint32_t fcol = rfl(sink.fail_col), fslab = rfl(sink.fail_slab);
-      if (lane == 0) {
-        atomicOr(&ctr->overflow, 1u);
-        const uint32_t q = atomicAdd(&ctr->n_resume, 1u);
-        Resume rs;
-        rs.tile = t;
-        rs.col = fcol;
-        rs.slab = fslab;
-        rs.pad = 0;
-        if (q < cfg.resume_cap) resume_out[q] = rs;
-      }
-      break;
+      // the queue is full: record where this tile resumes, and take no more
+      // (the loop records what is left of the wave's resume entries)
+      if (lane == 0) atomicOr(&ctr->overflow, 1u);
+      stopped = true;
+      record(t, rfl(sink.fail_col), rfl(sink.fail_slab));
     }
   }
   sink_pad(sink);
 }
 
-__device__ __forceinline__ void sink_init(Sink &sink, uint2 *queue, JoinCounters *ctr,
-                                          const FilterConfig &cfg, uint2 *stage) {
-  sink.queue = queue;
-  sink.ctr = ctr;
-  sink.cap = cfg.cap;
-  sink.chunk = max(cfg.chunk, kStage);
-  sink.pos = 0;
-  sink.end = 0;
+__device__ __forceinline__ void sink_init(Sink &sink, uint2 *stage) {
   sink.stage = stage;
   sink.fill = 0;
   sink.first_col = 0;
   sink.first_slab = 0;
   sink.fail_col = 0;
   sink.fail_slab = 0;
+  sink.stripe = wave_index() & (args()->cfg.stripes - 1);
+  sink.pos = 0;
+  sink.end = 0;
 }
 
 // Vector-ALU filter for one bitmap width (W words, R rows per lane, U
 // columns per step).
 template <int W, int R, int U, bool COS>
-__global__ __launch_bounds__(kBlock) void k_filter(
-    const uint64_t *__restrict__ bm_rows, const uint64_t *__restrict__ bm_cols,
-    const uint32_t *__restrict__ size_rows, const uint32_t *__restrict__ size_cols,
-    const uint32_t *__restrict__ sstart_cols, const uint32_t *__restrict__ tables,
-    const TaskDesc *__restrict__ tasks, const RowBlock *__restrict__ blocks,
-    const uint32_t *__restrict__ tile_block, uint2 *__restrict__ queue,
-    JoinCounters *__restrict__ ctr, const Resume *__restrict__ resume_in,
-    Resume *__restrict__ resume_out, FilterConfig cfg) {
-  __shared__ uint2 stage[kBlock / 64][kStage];
+__global__ __launch_bounds__(kBlock) void k_filter(FilterArgs) {
+  extern __shared__ uint2 stage[];  // kStage entries per wave
   Sink sink;
-  sink_init(sink, queue, ctr, cfg, stage[threadIdx.x >> 6]);
-  persistent(tables, tasks, blocks, tile_block, sstart_cols, ctr, resume_in, resume_out, cfg,
-             sink, [&](const TileJob &jb) {
-               return run_tile<W, R, U, COS>(bm_rows, bm_cols, size_rows, size_cols, jb.sstart,
-                                             jb.col_base, jb.slack, jb.cmin, jb.cmax, jb.cosine,
-                                             jb.p, jb.q, jb.row0, jb.row_end, jb.c0, jb.c1,
-                                             jb.diag, jb.first, sink);
-             });
+  sink_init(sink, stage + (threadIdx.x >> 6) * kStage);
+  tile_loop(sink, [&](const TileJob &jb) { return run_tile<W, R, U, COS>(jb, sink); });
 }
 
 // ---------------------------------------------------------------------------
@@ -828,11 +888,11 @@ __device__ __forceinline__ bool sweep_mfma(const uint4 *__restrict__ sg_cols, ui
 // One tile on the matrix cores: rows [row0, row_end) (at most 32*RT),
 // columns [c0, c1).
 template <int W, int RT, bool COS>
-__device__ __forceinline__ bool run_tile_mfma(const uint4 *__restrict__ sg_rows,
-                                              const uint4 *__restrict__ sg_cols, uint32_t n_rows,
-                                              uint32_t n_cols, const uint32_t *__restrict__ size_rows,
-                                              const uint32_t *__restrict__ size_cols,
-                                              const TileJob &jb, Sink &sink) {
+__device__ __forceinline__ bool run_tile_mfma(const TileJob &jb, Sink &sink) {
+  const ArgPtr ka = args();
+  const uint4 *__restrict__ sg_rows = ka->sg_rows, *__restrict__ sg_cols = ka->sg_cols;
+  const uint32_t *__restrict__ size_rows = ka->size_rows, *__restrict__ size_cols = ka->size_cols;
+  const uint32_t n_rows = ka->cfg.n_rows, n_cols = ka->cfg.n_cols;
   const uint32_t lane = threadIdx.x & 63, h = lane >> 5, jr = lane & 31;
   constexpr int32_t K = 64 * W;
   MRows<W, RT> rw;
@@ -879,41 +939,28 @@ __device__ __forceinline__ bool run_tile_mfma(const uint4 *__restrict__ sg_rows,
     j = g1;
   }
   // the tile's staged pairs go out before the next tile
-  return flush(sink);
+  return flush(sink, true);
 }
 
 template <int W, int RT, bool COS>
-__global__ __launch_bounds__(kBlock) void k_filter_mfma(
-    const uint4 *__restrict__ sg_rows, const uint4 *__restrict__ sg_cols,
-    const uint32_t *__restrict__ size_rows, const uint32_t *__restrict__ size_cols,
-    const uint32_t *__restrict__ sstart_cols, const uint32_t *__restrict__ tables,
-    const TaskDesc *__restrict__ tasks, const RowBlock *__restrict__ blocks,
-    const uint32_t *__restrict__ tile_block, uint2 *__restrict__ queue,
-    JoinCounters *__restrict__ ctr, const Resume *__restrict__ resume_in,
-    Resume *__restrict__ resume_out, FilterConfig cfg) {
-  __shared__ uint2 stage[kBlock / 64][kStage];
+__global__ __launch_bounds__(kBlock) void k_filter_mfma(FilterArgs) {
+  extern __shared__ uint2 stage[];  // kStage entries per wave
   Sink sink;
-  sink_init(sink, queue, ctr, cfg, stage[threadIdx.x >> 6]);
-  persistent(tables, tasks, blocks, tile_block, sstart_cols, ctr, resume_in, resume_out, cfg,
-             sink, [&](const TileJob &jb) {
-               return run_tile_mfma<W, RT, COS>(sg_rows, sg_cols, cfg.n_rows, cfg.n_cols,
-                                                size_rows, size_cols, jb, sink);
-             });
+  sink_init(sink, stage + (threadIdx.x >> 6) * kStage);
+  tile_loop(sink, [&](const TileJob &jb) { return run_tile_mfma<W, RT, COS>(jb, sink); });
 }
 
 template <int W, int R, int U, bool COS>
 hipError_t launch_shape(dim3 grid, hipStream_t st, const FilterArgs &a) {
-  hipLaunchKernelGGL((k_filter<W, R, U, COS>), grid, dim3(kBlock), 0, st, a.bm_rows, a.bm_cols,
-                     a.size_rows, a.size_cols, a.sstart_cols, a.tables, a.tasks, a.blocks,
-                     a.tile_block, a.queue, a.ctr, a.resume_in, a.resume_out, a.cfg);
+  hipLaunchKernelGGL((k_filter<W, R, U, COS>), grid, dim3(64 * a.cfg.block_waves),
+                     a.cfg.block_waves * kStage * sizeof(uint2), st, a);
   return hipGetLastError();
 }
 
 template <int W, int RT, bool COS>
 hipError_t launch_mfma(dim3 grid, hipStream_t st, const FilterArgs &a) {
-  hipLaunchKernelGGL((k_filter_mfma<W, RT, COS>), grid, dim3(kBlock), 0, st, a.sg_rows,
-                     a.sg_cols, a.size_rows, a.size_cols, a.sstart_cols, a.tables, a.tasks,
-                     a.blocks, a.tile_block, a.queue, a.ctr, a.resume_in, a.resume_out, a.cfg);
+  hipLaunchKernelGGL((k_filter_mfma<W, RT, COS>), grid, dim3(64 * a.cfg.block_waves),
+                     a.cfg.block_waves * kStage * sizeof(uint2), st, a);
   return hipGetLastError();
 }
 
@@ -995,16 +1042,31 @@ int filter_grid_blocks() {
   return cus * 8;  // 32 waves per CU
 }
 
-hipError_t launch_filter(uint32_t padded_words, bool cosine, const FilterArgs &a,
+hipError_t launch_filter(uint32_t padded_words, bool cosine, const FilterArgs &args_in,
                          hipStream_t st) {
+  FilterArgs a = args_in;
   // a persistent grid, but no more waves than the launch has tiles or resume
   // entries to hand out (small width classes would otherwise start thousands
-  // of waves that find nothing to do); wave k takes resume entry k
-  const uint64_t need = std::max<uint64_t>(
-      std::max<uint64_t>(a.cfg.tile_hi - a.cfg.tile_lo, a.cfg.n_resume_in), 1);
-  const uint64_t waves_per_block = kBlock / 64;
-  dim3 grid((unsigned)std::min<uint64_t>((uint64_t)filter_grid_blocks(),
-                                         (need + waves_per_block - 1) / waves_per_block));
+  // of waves that find nothing to do); a direct launch has a wave for every
+  // tile of its XCDs' regions, or for every resume entry
+  const uint64_t n_tiles = a.cfg.tile_hi - a.cfg.tile_lo;
+  const uint64_t waves_per_block = a.cfg.direct ? 1 : kBlock / 64;
+  if (a.cfg.stripes == 0 || (a.cfg.stripes & (a.cfg.stripes - 1)) ||
+      a.cfg.stripes > kQueueStripes)
+    return hipErrorInvalidValue;
+  dim3 grid;
+  if (a.cfg.direct && a.cfg.n_resume_in == 0) {
+    constexpr uint64_t kTurn = kXcds * kDirectDeal;
+    grid = dim3((unsigned)(kTurn * ((n_tiles + kTurn - 1) / kTurn)));
+  } else {
+    const uint64_t need = std::max<uint64_t>(
+        a.cfg.direct ? a.cfg.n_resume_in : std::max<uint64_t>(n_tiles, a.cfg.n_resume_in), 1);
+    grid = dim3((unsigned)std::min<uint64_t>((uint64_t)filter_grid_blocks() * 4 / waves_per_block,
+                                             (need + waves_per_block - 1) / waves_per_block));
+  }
+  a.cfg.block_waves = (uint32_t)waves_per_block;
+  a.cfg.waves = grid.x * (uint32_t)waves_per_block;
+  a.cfg.chunk = std::max(a.cfg.chunk, kFilterStage);
   if (a.sg_rows || a.sg_cols) {
     if (!a.sg_rows || !a.sg_cols) return hipErrorInvalidValue;
 #define X(w, rt)                                                \

@@ -222,7 +222,7 @@ __global__ __launch_bounds__(kBlock) void k_unique_to_queue(const unsigned long 
   const unsigned long long m = __ballot(first);
   if (!m) return;
   unsigned long long base = 0;
-  if (lane == 0) base = atomicAdd(&ctr->queue_count, (unsigned long long)__popcll(m));
+  if (lane == 0) base = atomicAdd(&ctr->queue_next[0][0], (unsigned long long)__popcll(m));
   base = __shfl(base, 0, 64);
   if (first) {
     const unsigned long long k = keys[i];

@@ -178,8 +178,16 @@ __device__ __forceinline__ uint32_t wide_distance(const uint64_t *__restrict__ x
 // true pair would hold its whole round that long.
 constexpr uint32_t kLongMerge = 128;
 
-// Result keys a verification wave stages in LDS.
-constexpr uint32_t kWaveResults = 256;
+// Threads of a k_verify workgroup: every workgroup adds its results (and
+// its survivors) with one same-address atomic, and those are served one at
+// a time across the chip, so the workgroups are as large as they get (16
+// waves, 256 workgroups on the chip, against 2048 workgroups of 4 waves).
+constexpr int kVerifyBlock = 1024;
+constexpr int kVerifyWaves = kVerifyBlock / 64;
+
+// Result keys and deferred pairs a verification wave stages in LDS.
+constexpr uint32_t kWaveResults = 128;
+constexpr uint32_t kWaveLong = 128;
 
 struct VerifyArgs {
   VerifySpace rows, cols;
@@ -304,35 +312,93 @@ __device__ __forceinline__ bool verify_entry(uint32_t x, uint32_t y, const Verif
   return hit;
 }
 
+// Wave-staged items [0, n) of `from` appended to `to` at one atomic on
+// *count per wave.
+template <class T>
+__device__ __forceinline__ void append_wave(const T *from, uint32_t n, T *__restrict__ to,
+                                            unsigned long long cap, unsigned long long *count) {
+  const uint32_t lane = threadIdx.x & 63;
+  __builtin_amdgcn_wave_barrier();
+  unsigned long long base = 0;
+  if (lane == 0) base = atomicAdd(count, (unsigned long long)n);
+  base = __shfl(base, 0, 64);
+  for (uint32_t x = lane; x < n; x += 64)
+    if (base + x < cap) to[base + x] = from[x];
+  __builtin_amdgcn_wave_barrier();
+}
+
+// One reservation of the workgroup's staged items on *count: this wave's
+// first slot.  `n` is the wave's number of items, `part` one LDS word per
+// wave; every thread of the workgroup calls it.
+template <int WAVES>
+__device__ __forceinline__ unsigned long long append_block(uint32_t n, unsigned long long *part,
+                                                           unsigned long long *count) {
+  const uint32_t wv = threadIdx.x >> 6;
+  if ((threadIdx.x & 63) == 0) part[wv] = n;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    unsigned long long total = 0;
+    for (int k = 0; k < WAVES; ++k) total += part[k];
+    unsigned long long at = total ? atomicAdd(count, total) : 0ull;
+    for (int k = 0; k < WAVES; ++k) {
+      const unsigned long long nk = part[k];
+      part[k] = at;
+      at += nk;
+    }
+  }
+  __syncthreads();
+  return part[wv];
+}
+
 // The queue holds the filter waves' chunks, whose unused ends are
-// sentinels.  Wave w reads the queue's 64-entry windows w, w + W, w + 2W, ...
+// sentinels, in `stripes` stripes of cap slots (lane s of a wave keeps
+// stripe s's first window and slot count, and a window's stripe is found
+// by one ballot).  Wave w reads the queue's 64-entry windows w, w + W, w + 2W, ...
 // (W waves; a run of full chunks is spread over many waves), packs the real
 // entries into an LDS list and verifies them 64 at a time, so that every
 // lane of a verification round has a survivor (the round's length is that
 // of its longest merge).
 template <int W2, bool ONE>
-__global__ __launch_bounds__(kBlock) void k_verify(const uint2 *__restrict__ queue,
-                                                   unsigned long long cap, VerifyArgs va,
-                                                   unsigned long long *__restrict__ results,
-                                                   unsigned long long results_cap,
-                                                   JoinCounters *__restrict__ ctr) {
-  __shared__ uint2 pend[kBlock / 64][128];
-  // result keys, staged per wave and written with one reservation per
-  // workgroup at the end (or per wave when a wave's list fills): one
-  // same-address atomic per workgroup instead of one per round
-  __shared__ unsigned long long rkeys[kBlock / 64][kWaveResults];
-  __shared__ unsigned long long rbase[kBlock / 64];
+__global__ __launch_bounds__(kVerifyBlock) void k_verify(
+    const uint2 *__restrict__ queue, unsigned long long cap, uint32_t stripes, VerifyArgs va,
+    unsigned long long *__restrict__ results, unsigned long long results_cap,
+    JoinCounters *__restrict__ ctr) {
+  __shared__ uint2 pend[kVerifyWaves][128];
+  // result keys and deferred long pairs, staged per wave and written with
+  // one reservation per workgroup at the end (or per wave when a wave's
+  // list fills): one same-address atomic per workgroup instead of one per
+  // round
+  __shared__ unsigned long long rkeys[kVerifyWaves][kWaveResults];
+  __shared__ uint2 lpairs[kVerifyWaves][kWaveLong];
+  __shared__ unsigned long long rpart[kVerifyWaves], lpart[kVerifyWaves];
   __shared__ uint32_t block_surv;
   uint2 *buf = pend[threadIdx.x >> 6];
   unsigned long long *rk = rkeys[threadIdx.x >> 6];
-  uint32_t rfill = 0;
+  uint2 *lp = lpairs[threadIdx.x >> 6];
+  uint32_t rfill = 0, lfill = 0;
   const uint32_t lane = threadIdx.x & 63;
+  const unsigned long long all = cap * stripes;  // slots of the queue (and of the long pairs)
   if (threadIdx.x == 0) block_surv = 0;
-  unsigned long long count = ctr->queue_count;
-  if (count > cap) count = cap;
-  const unsigned long long windows = (count + 63) / 64;
-  const unsigned long long n_waves = (unsigned long long)gridDim.x * (kBlock / 64);
-  const unsigned long long wave = (unsigned long long)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
+  unsigned long long slots = lane < stripes ? ctr->queue_next[lane][0] : 0ull;
+  if (slots > cap) slots = cap;
+  // windows of the stripes before lane's: an exclusive scan over the lanes
+  unsigned long long first = (slots + 63) / 64;
+  const unsigned long long own_windows = first;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const unsigned long long v = __shfl_up(first, d, 64);
+    if (lane >= (uint32_t)d) first += v;
+  }
+  const unsigned long long windows = __shfl(first, 63, 64);
+  first -= own_windows;
+  if (blockIdx.x == 0 && threadIdx.x < 64) {
+    unsigned long long total = slots;
+    for (int d = 32; d >= 1; d >>= 1) total += __shfl_xor(total, d, 64);
+    if (lane == 0) ctr->queue_count = total;
+  }
+  const unsigned long long n_waves = (unsigned long long)gridDim.x * kVerifyWaves;
+  const unsigned long long wave =
+      (unsigned long long)blockIdx.x * kVerifyWaves + (threadIdx.x >> 6);
   uint32_t fill = 0, surv = 0;
   const OneTask one = ONE ? one_task(va) : OneTask{};
   auto round = [&](uint2 qe, bool ok) {
@@ -341,26 +407,20 @@ __global__ __launch_bounds__(kBlock) void k_verify(const uint2 *__restrict__ que
     const bool hit = ok && verify_entry<W2, ONE>(qe.x, qe.y, va, one, defer, key);
     const unsigned long long dm = __ballot(defer);
     if (dm) {
-      unsigned long long base = 0;
-      if (lane == 0) base = atomicAdd(&ctr->long_count, (unsigned long long)__popcll(dm));
-      base = __shfl(base, 0, 64);
-      if (defer) {
-        const unsigned long long pos = base + (unsigned long long)__popcll(dm & __lanemask_lt());
-        if (pos < cap) va.longq[pos] = qe;
+      const uint32_t n = (uint32_t)__popcll(dm);
+      if (lfill + n > kWaveLong) {
+        append_wave(lp, lfill, va.longq, all, &ctr->long_count);
+        lfill = 0;
       }
+      if (defer) lp[lfill + (uint32_t)__popcll(dm & __lanemask_lt())] = qe;
+      lfill += n;
     }
     const unsigned long long m = __ballot(hit);
     if (m) {
       const uint32_t n = (uint32_t)__popcll(m);
       if (rfill + n > kWaveResults) {
         // this wave's list is full: write it out on its own
-        __builtin_amdgcn_wave_barrier();
-        unsigned long long base = 0;
-        if (lane == 0) base = atomicAdd(&ctr->results, (unsigned long long)rfill);
-        base = __shfl(base, 0, 64);
-        for (uint32_t x = lane; x < rfill; x += 64)
-          if (base + x < results_cap) results[base + x] = rk[x];
-        __builtin_amdgcn_wave_barrier();
+        append_wave(rk, rfill, results, results_cap, &ctr->results);
         rfill = 0;
       }
       if (hit) rk[rfill + (uint32_t)__popcll(m & __lanemask_lt())] = key;
@@ -369,8 +429,13 @@ __global__ __launch_bounds__(kBlock) void k_verify(const uint2 *__restrict__ que
   };
   // the next window's entry is loaded before the current one is used
   auto entry = [&](unsigned long long w) {
-    const unsigned long long e = w * 64 + lane;
-    return w < windows && e < count ? queue[e] : make_uint2(kSentinel, kSentinel);
+    if (w >= windows) return make_uint2(kSentinel, kSentinel);
+    // the last stripe whose first window is not past w (empty stripes share
+    // theirs with the next one)
+    const int s = 63 - __clzll(__ballot(first <= w));
+    const unsigned long long e = (w - __shfl(first, s, 64)) * 64 + lane;
+    return e < __shfl(slots, s, 64) ? queue[(unsigned long long)s * cap + e]
+                                    : make_uint2(kSentinel, kSentinel);
   };
   uint2 next = entry(wave);
   for (unsigned long long w = wave; w < windows; w += n_waves) {
@@ -399,30 +464,20 @@ __global__ __launch_bounds__(kBlock) void k_verify(const uint2 *__restrict__ que
   }
   // survivors seen and the staged results: one atomic each per workgroup
   // (same-address atomics from every XCD are served one at a time)
-  const uint32_t wv = threadIdx.x >> 6;
   uint32_t s = surv;
   for (int d = 32; d >= 1; d >>= 1) s += __shfl_xor(s, d, 64);
   __syncthreads();  // block_surv was cleared at the start
-  if (lane == 0) {
-    if (s) atomicAdd(&block_surv, s);
-    rbase[wv] = rfill;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    if (block_surv) atomicAdd(&ctr->survivors, (unsigned long long)block_surv);
-    unsigned long long total = 0;
-    for (uint32_t k = 0; k < kBlock / 64; ++k) total += rbase[k];
-    unsigned long long at = total ? atomicAdd(&ctr->results, total) : 0ull;
-    for (uint32_t k = 0; k < kBlock / 64; ++k) {
-      const unsigned long long nk = rbase[k];
-      rbase[k] = at;
-      at += nk;
-    }
-  }
-  __syncthreads();
-  const unsigned long long base = rbase[wv];
+  if (lane == 0 && s) atomicAdd(&block_surv, s);
+  const unsigned long long base = append_block<kVerifyWaves>(rfill, rpart, &ctr->results);
   for (uint32_t x = lane; x < rfill; x += 64)
     if (base + x < results_cap) results[base + x] = rk[x];
+  if (va.longq) {
+    const unsigned long long at = append_block<kVerifyWaves>(lfill, lpart, &ctr->long_count);
+    for (uint32_t x = lane; x < lfill; x += 64)
+      if (at + x < all) va.longq[at + x] = lp[x];
+  }
+  if (threadIdx.x == 0 && block_surv)
+    atomicAdd(&ctr->survivors[blockIdx.x % kSurvivorStripes][0], (unsigned long long)block_surv);
 }
 
 // The deferred long pairs (their bitmap tests passed).  A few of them (up to
@@ -430,6 +485,8 @@ __global__ __launch_bounds__(kBlock) void k_verify(const uint2 *__restrict__ que
 // turn, so that each takes a few round trips.  Many: a lane per pair, 64 at
 // a time, which takes longer per pair but costs the wave less (a wave's
 // merge of one pair is about eight times the work of a lane's).
+// Result keys are staged per wave as in k_verify: with one atomic per pair the
+// 1,000,000-set join at 4/5 spent 124 us here, most of it waiting for them.
 constexpr uint32_t kLaneMode = 8;
 
 template <bool ONE>
@@ -437,7 +494,24 @@ __global__ __launch_bounds__(kBlock) void k_verify_long(unsigned long long cap, 
                                                         unsigned long long *__restrict__ results,
                                                         unsigned long long results_cap,
                                                         JoinCounters *__restrict__ ctr) {
+  constexpr int kWaves = kBlock / 64;
+  __shared__ unsigned long long rkeys[kWaves][kWaveResults];
+  __shared__ unsigned long long rpart[kWaves];
   const uint32_t lane = threadIdx.x & 63;
+  unsigned long long *rk = rkeys[threadIdx.x >> 6];
+  uint32_t rfill = 0;
+  // append the keys of the lanes that hit to the wave's list
+  auto stage = [&](bool hit, unsigned long long key) {
+    const unsigned long long m = __ballot(hit);
+    if (!m) return;
+    const uint32_t n = (uint32_t)__popcll(m);
+    if (rfill + n > kWaveResults) {
+      append_wave(rk, rfill, results, results_cap, &ctr->results);
+      rfill = 0;
+    }
+    if (hit) rk[rfill + (uint32_t)__popcll(m & __lanemask_lt())] = key;
+    rfill += n;
+  };
   unsigned long long count = ctr->long_count;
   if (count > cap) count = cap;
   const unsigned long long n_waves = (unsigned long long)gridDim.x * (kBlock / 64);
@@ -466,18 +540,9 @@ __global__ __launch_bounds__(kBlock) void k_verify_long(unsigned long long cap, 
         hit = overlap_reaches(rt + r0, a, ct + s0, c, need);
         if (hit) key = result_key(px, py, td, task, va.ib, va.jb);
       }
-      const unsigned long long m = __ballot(hit);
-      if (m) {
-        unsigned long long base = 0;
-        if (lane == 0) base = atomicAdd(&ctr->results, (unsigned long long)__popcll(m));
-        base = __shfl(base, 0, 64);
-        if (hit) {
-          const unsigned long long pos = base + (unsigned long long)__popcll(m & __lanemask_lt());
-          if (pos < results_cap) results[pos] = key;
-        }
-      }
+      stage(hit, key);
     }
-    return;
+    count = 0;  // all done
   }
   for (unsigned long long e = wave; e < count; e += n_waves) {
     const uint2 qe = va.longq[e];
@@ -495,11 +560,11 @@ __global__ __launch_bounds__(kBlock) void k_verify_long(unsigned long long cap, 
     const uint32_t *rt = ONE ? one.r_tok : rows.sides[sr].tokens;
     const uint32_t *ct = ONE ? one.c_tok : cols.sides[sc].tokens;
     const uint32_t o = wave_overlap(rt + r0, a, ct + s0, c);
-    if (o >= need && lane == 0) {
-      const unsigned long long pos = atomicAdd(&ctr->results, 1ull);
-      if (pos < results_cap) results[pos] = result_key(px, py, td, task, va.ib, va.jb);
-    }
+    stage(o >= need && lane == 0, result_key(px, py, td, task, va.ib, va.jb));
   }
+  const unsigned long long base = append_block<kWaves>(rfill, rpart, &ctr->results);
+  for (uint32_t x = lane; x < rfill; x += 64)
+    if (base + x < results_cap) results[base + x] = rk[x];
 }
 
 // Sorted keys -> pairs, and the first result of every task: the key at x
@@ -546,10 +611,10 @@ static int verify_grid_blocks() {
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
       cus <= 0)
     cus = 256;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_verify<W2, ONE>, kBlock, 0) !=
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_verify<W2, ONE>, kVerifyBlock, 0) !=
           hipSuccess ||
       per_cu <= 0)
-    per_cu = 4;
+    per_cu = 1;
   if (dev >= 0 && dev < kVerifyDevices) cached[dev].store(cus * per_cu, std::memory_order_relaxed);
   return cus * per_cu;
 }
@@ -575,18 +640,18 @@ static int verify_long_grid_blocks() {
 }
 
 template <int W2, bool ONE>
-static void launch_verify_as(const uint2 *queue, unsigned long long cap, const VerifyArgs &va,
-                             unsigned long long *results, unsigned long long results_cap,
-                             JoinCounters *ctr, hipStream_t st) {
-  hipLaunchKernelGGL((k_verify<W2, ONE>), dim3(verify_grid_blocks<W2, ONE>()), dim3(kBlock), 0,
-                     st, queue, cap, va, results, results_cap, ctr);
+static void launch_verify_as(const uint2 *queue, unsigned long long cap, uint32_t stripes,
+                             const VerifyArgs &va, unsigned long long *results,
+                             unsigned long long results_cap, JoinCounters *ctr, hipStream_t st) {
+  hipLaunchKernelGGL((k_verify<W2, ONE>), dim3(verify_grid_blocks<W2, ONE>()),
+                     dim3(kVerifyBlock), 0, st, queue, cap, stripes, va, results, results_cap, ctr);
   if (va.longq)
     hipLaunchKernelGGL((k_verify_long<ONE>), dim3(verify_long_grid_blocks<ONE>()), dim3(kBlock),
-                       0, st, cap, va, results, results_cap, ctr);
+                       0, st, cap * stripes, va, results, results_cap, ctr);
 }
 
 hipError_t launch_verify(const uint2 *queue, uint2 *longq, unsigned long long cap,
-                         VerifySpace rows, VerifySpace cols, const uint32_t *side_task,
+                         uint32_t stripes, VerifySpace rows, VerifySpace cols, const uint32_t *side_task,
                          const TaskDesc *tasks, uint32_t n_tasks, const uint32_t *tables, int ib,
                          int jb, uint32_t survivors_only, uint32_t w2,
                          unsigned long long *results, unsigned long long results_cap,
@@ -596,7 +661,7 @@ hipError_t launch_verify(const uint2 *queue, uint2 *longq, unsigned long long ca
   if ((rows.bmw == nullptr) != (cols.bmw == nullptr)) return hipErrorInvalidValue;
   if (!rows.bm2) w2 = 0;
   if (w2 != 0 && w2 != 2 && w2 != 4 && w2 != 8) return hipErrorInvalidValue;
-  if (n_tasks == 0) return hipErrorInvalidValue;
+  if (n_tasks == 0 || stripes == 0 || stripes > kQueueStripes) return hipErrorInvalidValue;
   // only pairs that passed a cascade test are deferred: they are nearly all
   // true pairs, which a lane's merge cannot leave early; without a cascade
   // most survivors are false, and a lane's merge rejects them in a few
@@ -605,14 +670,14 @@ hipError_t launch_verify(const uint2 *queue, uint2 *longq, unsigned long long ca
                       survivors_only || !rows.bm2 ? nullptr : longq};
   const bool one = n_tasks == 1;
   switch (w2 * 2 + (one ? 1 : 0)) {
-    case 0: launch_verify_as<0, false>(queue, cap, va, results, results_cap, ctr, st); break;
-    case 1: launch_verify_as<0, true>(queue, cap, va, results, results_cap, ctr, st); break;
-    case 4: launch_verify_as<2, false>(queue, cap, va, results, results_cap, ctr, st); break;
-    case 5: launch_verify_as<2, true>(queue, cap, va, results, results_cap, ctr, st); break;
-    case 8: launch_verify_as<4, false>(queue, cap, va, results, results_cap, ctr, st); break;
-    case 9: launch_verify_as<4, true>(queue, cap, va, results, results_cap, ctr, st); break;
-    case 16: launch_verify_as<8, false>(queue, cap, va, results, results_cap, ctr, st); break;
-    default: launch_verify_as<8, true>(queue, cap, va, results, results_cap, ctr, st); break;
+    case 0: launch_verify_as<0, false>(queue, cap, stripes, va, results, results_cap, ctr, st); break;
+    case 1: launch_verify_as<0, true>(queue, cap, stripes, va, results, results_cap, ctr, st); break;
+    case 4: launch_verify_as<2, false>(queue, cap, stripes, va, results, results_cap, ctr, st); break;
+    case 5: launch_verify_as<2, true>(queue, cap, stripes, va, results, results_cap, ctr, st); break;
+    case 8: launch_verify_as<4, false>(queue, cap, stripes, va, results, results_cap, ctr, st); break;
+    case 9: launch_verify_as<4, true>(queue, cap, stripes, va, results, results_cap, ctr, st); break;
+    case 16: launch_verify_as<8, false>(queue, cap, stripes, va, results, results_cap, ctr, st); break;
+    default: launch_verify_as<8, true>(queue, cap, stripes, va, results, results_cap, ctr, st); break;
   }
   return hipGetLastError();
 }

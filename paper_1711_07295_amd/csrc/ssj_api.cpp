@@ -311,11 +311,11 @@ void d2h(T *dst, const T *src, uint64_t n, hipStream_t st) {
   if (n == 0) return;
   check(hipMemcpyAsync(dst, src, n * sizeof(T), hipMemcpyDeviceToHost, st));
 }
-// The counters the host reads sit before the tile cursors: copy only those.
+// The counters the host reads sit before the queue's and the tiles': copy only those.
 template <>
 void d2h<JoinCounters>(JoinCounters *dst, const JoinCounters *src, uint64_t n, hipStream_t st) {
   if (n != 1) throw Fail{SSJ_E_DEVICE};
-  check(hipMemcpyAsync(dst, src, offsetof(JoinCounters, tile_next), hipMemcpyDeviceToHost, st));
+  check(hipMemcpyAsync(dst, src, offsetof(JoinCounters, queue_next), hipMemcpyDeviceToHost, st));
 }
 template <class T>
 void h2d(T *dst, const T *src, uint64_t n, hipStream_t st) {
@@ -1310,7 +1310,7 @@ struct JoinRun {
   const TaskDesc *d_tasks = nullptr;
   const uint32_t *d_side_task = nullptr, *d_tables = nullptr;
   uint32_t *d_tile_block = nullptr;
-  uint64_t qcap = 0;
+  uint64_t qcap = 0;             // slots of the queue, over its stripes
   uint32_t dense_chunk = 0;
   uint2 *queue = nullptr;
   Resume *res_a = nullptr, *res_b = nullptr;
@@ -1333,6 +1333,11 @@ struct RoundTimes {
   hipEvent_t graph_ev[2] = {nullptr, nullptr};  // around a prepared join's graph
 };
 
+// Whether the tiles of width slot k get a wave each (kDirectTiles).
+bool direct_slot(const Plan &pl, uint32_t k) {
+  return pl.tile_hi[k] - pl.tile_lo[k] <= kDirectTiles;
+}
+
 // One filter/verify round: a filter launch per width slot, then the
 // verification of the queue.  Timed when tm is given (L then runs at once).
 void launch_round(const JoinRun &jr, FilterConfig cfg, uint2 *queue, uint64_t qcap,
@@ -1340,7 +1345,10 @@ void launch_round(const JoinRun &jr, FilterConfig cfg, uint2 *queue, uint64_t qc
                   uint64_t res_cap, hipStream_t st, Launcher *L, RoundTimes *tm) {
   const Plan &pl = jr.pl;
   const Space &R = *jr.R, &C = *jr.C;
-  cfg.cap = qcap;
+  const uint32_t stripes = queue_stripes(qcap);
+  const uint64_t scap = qcap / stripes;  // slots of one stripe
+  cfg.cap = (uint32_t)scap;
+  cfg.stripes = stripes;
   // one launch per width slot; after an overflow the later launches of
   // the round leave at once and resume in the next round
   for (uint32_t k = 0; k < pl.n_slots; ++k) {
@@ -1349,6 +1357,7 @@ void launch_round(const JoinRun &jr, FilterConfig cfg, uint2 *queue, uint64_t qc
     cfg.tile_hi = pl.tile_hi[k];
     cfg.tile_cols = pl.slot_tile_cols[k];
     cfg.cls = k;
+    cfg.direct = direct_slot(pl, k) ? 1u : 0u;
     cfg.chunk = jr.automatic && pl.slot_words[k] < kCascadeWords ? kFilterStage : dense_chunk;
     const uint32_t w = pl.slot_words[k];
     const bool mf = pl.slot_mfma[k], cos = jr.any_cosine;
@@ -1376,7 +1385,7 @@ void launch_round(const JoinRun &jr, FilterConfig cfg, uint2 *queue, uint64_t qc
   const uint32_t so = jr.jc.survivors_only ? 1u : 0u;
   JoinCounters *ctr = jr.ctr;
   go(L, st, [=](hipStream_t s) {
-    return launch_verify(queue, queue + qcap, qcap, vr, vc, side_task, tasks, n_tasks, tables,
+    return launch_verify(queue, queue + qcap, scap, stripes, vr, vc, side_task, tasks, n_tasks, tables,
                          ib, jb, so, w2, results, res_cap, ctr, s);
   });
   if (tm) check(hipEventRecord(tm->verify.back().ev[1], st));
@@ -1731,12 +1740,20 @@ void join_begin(Space &R, Space &C, const std::vector<TaskIn> &tasks, const Join
   // and their waves take up to 1024.
   static_assert(kFilterStage <= 4096, "the queue holds at least 4096 entries");
   uint64_t qcap = std::max<uint64_t>(4096, std::min<uint64_t>(jc.cap, pl.band_pairs + 1));
+  // slots of a stripe are counted in 32 bits
+  qcap = std::min<uint64_t>(qcap, (uint64_t)kQueueStripes << 30);
   uint32_t dense_chunk =
       (uint32_t)std::min<uint64_t>(1024, std::max<uint64_t>(kFilterStage, qcap / 64));
   // the queue, then as many slots for the long pairs verification defers
   uint2 *queue = ar.alloc<uint2>(2 * qcap);
-  const uint32_t max_waves = (uint32_t)filter_grid_blocks() * (kBlock / 64);
-  Resume *res_a = ar.alloc<Resume>(max_waves), *res_b = ar.alloc<Resume>(max_waves);
+  // Resume entries of a round: the launches run one after the other, and the
+  // first that finds the queue full is the only one with tiles begun -- at
+  // most one per wave of a persistent launch, each tile of a direct one --
+  // while later direct launches record every tile they had.
+  uint32_t max_resume = (uint32_t)filter_grid_blocks() * (kBlock / 64);
+  for (uint32_t k = 0; k < pl.n_slots; ++k)
+    if (direct_slot(pl, k)) max_resume += pl.tile_hi[k] - pl.tile_lo[k];
+  Resume *res_a = ar.alloc<Resume>(max_resume), *res_b = ar.alloc<Resume>(max_resume);
   uint64_t res_cap = std::max<uint64_t>(qcap, 1024);
   unsigned long long *results = ar.alloc<unsigned long long>(res_cap);
   // result keys (task, i, j): i of the row side, j of the column side
@@ -1793,8 +1810,7 @@ void join_begin(Space &R, Space &C, const std::vector<TaskIn> &tasks, const Join
   cfg.n_cols = (uint32_t)C.n;
   cfg.n_tiles = pl.n_tiles;
   cfg.n_blocks = (uint32_t)nB;
-  cfg.resume_cap = max_waves;
-  cfg.cap = qcap;
+  cfg.resume_cap = max_resume;
   cfg.n_resume_in = 0;
   if (pl.n_tiles)
     launch_round(jr, cfg, queue, qcap, dense_chunk, res_a, res_b, results, res_cap, st, L, tm);
@@ -1838,7 +1854,8 @@ void join_end(const JoinRun &jr, Arena &ar, hipStream_t st, RoundTimes &tm, Time
       if (ctr_h.error & kErrUnsorted) throw Fail{SSJ_E_UNSORTED};
       queue_slots += std::min<uint64_t>(ctr_h.queue_count, qcap);
       results_n = ctr_h.results;
-      if (results_n > res_cap) throw Fail{SSJ_E_DEVICE};  // cannot happen: capacity grows first
+      // neither can happen: capacity grows first, and max_resume holds every tile
+      if (results_n > res_cap || ctr_h.n_resume > cfg.resume_cap) throw Fail{SSJ_E_DEVICE};
       if (!ctr_h.overflow) break;
       // drain done; a queue the library sized itself grows for the next round
       if (!jc.cap_fixed && qcap < std::min<uint64_t>(kMaxQueue, pl.band_pairs + 1)) {
@@ -1938,7 +1955,7 @@ void join_end(const JoinRun &jr, Arena &ar, hipStream_t st, RoundTimes &tm, Time
           results = nr;
           res_cap = ncap;
         }
-        check(launch_verify(pqueue, pqueue + ccap, ccap, vrows, vcols, d_side_task, d_tasks,
+        check(launch_verify(pqueue, pqueue + ccap, ccap, 1, vrows, vcols, d_side_task, d_tasks,
                             n_tasks, d_tables, ib, jb, jc.survivors_only ? 1u : 0u, w2, results,
                             res_cap, ctr, st));
         d2h(&ctr_h, ctr, 1, st);
@@ -1980,7 +1997,7 @@ void join_end(const JoinRun &jr, Arena &ar, hipStream_t st, RoundTimes &tm, Time
   sync(st);
   if (stats) {
     stats->band_pairs = pl.band_pairs;
-    stats->survivors = ctr_h.survivors;
+    for (const auto &v : ctr_h.survivors) stats->survivors += v[0];
     stats->results = results_n;
     stats->filter_launches = tm.launches;
     stats->b_bits = jc.b_bits;

@@ -24,21 +24,39 @@ constexpr uint32_t kParts = 64; // tile cursors per width class, kParts / kXcds 
 // Width classes of one join (one filter launch each).
 constexpr uint32_t kMaxClasses = 6;
 
+// The survivor queue is cut into up to kQueueStripes stripes of equal
+// capacity, each with a slot counter of its own: same-address atomics from
+// every XCD are served one at a time, so that one counter for every wave of
+// a launch would hold the launch up.
+constexpr uint32_t kQueueStripes = 64;
+constexpr uint64_t kStripeMin = 16384;  // least slots of a stripe
+// Stripes of a queue of cap slots, a power of two.
+inline uint32_t queue_stripes(uint64_t cap) {
+  uint32_t s = kQueueStripes;
+  while (s > 1 && cap / s < kStripeMin) s >>= 1;
+  return s;
+}
+// Counters of the survivors seen, by workgroup number.
+constexpr uint32_t kSurvivorStripes = 8;
+
 // Counters of one filter/verify round, in device memory.
 struct JoinCounters {
-  unsigned long long queue_count;   // slots reserved in the survivor queue
-  unsigned long long survivors;     // real survivors seen by verification
+  unsigned long long queue_count;   // slots reserved in the survivor queue (set by verification)
   unsigned long long results;       // pairs written to the result buffer
   unsigned long long long_count;    // long pairs deferred by this round's verification
   uint32_t overflow;                // the queue filled during this filter launch
   uint32_t n_resume;                // resume entries written this launch
   uint32_t error;                   // validation error bits (kErr*)
   uint32_t max_size;                // largest set size seen
+  // real survivors seen by verification, each counter in its own line
+  alignas(128) unsigned long long survivors[kSurvivorStripes][16];
+  // The host reads only the fields above.
+  // slots reserved in each stripe of the queue, each in its own line
+  alignas(128) unsigned long long queue_next[kQueueStripes][16];
   // Tile cursors: each width class's tile range is cut into kXcds
   // contiguous regions, one per XCD, and each region's tiles are dealt to
   // kParts / kXcds sub-cursors; a cursor counts the tiles it has handed
-  // out.  Each sits in its own 128-byte line.  The host reads only the
-  // fields above.
+  // out.  Each sits in its own 128-byte line.
   alignas(128) uint32_t tile_next[kMaxClasses][kParts][32];
 };
 
@@ -116,12 +134,14 @@ struct RowBlock {
   uint32_t pad;
 };
 
-// A tile to resume after a queue drain: tile index, first column, and
+// A tile to resume after a queue drain: tile index, first column (kTileStart:
+// the whole tile is still to do), and
 //  - vector-ALU kernel: the first slab of rows (rows r*64 .. r*64+63 of the
 //    block) of that column still to be written;
 //  - matrix-core kernel: `col` starts a step of 32 columns and `slab` counts
 //    the kept pairs of that step already written (in the step's fixed
 //    emission order).
+constexpr uint32_t kTileStart = 0xFFFFFFFFu;
 struct Resume {
   uint32_t tile;
   uint32_t col;
@@ -139,12 +159,20 @@ struct FilterConfig {
   uint32_t n_blocks;
   uint32_t resume_cap;    // entries of the resume buffers
   uint32_t cls;           // width class (selects the tile cursors)
-  unsigned long long cap; // survivor queue capacity (entries)
+  uint32_t cap;           // capacity of one stripe of the survivor queue (entries)
+  uint32_t waves;         // waves of the launch (set by launch_filter)
   uint32_t tile_lo;       // this launch's tile range [tile_lo, tile_hi)
   uint32_t tile_hi;
   uint32_t chunk;         // queue slots a wave reserves at a time (kFilterStage..cap)
-  uint32_t pad;
+  uint32_t stripes;       // stripes of the queue, a power of two
+  uint32_t direct;        // 1: one wave per tile, no cursors
+  uint32_t block_waves;   // waves of a workgroup (set by launch_filter)
 };
+
+// A launch of at most this many tiles starts one wave per tile and leaves
+// their balance to the workgroup dispatch (FilterConfig::direct); see
+// launch_filter.
+constexpr uint32_t kDirectTiles = 16384;
 
 // ---------------------------------------------------------------- launchers
 // All launchers enqueue on `st` and return hipSuccess or the launch error.
@@ -356,11 +384,12 @@ struct VerifySpace {
 // set, or both NULL for no second test); rows.bmw and cols.bmw likewise for
 // the wide test.  n_tasks: tasks of the call (>= 1); the column of an entry
 // lies in its task's column side.
-// longq (optional, cap entries, ctr->long_count zero): the pairs of long
+// longq (optional, stripes * cap entries, ctr->long_count zero): the pairs of long
 // sets that pass the bitmap tests are merged there by whole waves, in a
 // second launch on the same stream.
+// The queue has `stripes` stripes of cap slots each.
 hipError_t launch_verify(const uint2 *queue, uint2 *longq, unsigned long long cap,
-                         VerifySpace rows, VerifySpace cols, const uint32_t *side_task,
+                         uint32_t stripes, VerifySpace rows, VerifySpace cols, const uint32_t *side_task,
                          const TaskDesc *tasks, uint32_t n_tasks, const uint32_t *tables, int ib,
                          int jb, uint32_t survivors_only, uint32_t w2,
                          unsigned long long *results, unsigned long long results_cap,
@@ -421,7 +450,7 @@ hipError_t launch_probe_count(const ProbeArgs &a, uint64_t n_rows, uint32_t *cou
 hipError_t launch_probe_fill(const ProbeArgs &a, uint64_t x0, uint64_t x1,
                              const unsigned long long *row_off, unsigned long long base,
                              unsigned long long *out, hipStream_t st);
-// sorted candidate keys -> distinct queue entries (appended at queue_count)
+// sorted candidate keys -> distinct queue entries (appended to stripe 0)
 hipError_t launch_unique_to_queue(const unsigned long long *keys, uint64_t n, uint2 *queue,
                                   JoinCounters *ctr, hipStream_t st);
 
