@@ -55,10 +55,53 @@ __device__ __forceinline__ ArgPtr args() {
   return a;
 }
 
+// Uniform data that is not written while the kernel runs (column bitmaps,
+// sizes, group starts, the plan) is read through the constant address space:
+// uniform loads from it always become scalar loads (s_load), whatever the
+// slow path stores.
+typedef const __attribute__((address_space(4))) uint32_t *const_u32_ptr;
+
+template <class T>
+__device__ __forceinline__ const __attribute__((address_space(4))) T *as_const(const T *p) {
+  return (const __attribute__((address_space(4))) T *)(p);
+}
+
 // Index of this wave in the launch: workgroups of four waves, or of one in a
 // direct launch.
 __device__ __forceinline__ uint32_t wave_index() {
   return rfl(blockIdx.x * args()->cfg.block_waves + (threadIdx.x >> 6));
+}
+
+// A run of columns [j, end) of sizes lo .. hi that one sweep takes: one size
+// group, or, where a group has fewer than kRunCols columns (the sparse tail
+// of the size distribution), the groups of sizes up to lo + lo / 32 with
+// it.  Every run starts with a chain of dependent loads (size, group starts,
+// thresholds, first columns) of a few microseconds that its few steps
+// cannot hide: with a run per group, a tile of a few hundred columns of
+// 200 .. 500 tokens took 200 us and its launch waited for it.
+//
+// A run of several sizes is tested against the loosest of its thresholds: the
+// slack a + c - 2 omin(a, c) falls nowhere by more than 1 as c grows inside
+// the length band (omin is the ceiling of something that grows by at most
+// 1/2 per token there), so slack(a, hi) + 1 bounds them.  The pairs it
+// lets through are then tested at their own sizes.
+struct ColRun {
+  uint32_t lo, hi, end;
+};
+constexpr uint32_t kRunCols = 64;
+
+__device__ __forceinline__ ColRun col_run(const_u32_ptr sstart, uint32_t col_base,
+                                          uint32_t max_size, uint32_t c, uint32_t j, uint32_t c1) {
+  const uint32_t wide = min(c + (c >> kRunShift), max_size);
+  const uint32_t e1 = col_base + sstart[c + 1], e2 = col_base + sstart[wide + 1];
+  const bool several = e1 < j + kRunCols && wide > c;
+  ColRun r;
+  r.lo = c;
+  r.hi = several ? wide : c;
+  // no more of the wider sizes than fill the run: a group that is long enough
+  // gets its own threshold
+  r.end = min(max(several ? min(e2, j + kRunCols) : e1, j + 1), c1);  // advances
+  return r;
 }
 
 template <int W, int R>
@@ -82,11 +125,14 @@ constexpr uint32_t kStage = kFilterStage;
 
 struct Sink {
   uint2 *stage;                // this wave's kStage LDS entries
+  int16_t *dots;               // this wave's 1024 LDS dot products (matrix cores)
   uint32_t fill;               // entries staged (wave-uniform)
   uint32_t first_col;          // (column, row slab) of the first staged entry
   uint32_t first_slab;
+  uint32_t first_end;          // end of the run of columns of that entry's step (matrix cores)
   uint32_t fail_col;           // resume point, set when the queue fills
   uint32_t fail_slab;
+  uint32_t fail_end;
   uint32_t stripe;             // the wave's stripe of the queue
   uint32_t pos, end;           // the wave's reserved slots [pos, end) of that stripe
 };
@@ -137,6 +183,7 @@ __device__ __forceinline__ bool flush(Sink &s, bool last = false) {
       s.fill = 0;
       s.fail_col = s.first_col;
       s.fail_slab = s.first_slab;
+      s.fail_end = s.first_end;
       return false;
     }
   }
@@ -148,6 +195,59 @@ __device__ __forceinline__ bool flush(Sink &s, bool last = false) {
   s.fill = 0;
   return true;
 }
+
+// What a wave needs to run one tile.
+struct TileJob {
+  uint32_t row0, row_end, c0, c1;
+  bool diag;
+  uint32_t first;  // resumed inside the tile: first slab (vector ALU) or pairs to skip (MFMA)
+  uint32_t end;    // ... and the end of the step's run (MFMA), else 0
+  const int32_t *slack;
+  const uint32_t *cmin, *cmax;
+  const_u32_ptr sstart;
+  uint32_t col_base, col_max;  // first column and largest size of the column space
+  bool cosine;
+  uint32_t p, q;
+  float t;         // p / q
+};
+
+// Largest slack a + c' - 2 omin(a, c') a row of size a can have with a column of
+// size c' in [lo, hi], all inside the band: exact for lo == hi, else at most
+// 1 above slack(a, hi) (see ColRun).  Cosine's least overlap, the ceiling of
+// t sqrt(a c), is bounded below in single precision (relative error of the
+// three roundings and the root below 1e-6), so its slack is always a bound;
+// the slow path decides each pair.
+template <bool COS>
+__device__ __forceinline__ int32_t run_slack(const TileJob &jb, uint32_t a, uint32_t lo,
+                                             uint32_t hi) {
+  const int32_t more = hi > lo ? 1 : 0;
+  if (COS && jb.cosine) {
+    const float x = jb.t * sqrtf((float)a * (float)hi) * (1.0f - 1.0e-6f);
+    return (int32_t)(a + hi) - 2 * (int32_t)ceilf(x) + more;
+  }
+  return jb.slack[a + hi] + more;
+}
+
+// Whether a pair of sizes a and c inside the band, h differing bits, is kept:
+// h <= a + c - 2 omin(a, c).  For Cosine: half of a + c - h, the overlap
+// bound, reaches the threshold.
+template <bool COS>
+__device__ __forceinline__ bool pair_kept(const TileJob &jb, uint32_t a, uint32_t c, int32_t h) {
+  if (COS && jb.cosine) {
+    const int32_t s = (int32_t)(a + c) - h;
+    return s >= 0 && cosine_reaches((uint32_t)s >> 1, a, c, jb.p, jb.q);
+  }
+  return h <= jb.slack[a + c];
+}
+
+// What a step's slow path needs when the run's thresholds are only bounds.
+template <int R>
+struct Exact {
+  bool bound;
+  const uint32_t (&bias)[R];
+  const uint32_t *size_cols;
+  const TileJob *job;
+};
 
 // popcount(x) + acc as one v_bcnt_u32_b32.  Written out so that the sum over
 // a bitmap's words stays one accumulating chain (the compiler would otherwise
@@ -175,9 +275,9 @@ __device__ __forceinline__ uint32_t biased_distance(const Rows<W, R> &rw, const 
 // slab) mask at a time in (column, slab) order, from the biased distances
 // the step computed.  False when the queue filled (resume point in the
 // sink).
-template <int W, int R, int U>
+template <int W, int R, int U, bool COS>
 __device__ __forceinline__ bool emit(const Rows<W, R> &rw, const uint32_t (&d)[U][R], uint32_t j,
-                                     Sink &sink) {
+                                     const Exact<R> &ex, Sink &sink) {
   static_assert(U * R <= 32, "one word holds the step's kept flags");
   const unsigned long long below = __lanemask_lt();
   // bit u*R + r: this lane's pair (column j + u, row slab r) is kept; one
@@ -186,6 +286,19 @@ __device__ __forceinline__ bool emit(const Rows<W, R> &rw, const uint32_t (&d)[U
 #pragma unroll
   for (int x = U * R - 1; x >= 0; --x)
     kb = (kb << 1) | ((int32_t)d[x / R][x % R] < 0 ? 1u : 0u);
+  if (ex.bound) {
+    // each kept pair at its own sizes.  The
+    // biased distance is bias + h, so h = d - bias.
+#pragma unroll
+    for (int x = 0; x < U * R; ++x) {
+      const uint32_t c = as_const(ex.size_cols)[j + x / R];
+      const uint32_t h = d[x / R][x % R] - ex.bias[x % R];
+      if (((kb >> x) & 1u) &&
+          !(c >= rw.cmn[x % R] && c <= rw.cmx[x % R] &&
+            pair_kept<COS>(*ex.job, rw.size[x % R], c, (int32_t)h)))
+        kb &= ~(1u << x);
+    }
+  }
   const uint32_t row_slab0 = rw.idx[0];  // this lane's row in slab r: + 64 r
 #pragma unroll 1
   for (uint32_t x = 0; x < (uint32_t)(U * R); ++x) {
@@ -207,20 +320,11 @@ __device__ __forceinline__ bool emit(const Rows<W, R> &rw, const uint32_t (&d)[U
   return true;
 }
 
-// Column bitmaps are read through the constant address space: they are not
-// written while the kernel runs, and uniform loads from that space always
-// become scalar loads (s_load), whatever the slow path stores.
-typedef const __attribute__((address_space(4))) uint32_t *const_u32_ptr;
-
-__device__ __forceinline__ const_u32_ptr as_const(const uint64_t *p) {
-  return (const_u32_ptr)(p);
-}
-
 // Bitmaps of columns [j, j + U) into SGPRs.
 template <int W, int U>
 __device__ __forceinline__ void load_cols(const uint64_t *__restrict__ bm_cols, uint32_t j,
                                           uint32_t (&cb)[U][2 * W]) {
-  const_u32_ptr p = as_const(bm_cols + (size_t)j * W);
+  const_u32_ptr p = (const_u32_ptr)as_const(bm_cols + (size_t)j * W);
 #pragma unroll
   for (int u = 0; u < U; ++u)
 #pragma unroll
@@ -240,8 +344,8 @@ __device__ __forceinline__ uint32_t after(uint32_t j) {
 // whether any is kept; only then does the slow path stage them.  On a
 // diagonal tile a pair off the lower triangle (j >= i) is made positive.
 // False when the queue filled.
-template <int W, int R, int U, bool DIAG>
-__device__ __forceinline__ bool step(const Rows<W, R> &rw, const uint32_t (&bias)[R],
+template <int W, int R, int U, bool DIAG, bool COS>
+__device__ __forceinline__ bool step(const Rows<W, R> &rw, const Exact<R> &ex,
                                      const uint32_t (&cb)[U][2 * W], uint32_t j, Sink &sink) {
   uint32_t d[U][R];
   uint32_t acc = 0;
@@ -249,23 +353,25 @@ __device__ __forceinline__ bool step(const Rows<W, R> &rw, const uint32_t (&bias
   for (int u = 0; u < U; ++u)
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      uint32_t h = biased_distance<W, R>(rw, cb[u], r, bias[r]);
+      uint32_t h = biased_distance<W, R>(rw, cb[u], r, ex.bias[r]);
       if (DIAG) h = j + u < rw.idx[r] ? h : 0u;
       d[u][r] = h;
       acc |= h;
     }
-  if (__ballot((int32_t)acc < 0)) return emit<W, R, U>(rw, d, j, sink);
+  if (__ballot((int32_t)acc < 0)) return emit<W, R, U, COS>(rw, d, j, ex, sink);
   return true;
 }
 
-// Columns [j, g1) of one size group.
-template <int W, int R, int U, bool DIAG>
+// Columns [j, g1) of one run.
+template <int W, int R, int U, bool DIAG, bool COS>
 __device__ __forceinline__ bool sweep(const uint64_t *__restrict__ bm_cols, const Rows<W, R> &rw,
                                       const int32_t (&thr)[R], uint32_t j, uint32_t g1,
-                                      Sink &sink) {
+                                      bool bound, const uint32_t *size_cols,
+                                      const TileJob &jb, Sink &sink) {
   uint32_t bias[R];
 #pragma unroll
   for (int r = 0; r < R; ++r) bias[r] = (uint32_t)(-thr[r] - 1);
+  const Exact<R> ex{bound, bias, size_cols, &jb};
   // Scalar loads may return out of order, so a wave can only wait for all
   // of them.  Two register buffers alternate: the wait for the current
   // step's columns comes before the next step's load is issued (the next
@@ -278,33 +384,21 @@ __device__ __forceinline__ bool sweep(const uint64_t *__restrict__ bm_cols, cons
     if (j + U > g1) break;
     const uint32_t jb = after(j + U);
     if (jb + U <= g1) load_cols<W, U>(bm_cols, jb, bb);
-    if (!step<W, R, U, DIAG>(rw, bias, ba, j, sink)) return false;
+    if (!step<W, R, U, DIAG, COS>(rw, ex, ba, j, sink)) return false;
     j += U;
     if (j + U > g1) break;
     const uint32_t ja = after(j + U);
     if (ja + U <= g1) load_cols<W, U>(bm_cols, ja, ba);
-    if (!step<W, R, U, DIAG>(rw, bias, bb, j, sink)) return false;
+    if (!step<W, R, U, DIAG, COS>(rw, ex, bb, j, sink)) return false;
     j += U;
   }
   for (; j < g1; ++j) {
     uint32_t cb[1][2 * W];
     load_cols<W, 1>(bm_cols, j, cb);
-    if (!step<W, R, 1, DIAG>(rw, bias, cb, j, sink)) return false;
+    if (!step<W, R, 1, DIAG, COS>(rw, ex, cb, j, sink)) return false;
   }
   return true;
 }
-
-// What a wave needs to run one tile.
-struct TileJob {
-  uint32_t row0, row_end, c0, c1;
-  bool diag;
-  uint32_t first;  // resumed inside the tile: first slab (vector ALU) or pairs to skip (MFMA)
-  const int32_t *slack;
-  const uint32_t *cmin, *cmax, *sstart;
-  uint32_t col_base;
-  bool cosine;
-  uint32_t p, q;
-};
 
 // One tile: rows [row0, row_end) of a row block (at most 64*R of them, R per
 // lane, interleaved by 64), columns [c0, c1).  Returns false when the queue
@@ -315,8 +409,6 @@ __device__ __forceinline__ bool run_tile(const TileJob &jb, Sink &sink) {
   const uint64_t *__restrict__ bm_rows = ka->bm_rows, *__restrict__ bm_cols = ka->bm_cols;
   const uint32_t *__restrict__ size_rows = ka->size_rows, *__restrict__ size_cols = ka->size_cols;
   const uint32_t *__restrict__ cmin = jb.cmin, *__restrict__ cmax = jb.cmax;
-  const uint32_t *__restrict__ sstart_cols = jb.sstart;
-  const int32_t *__restrict__ slack = jb.slack;
   const uint32_t col_base = jb.col_base, row0 = jb.row0, row_end = jb.row_end, c0 = jb.c0,
                  c1 = jb.c1;
   const bool diag = jb.diag;
@@ -344,30 +436,36 @@ __device__ __forceinline__ bool run_tile(const TileJob &jb, Sink &sink) {
     }
   }
   uint32_t j = c0;
+  uint32_t c = j < c1 ? as_const(size_cols)[j] : 0u;
   while (j < c1) {
-    const uint32_t c = rfl(size_cols[j]);
-    const uint32_t g1 = min(max(col_base + rfl(sstart_cols[c + 1]), j + 1), c1);  // advances
+    const ColRun run = col_run(jb.sstart, col_base, jb.col_max, c, j, c1);
+    const bool bound = run.hi > run.lo || (COS && jb.cosine);  // thresholds are bounds only
     int32_t thr[R];
     bool any_ok = false;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      const bool in_band = c >= rw.cmn[r] && c <= rw.cmx[r];
+      const bool in_band = run.lo <= rw.cmx[r] && run.hi >= rw.cmn[r];
       if (!in_band) thr[r] = -1;
-      else if (COS && jb.cosine) thr[r] = cosine_slack(rw.size[r], c, jb.p, jb.q);
-      else thr[r] = slack[rw.size[r] + c];
+      else thr[r] = run_slack<COS>(jb, rw.size[r], run.lo, min(run.hi, rw.cmx[r]));
       any_ok |= in_band;
     }
+    // the next run's first size, while this run is swept
+    if (run.end < c1) c = as_const(size_cols)[run.end];
     // resumed inside column j: its slabs below first_slab are already queued,
     // so column j runs alone with those slabs masked off
-    const uint32_t gend = first_slab ? j + 1 : g1;
+    const uint32_t gend = first_slab ? j + 1 : run.end;
+    if (first_slab && gend < c1) c = as_const(size_cols)[gend];
+    // a masked slab keeps nothing, also not at a pair's own sizes: -1 is
+    // below every distance
 #pragma unroll
     for (int r = 0; r < R; ++r)
       if ((uint32_t)r < first_slab) thr[r] = -1;
     first_slab = 0;
     if (__ballot(any_ok)) {
-      const bool ok =
-          diag ? sweep<W, R, U, true>(bm_cols, rw, thr, j, gend, sink)
-               : sweep<W, R, U, false>(bm_cols, rw, thr, j, gend, sink);
+      const bool ok = diag ? sweep<W, R, U, true, COS>(bm_cols, rw, thr, j, gend, bound,
+                                                       size_cols, jb, sink)
+                           : sweep<W, R, U, false, COS>(bm_cols, rw, thr, j, gend, bound,
+                                                        size_cols, jb, sink);
       if (!ok) return false;
     }
     j = gend;
@@ -399,12 +497,12 @@ template <class Run>
 __device__ __forceinline__ void tile_loop(Sink &sink, Run &&run) {
   const uint32_t lane = threadIdx.x & 63;
   const uint32_t wave = wave_index();
-  uint32_t t = 0, col = 0, slab = 0;
+  uint32_t t = 0, col = 0, slab = 0, end = 0;
   uint32_t entry = wave;
   bool fresh = true;     // direct: the wave's tile is still to take
   bool stopped = false;  // this wave found the queue full
-  // the tile stays to be done from (c, s) on
-  auto record = [&](uint32_t tile, uint32_t c, uint32_t s) {
+  // the tile stays to be done from (c, s) on, a step of a run that ends at e
+  auto record = [&](uint32_t tile, uint32_t c, uint32_t s, uint32_t e) {
     const ArgPtr a = args();
     if (lane == 0) {
       const uint32_t q = atomicAdd(&a->ctr->n_resume, 1u);
@@ -412,7 +510,7 @@ __device__ __forceinline__ void tile_loop(Sink &sink, Run &&run) {
       rs.tile = tile;
       rs.col = c;
       rs.slab = s;
-      rs.pad = 0;
+      rs.end = e;
       if (q < a->cfg.resume_cap) a->resume_out[q] = rs;
     }
   };
@@ -435,10 +533,11 @@ __device__ __forceinline__ void tile_loop(Sink &sink, Run &&run) {
     const uint32_t n_resume = min(a->cfg.n_resume_in, a->cfg.resume_cap);
     bool resumed = false;
     while (entry < n_resume && !resumed) {
-      const Resume *in = a->resume_in + entry;
+      const auto *in = as_const(a->resume_in) + entry;
       t = rfl(in->tile);
       col = rfl(in->col);
       slab = rfl(in->slab);
+      end = rfl(in->end);
       resumed = t >= tile_lo && t < tile_hi;
       entry += a->cfg.waves;
     }
@@ -446,7 +545,7 @@ __device__ __forceinline__ void tile_loop(Sink &sink, Run &&run) {
         stopped ||
         rfl(__hip_atomic_load(&ctr->overflow, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) != 0;
     if (resumed && full) {
-      record(t, col, slab);
+      record(t, col, slab, end);
       continue;
     }
     if (!resumed && a->cfg.direct) {
@@ -458,7 +557,7 @@ __device__ __forceinline__ void tile_loop(Sink &sink, Run &&run) {
       if (k >= n_tiles) break;
       t = tile_lo + k;
       if (full) {
-        record(t, kTileStart, 0);
+        record(t, kTileStart, 0, 0);
         break;
       }
     } else if (!resumed) {
@@ -490,9 +589,9 @@ __device__ __forceinline__ void tile_loop(Sink &sink, Run &&run) {
       if (!got) break;
     }
     // decode the tile
-    const uint32_t b = rfl(a->tile_block[t]);
+    const uint32_t b = as_const(a->tile_block)[t];
     if (b >= a->cfg.n_blocks) break;
-    const RowBlock *blocks = a->blocks;
+    const auto *blocks = as_const(a->blocks);
     const uint32_t *tables = a->tables;
     const uint32_t tile_cols = a->cfg.tile_cols;
     TileJob job;
@@ -503,15 +602,17 @@ __device__ __forceinline__ void tile_loop(Sink &sink, Run &&run) {
     const uint32_t k = t - rfl(blocks[b].tile_begin);
     const uint32_t task = rfl(blocks[b].task);
     const bool self = rfl(blocks[b].self) != 0;
-    const TaskDesc *td = a->tasks + task;
+    const auto *td = as_const(a->tasks) + task;
     job.slack = reinterpret_cast<const int32_t *>(tables + rfl(td->slack_off));
     job.cmin = tables + rfl(td->cmin_off);
     job.cmax = tables + rfl(td->cmax_off);
-    job.sstart = a->sstart_cols + rfl64(td->col_sstart_off);
+    job.sstart = as_const(a->sstart_cols) + rfl64(td->col_sstart_off);
     job.col_base = rfl(td->col_base);
+    job.col_max = a->cfg.col_max_size;
     job.cosine = rfl(td->sim) == SSJ_SIM_COSINE;
     job.p = rfl(td->p);
     job.q = rfl(td->q);
+    job.t = (float)job.p / (float)job.q;
     uint32_t c0, c1;
     job.diag = false;
     if (self) {
@@ -529,9 +630,11 @@ __device__ __forceinline__ void tile_loop(Sink &sink, Run &&run) {
       c1 = min(c0 + tile_cols, cend);
     }
     job.first = 0;
+    job.end = 0;
     if (resumed && col != kTileStart) {
       c0 = col;
       job.first = slab;
+      job.end = end;
     }
     job.c0 = c0;
     job.c1 = min(c1, a->cfg.n_cols);
@@ -540,19 +643,22 @@ __device__ __forceinline__ void tile_loop(Sink &sink, Run &&run) {
       // (the loop records what is left of the wave's resume entries)
       if (lane == 0) atomicOr(&ctr->overflow, 1u);
       stopped = true;
-      record(t, rfl(sink.fail_col), rfl(sink.fail_slab));
+      record(t, rfl(sink.fail_col), rfl(sink.fail_slab), rfl(sink.fail_end));
     }
   }
   sink_pad(sink);
 }
 
-__device__ __forceinline__ void sink_init(Sink &sink, uint2 *stage) {
+__device__ __forceinline__ void sink_init(Sink &sink, uint2 *stage, int16_t *dots) {
   sink.stage = stage;
+  sink.dots = dots;
   sink.fill = 0;
   sink.first_col = 0;
   sink.first_slab = 0;
+  sink.first_end = 0;
   sink.fail_col = 0;
   sink.fail_slab = 0;
+  sink.fail_end = 0;
   sink.stripe = wave_index() & (args()->cfg.stripes - 1);
   sink.pos = 0;
   sink.end = 0;
@@ -564,7 +670,7 @@ template <int W, int R, int U, bool COS>
 __global__ __launch_bounds__(kBlock) void k_filter(FilterArgs) {
   extern __shared__ uint2 stage[];  // kStage entries per wave
   Sink sink;
-  sink_init(sink, stage + (threadIdx.x >> 6) * kStage);
+  sink_init(sink, stage + (threadIdx.x >> 6) * kStage, nullptr);
   tile_loop(sink, [&](const TileJob &jb) { return run_tile<W, R, U, COS>(jb, sink); });
 }
 
@@ -595,23 +701,33 @@ __global__ __launch_bounds__(kBlock) void k_filter(FilterArgs) {
 typedef int v8i_t __attribute__((ext_vector_type(8)));
 typedef float v16f_t __attribute__((ext_vector_type(16)));
 
-constexpr float kNever = 1.0e30f;  // threshold of a row that no column of the group pairs with
+constexpr float kNever = 1.0e9f;  // threshold of a row that no column of the group pairs with
 
 template <int W, int RT>
 struct MRows {
   uint4 sg[RT][W];  // this lane's half of every 64-bit block of its row in each row tile
-  float thr[RT];    // dot threshold for the current size group
-  // the same threshold for the fast test, which compares the bit patterns
+  // dot threshold for the current run, for the fast test, which compares the bit patterns
   // of the dot products as integers: for a positive threshold those order
   // like the values (every value is an exact integer, +0 included, and the
   // negative ones fall below every positive pattern); a threshold of 0 or
-  // less becomes INT32_MIN, so that every step goes to the exact test
+  // less is below every pattern, so that every step goes to the exact test
   int32_t thr_bits[RT];
   uint32_t size[RT];
   uint32_t cmn[RT];
   uint32_t cmx[RT];
   uint32_t idx;     // this lane's row in row tile 0 (row tile rt: idx + 32 rt)
 };
+
+// The dot threshold a lane's thr_bits stand for.
+__device__ __forceinline__ int32_t dot_threshold(int32_t bits) {
+  return bits < INT32_MIN + (1 << 16) ? INT32_MIN - bits : (int32_t)__int_as_float(bits);
+}
+// ... and the other way: a threshold t of 0 or less becomes INT32_MIN - t, below
+// every bit pattern of a dot product (INT32_MIN itself would be -0, which an
+// accumulator that starts at +0 never holds).
+__device__ __forceinline__ int32_t dot_threshold_bits(int32_t t) {
+  return t > 0 ? __float_as_int((float)t) : INT32_MIN - max(t, -(1 << 15));
+}
 
 __device__ __forceinline__ v16f_t mfma_pm1(const uint4 &a, const uint4 &b, const v16f_t &c) {
   const v8i_t x = {(int)a.x, (int)a.y, (int)a.z, (int)a.w, 0, 0, 0, 0};
@@ -651,8 +767,8 @@ __device__ __forceinline__ void load_cols(const uint4 *__restrict__ planes, uint
 // the caller's; column per lane): `skip` pairs are dropped first, `done`
 // counts the step's pairs in order.
 __device__ __forceinline__ bool stage_mask(unsigned long long m, uint32_t row, uint32_t col,
-                                           uint32_t j0, uint32_t &skip, uint32_t &done,
-                                           Sink &sink) {
+                                           uint32_t j0, uint32_t gend, uint32_t &skip,
+                                           uint32_t &done, Sink &sink) {
   const uint32_t lane = threadIdx.x & 63;
   uint32_t cnt = (uint32_t)__popcll(m);
   if (skip) {
@@ -670,6 +786,7 @@ __device__ __forceinline__ bool stage_mask(unsigned long long m, uint32_t row, u
   if (sink.fill == 0) {
     sink.first_col = j0;
     sink.first_slab = done;
+    sink.first_end = gend;
   }
   if ((m >> lane) & 1ull)
     sink.stage[sink.fill + (uint32_t)__popcll(m & __lanemask_lt())] = make_uint2(row, col);
@@ -687,10 +804,13 @@ __device__ __forceinline__ bool stage_mask(unsigned long long m, uint32_t row, u
 // (v, lane).  The choice depends only on the step's values, so a step
 // resumed after a full queue takes the same order and skips exactly the
 // `skip` pairs it had written.
-template <int W, int RT>
+template <int W, int RT, bool COS>
 __device__ __forceinline__ bool emit_mfma(const MRows<W, RT> &rw, const uint4 (&a)[W],
-                                          const int32_t (&mx)[RT], uint32_t j0, uint32_t gend,
-                                          bool diag, uint32_t &skip, Sink &sink) {
+                                          const int32_t (&mx)[RT], uint32_t j0,
+                                          const ColRun &run, const TileJob &jb, uint32_t &skip,
+                                          Sink &sink) {
+  const bool diag = jb.diag;
+  const uint32_t gend = run.end;
   constexpr uint32_t kFewLanes = 4;
   const uint32_t lane = threadIdx.x & 63, h = lane >> 5;
   const uint32_t cb = j0 + 4u * h;  // this lane's column for v is cb + 8(v/4) + v%4
@@ -705,19 +825,40 @@ __device__ __forceinline__ bool emit_mfma(const MRows<W, RT> &rw, const uint4 (&
 #pragma unroll
     for (int kb = 0; kb < W; ++kb) d = mfma_pm1(a[kb], rw.sg[rt][kb], d);
     const uint32_t my_row = rw.idx + 32u * rt;
-    uint32_t k = 0;  // bit v: value v kept (built by shifting: no wide constants)
+    uint32_t k = 0;  // bit v: value v kept
+    const int32_t thr = dot_threshold(rw.thr_bits[rt]);
+    // built by shifting: no wide constants
 #pragma unroll
     for (int v = 15; v >= 0; --v) {
       const uint32_t col = cb + 8u * (v / 4) + (uint32_t)(v % 4);
-      const bool kp = d[v] >= rw.thr[rt] && col < gend && (!diag || col < my_row);
+      const bool kp = d[v] >= (float)thr && col < gend && (!diag || col < my_row);
       k = (k << 1) | (kp ? 1u : 0u);
+    }
+    if ((run.hi > run.lo || (COS && jb.cosine)) && __ballot(k != 0)) {
+      // the threshold is only a bound: each value that reaches it is tested
+      // at its own column's size, one value per lane at a time, from a copy
+      // of the products in LDS
+#pragma unroll
+      for (int v = 0; v < 16; ++v) sink.dots[64 * v + lane] = (int16_t)d[v];
+      __builtin_amdgcn_wave_barrier();
+      const uint32_t *size_cols = args()->size_cols;
+      for (uint32_t todo = k; todo; todo &= todo - 1) {
+        const uint32_t v = (uint32_t)__builtin_ctz(todo);
+        const uint32_t c = size_cols[cb + 8u * (v >> 2) + (v & 3u)];
+        const int32_t dot = sink.dots[64 * v + lane];
+        if (!(c >= rw.cmn[rt] && c <= rw.cmx[rt] &&
+              pair_kept<COS>(jb, rw.size[rt], c, (64 * W - dot) >> 1)))
+          k &= ~(1u << v);
+      }
+      __builtin_amdgcn_wave_barrier();
     }
     unsigned long long lm = __ballot(k != 0);
     if ((uint32_t)__popcll(lm) > kFewLanes) {
 #pragma unroll 1
       for (uint32_t v = 0; v < 16; ++v) {
         const unsigned long long m = __ballot((k >> v) & 1u);
-        if (m && !stage_mask(m, my_row, cb + 8u * (v >> 2) + (v & 3u), j0, skip, done, sink))
+        if (m && !stage_mask(m, my_row, cb + 8u * (v >> 2) + (v & 3u), j0, gend, skip,
+                             done, sink))
           return false;
       }
       continue;
@@ -740,6 +881,7 @@ __device__ __forceinline__ bool emit_mfma(const MRows<W, RT> &rw, const uint4 (&
         if (sink.fill == 0) {
           sink.first_col = j0;
           sink.first_slab = done;
+          sink.first_end = gend;
         }
         if (lane == 0) sink.stage[sink.fill] = make_uint2(row, cL + 8u * (v >> 2) + (v & 3u));
         ++sink.fill;
@@ -811,7 +953,8 @@ __device__ __forceinline__ bool fast_mfma(const uint4 (&a)[W], const uint4 (&an)
   return hit != 0;
 }
 
-// The steps of columns [j, g1) of one size group.  Column loads run two
+// The steps of columns [j, g1) of one run; b0 and b1 hold (or are being
+// loaded with) the columns of its first two steps.  Column loads run two
 // steps ahead in a ring of three register buffers; the loop is unrolled by
 // three so that the ring turns without register copies (a copy of a buffer
 // still being loaded would wait for that load) and the accumulators of the
@@ -822,18 +965,18 @@ __device__ __forceinline__ bool fast_mfma(const uint4 (&a)[W], const uint4 (&an)
 // branch leaves the loop, none enters it in the middle, and every buffer
 // is read on both sides of each exit: the compiler keeps the ring in fixed
 // registers and leaves the loads where they are.
-template <int W, int RT>
+template <int W, int RT, bool COS>
 __device__ __forceinline__ bool sweep_mfma(const uint4 *__restrict__ sg_cols, uint32_t n_cols,
-                                           const MRows<W, RT> &rw, uint32_t j, uint32_t g1,
-                                           bool diag, uint32_t &skip, Sink &sink) {
+                                           const MRows<W, RT> &rw, uint4 (&b0)[W],
+                                           uint4 (&b1)[W], uint32_t j, const ColRun &run,
+                                           const TileJob &jb, uint32_t &skip, Sink &sink) {
   const uint32_t lane = threadIdx.x & 63;
   const uint32_t loff = (lane & 31u) * 32u + (lane >> 5) * 16u;
-  uint4 b0[W], b1[W], b2[W];
+  const uint32_t g1 = run.end;
+  uint4 b2[W];
   int32_t mx[RT];
   v16f_t acc[3];
   uint32_t j0 = j;
-  load_cols<W>(sg_cols, n_cols, j0, loff, b0);
-  load_cols<W>(sg_cols, n_cols, j0 + 32, loff, b1);
   for (;;) {
     int phase;  // the ring buffer that holds the columns of step j0
     // The step's columns for the slow path, copied on the way out of the
@@ -871,7 +1014,7 @@ __device__ __forceinline__ bool sweep_mfma(const uint4 *__restrict__ sg_cols, ui
       skip = 0;
       if ((j0 += 32) >= g1) return true;
     }
-    if (!emit_mfma<W, RT>(rw, cur, mx, j0, g1, diag, skip, sink)) return false;
+    if (!emit_mfma<W, RT, COS>(rw, cur, mx, j0, run, jb, skip, sink)) return false;
     skip = 0;
     if ((j0 += 32) >= g1) return true;
     // b0 and b1 take the columns of steps j0 and j0 + 32
@@ -914,39 +1057,65 @@ __device__ __forceinline__ bool run_tile_mfma(const TileJob &jb, Sink &sink) {
   }
   uint32_t skip = jb.first;
   uint32_t j = jb.c0;
+  const uint32_t loff = jr * 32u + h * 16u;
+  uint32_t c = j < jb.c1 ? as_const(size_cols)[j] : 0u;
+  uint32_t resumed_end = jb.end;
   while (j < jb.c1) {
-    const uint32_t c = rfl(size_cols[j]);
-    const uint32_t g1 =
-        min(max(jb.col_base + rfl(jb.sstart[c + 1]), j + 1), jb.c1);  // advances
+    // the run's first columns, its end and its thresholds are loaded
+    // together (they need only j and c), the next run's first size while
+    // this run is swept
+    uint4 b0[W], b1[W];
+    if (W < 16) {
+      load_cols<W>(sg_cols, n_cols, j, loff, b0);
+      load_cols<W>(sg_cols, n_cols, j + 32, loff, b1);
+    }
+    ColRun run = col_run(jb.sstart, jb.col_base, jb.col_max, c, j, jb.c1);
+    if (resumed_end) {
+      // resumed inside a run: its step ends where it did
+      run.end = min(max(resumed_end, j + 1), jb.c1);
+      run.hi = as_const(size_cols)[run.end - 1];
+      resumed_end = 0;
+    }
+    if (run.end < jb.c1) c = as_const(size_cols)[run.end];
     bool any_ok = false;
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) {
-      const bool in_band = c >= rw.cmn[rt] && c <= rw.cmx[rt];
+      const bool in_band = run.lo <= rw.cmx[rt] && run.hi >= rw.cmn[rt];
       int32_t sl = 0;
-      if (in_band) sl = (COS && jb.cosine) ? cosine_slack(rw.size[rt], c, jb.p, jb.q)
-                                           : jb.slack[rw.size[rt] + c];
-      const int32_t t = K - 2 * sl;
-      rw.thr[rt] = in_band ? (float)t : kNever;
-      rw.thr_bits[rt] = !in_band ? __float_as_int(kNever)
-                        : t > 0  ? __float_as_int((float)t)
-                                 : INT32_MIN;
+      if (in_band)
+        sl = run_slack<COS>(jb, rw.size[rt], run.lo, min(run.hi, rw.cmx[rt]));
+      rw.thr_bits[rt] = in_band ? dot_threshold_bits(K - 2 * sl) : __float_as_int(kNever);
       any_ok |= in_band;
     }
     if (__ballot(any_ok)) {
-      if (!sweep_mfma<W, RT>(sg_cols, n_cols, rw, j, g1, jb.diag, skip, sink)) return false;
+      if (W >= 16) {  // no registers to hold them through the thresholds
+        load_cols<W>(sg_cols, n_cols, j, loff, b0);
+        load_cols<W>(sg_cols, n_cols, j + 32, loff, b1);
+      }
+      if (!sweep_mfma<W, RT, COS>(sg_cols, n_cols, rw, b0, b1, j, run, jb, skip, sink))
+        return false;
     }
     skip = 0;
-    j = g1;
+    j = run.end;
   }
   // the tile's staged pairs go out before the next tile
   return flush(sink, true);
 }
 
+// Waves per SIMD the register budget of a shape aims at.
+template <int W>
+constexpr int mfma_waves() {
+  return W <= 2 ? 3 : W <= 4 ? 2 : 1;
+}
+
 template <int W, int RT, bool COS>
-__global__ __launch_bounds__(kBlock) void k_filter_mfma(FilterArgs) {
-  extern __shared__ uint2 stage[];  // kStage entries per wave
+__global__ __launch_bounds__(kBlock, mfma_waves<W>()) void k_filter_mfma(FilterArgs) {
+  // kStage entries per wave, then 1024 dot products per wave
+  extern __shared__ uint2 stage[];
+  const uint32_t w = threadIdx.x >> 6;
   Sink sink;
-  sink_init(sink, stage + (threadIdx.x >> 6) * kStage);
+  sink_init(sink, stage + w * kStage,
+            reinterpret_cast<int16_t *>(stage + (blockDim.x >> 6) * kStage) + w * 1024);
   tile_loop(sink, [&](const TileJob &jb) { return run_tile_mfma<W, RT, COS>(jb, sink); });
 }
 
@@ -960,7 +1129,7 @@ hipError_t launch_shape(dim3 grid, hipStream_t st, const FilterArgs &a) {
 template <int W, int RT, bool COS>
 hipError_t launch_mfma(dim3 grid, hipStream_t st, const FilterArgs &a) {
   hipLaunchKernelGGL((k_filter_mfma<W, RT, COS>), grid, dim3(64 * a.cfg.block_waves),
-                     a.cfg.block_waves * kStage * sizeof(uint2), st, a);
+                     a.cfg.block_waves * (kStage * sizeof(uint2) + 1024 * sizeof(int16_t)), st, a);
   return hipGetLastError();
 }
 

@@ -45,20 +45,25 @@ namespace {
 constexpr uint64_t kInitialQueue = 1ull << 23;
 constexpr uint64_t kMaxQueue = 1ull << 29;
 constexpr uint32_t kDefaultTileCols = 2048;
-// A width class with fewer than about kMinSlotTiles tiles of the default
+// A width class with fewer than about min_slot_tiles tiles of the default
 // width gets narrower tiles, down to kMinTileCols columns; kMinTileColsValu
 // for the vector-ALU kernel, whose classes hold the largest sets: on the
 // sparse tail of the size distribution a tile crosses a size group every
 // few columns, and the launch lasts as long as its slowest tile.  (The
 // matrix-core kernel measured no gain below 64: it takes 32 columns a step.)
-constexpr uint64_t kMinSlotTiles = 16384;
-// A call of one task uses fewer, wider tiles: its blocks' column ranges are
-// long, and each tile and each size group it crosses starts with dependent
-// loads that three waves per SIMD do not hide (the 1,000,000-set join's
-// b = 128 class: 0.185 ms at 4,096 tiles against 0.246 ms at 16,384).  The
-// many short ranges of a batch's tasks balance the waves better with more
-// tiles (its b = 64 class: 1.71 ms at 16,384 against 2.18 ms at 4,096).
-constexpr uint64_t kMinSlotTilesOneTask = 4096;
+//
+// Eight tiles for every wave the GPU holds at the kernel's registers (three,
+// two or one waves per SIMD at up to 128, 256 and more bits; the vector-ALU
+// classes as the last): with fewer the last round of tiles leaves much of
+// the GPU idle, with more the tiles' starts weigh.  Measured at 4,096 /
+// 8,192 / 16,384 / 32,768 tiles: b = 128 in a batch of 48 collections
+// 1272 / 1273 / 996 / 650 us, in a query of 2,000 sets 353 / 291 / 268 / 265;
+// b = 256 in the batch 927 / 930 / 741 / 768, in a 3,000-set R-S join 201 /
+// 133 / 121 / 124; b = 512 in the batch 274 / 292 / 324 / 408.
+uint64_t min_slot_tiles(const FilterShape &shape) {
+  if (!shape.mfma || shape.words > 4) return 8 * 1024;
+  return shape.words > 2 ? 8 * 2048 : 8 * 3072;
+}
 // Host threads that plan the width classes of a call's tasks (16 tasks or
 // more per thread), when the tasks' largest sizes sum to kPlanThreadSizes
 // or more.
@@ -1426,8 +1431,8 @@ void join_begin(Space &R, Space &C, const std::vector<TaskIn> &tasks, const Join
   }
   std::map<TableKey, TaskDesc> shared_tables;
   for (const auto &e : table_sizes)
-    add_tables(pl, shared_tables[e.first], e.second.first, e.second.second, e.first.first,
-               e.first.second.first, e.first.second.second);
+    add_tables(pl, shared_tables[e.first], e.second.first, widest_run_size(e.second.second),
+               e.first.first, e.first.second.first, e.first.second.second);
   for (uint32_t k = 0; k < n_tasks; ++k) {
     const TaskIn &tk = tasks[k];
     const uint32_t key_side = tk.row_side;
@@ -1553,8 +1558,7 @@ void join_begin(Space &R, Space &C, const std::vector<TaskIn> &tasks, const Join
     }
     if (!jc.tile_cols_fixed) {
       const FilterShape shape = filter_shape(pl.slot_words[k], pl.slot_mfma[k]);
-      const uint64_t min_tiles = n_tasks > 1 ? kMinSlotTiles : kMinSlotTilesOneTask;
-      const uint64_t want = slot_band[k] / ((uint64_t)shape.rows * min_tiles);
+      const uint64_t want = slot_band[k] / ((uint64_t)shape.rows * min_slot_tiles(shape));
       const uint32_t floor_cols = shape.mfma ? kMinTileCols : kMinTileColsValu;
       tile_cols = (uint32_t)std::max<uint64_t>(floor_cols, std::min<uint64_t>(tile_cols, want));
     }
@@ -1808,6 +1812,7 @@ void join_begin(Space &R, Space &C, const std::vector<TaskIn> &tasks, const Join
   cfg = FilterConfig{};
   cfg.n_rows = (uint32_t)R.n;
   cfg.n_cols = (uint32_t)C.n;
+  cfg.col_max_size = C.max_size;
   cfg.n_tiles = pl.n_tiles;
   cfg.n_blocks = (uint32_t)nB;
   cfg.resume_cap = max_resume;

@@ -96,19 +96,22 @@ struct TaskDesc {
   uint32_t pad;
 };
 
-// Least overlap o with Cosine o / sqrt(a c) >= p / q (Table 1), exactly:
-// the smallest o with q^2 o^2 >= p^2 a c, in 128-bit integers.  A double
-// estimate is corrected by at most a few steps either way.
+// Cosine o / sqrt(a c) >= p / q (Table 1), exactly: q^2 o^2 >= p^2 a c in
+// 128-bit integers.
+__host__ __device__ inline bool cosine_reaches(uint64_t o, uint32_t a, uint32_t c, uint32_t p,
+                                               uint32_t q) {
+  const uint64_t x = (uint64_t)q * o;
+  return (unsigned __int128)x * x >=
+         (unsigned __int128)((uint64_t)p * p) * ((uint64_t)a * c);
+}
+
+// Least overlap o that reaches a Cosine threshold: a double estimate is
+// corrected by at most a few steps either way.
 __host__ __device__ inline uint32_t cosine_omin(uint32_t a, uint32_t c, uint32_t p, uint32_t q) {
-  const unsigned __int128 rhs = (unsigned __int128)((uint64_t)p * p) * ((uint64_t)a * c);
-  auto reaches = [&](uint64_t o) {
-    const uint64_t x = (uint64_t)q * o;
-    return (unsigned __int128)x * x >= rhs;
-  };
   const double est = (double)p / (double)q * sqrt((double)a * (double)c);
   uint64_t o = est > 0.0 ? (uint64_t)est : 0u;
-  while (o > 0 && reaches(o - 1)) --o;
-  while (!reaches(o)) ++o;
+  while (o > 0 && cosine_reaches(o - 1, a, c, p, q)) --o;
+  while (!cosine_reaches(o, a, c, p, q)) ++o;
   return (uint32_t)o;
 }
 
@@ -146,7 +149,7 @@ struct Resume {
   uint32_t tile;
   uint32_t col;
   uint32_t slab;
-  uint32_t pad;
+  uint32_t end;   // matrix-core kernel: where the step's run of columns ends
 };
 
 // Filter launch arguments that are not hot pointers.
@@ -167,12 +170,14 @@ struct FilterConfig {
   uint32_t stripes;       // stripes of the queue, a power of two
   uint32_t direct;        // 1: one wave per tile, no cursors
   uint32_t block_waves;   // waves of a workgroup (set by launch_filter)
+  uint32_t col_max_size;  // largest size of the column space
 };
 
 // A launch of at most this many tiles starts one wave per tile and leaves
-// their balance to the workgroup dispatch (FilterConfig::direct); see
-// launch_filter.
-constexpr uint32_t kDirectTiles = 16384;
+// their balance to the workgroup dispatch (FilterConfig::direct).  It saves
+// the cursors' fixed cost; a launch of more tiles takes long enough not to
+// notice it, and keeps an XCD's waves on neighbouring tiles.
+constexpr uint32_t kDirectTiles = 65536;
 
 // ---------------------------------------------------------------- launchers
 // All launchers enqueue on `st` and return hipSuccess or the launch error.
@@ -322,6 +327,12 @@ hipError_t launch_expand_tiles(const RowBlock *blocks, uint32_t n_blocks, uint32
 // Kept pairs a wave stages in LDS before one queue reservation: the
 // largest reservation a filter launch makes.
 constexpr uint32_t kFilterStage = 256;
+
+// The filter sweeps columns of sizes c .. c + c / 2^kRunShift in one run and
+// reads the slack table up to the run's largest size: the largest size it
+// looks up for columns of up to c_max tokens.
+constexpr uint32_t kRunShift = 5;
+inline uint64_t widest_run_size(uint64_t c_max) { return c_max + (c_max >> kRunShift); }
 
 // Filter geometry for a padded width.
 struct FilterShape {

@@ -13,8 +13,8 @@ pytestmark = pytest.mark.gpu
 
 @pytest.fixture(scope="module")
 def dense():
-    """6,000 sets whose 64-bit bitmaps keep over 50,000 pairs at 1/2."""
-    c = gen.generate(n_sets=6000, universe=500, zipf_s=1.0, size_dist=gen.SIZE_LOGNORMAL,
+    """9,000 sets whose 64-bit bitmaps keep over 40,000 pairs at 1/2."""
+    c = gen.generate(n_sets=9000, universe=500, zipf_s=1.0, size_dist=gen.SIZE_LOGNORMAL,
                      size_a=20.0, size_b=0.8, size_lo=1, size_hi=60, planted_frac=0.3, seed=77)
     want = oracle.self_join(c.offsets, c.tokens, 1, 2)
     bm = oracle.bitmaps(c.offsets, c.tokens, 64, oracle.BM_XOR)
@@ -33,20 +33,52 @@ def test_tiles_and_stripes(dense, cap, tile_cols, flags):
     c, d, want, survivors = dense
     got, st = ssj.ssj_self_join(d, 1, 2, b_bits=64, queue_capacity=cap, tile_cols=tile_cols,
                                 flags=flags)
-    assert (st["class_tiles"][0] > 16384) == (tile_cols == 1)
+    assert (st["class_tiles"][0] > 65536) == (tile_cols == 1)
     assert np.array_equal(got, want) and st["survivors"] == survivors
     assert (st["filter_launches"] > 1) == (0 < cap < survivors)
 
 
-def test_several_classes_resume_from_their_tile_starts():
+def test_later_classes_resume_from_their_tile_starts():
     """Width classes after the one that fills the queue have started none of
     their tiles; the resumed rounds run each of them once."""
-    c = gen.generate(n_sets=30_000, universe=3000, zipf_s=1.0, size_dist=gen.SIZE_LOGNORMAL,
-                     size_a=30.0, size_b=0.9, size_lo=2, size_hi=600, planted_frac=0.3, seed=78)
-    d = ssj.to_device(c.offsets, c.tokens)
-    one, s1 = ssj.ssj_self_join(d, 7, 10, b_bits=0)
-    got, st = ssj.ssj_self_join(d, 7, 10, b_bits=0, queue_capacity=4096)
+    cols = [gen.generate(n_sets=n, universe=2000, zipf_s=1.0, size_dist=gen.SIZE_LOGNORMAL,
+                         size_a=m, size_b=0.6, size_lo=2, size_hi=600, planted_frac=0.3, seed=s)
+            for n, m, s in ((8000, 8.0, 78), (3000, 150.0, 79))]
+    devs = [ssj.to_device(c.offsets, c.tokens) for c in cols]
+    p, q = [4, 1], [5, 2]
+    one, s1 = ssj.ssj_self_join_batch(devs, p, q)
+    got, st = ssj.ssj_self_join_batch(devs, p, q, queue_capacity=4096)
     assert st["n_classes"] == s1["n_classes"] >= 2
     assert st["filter_launches"] > s1["filter_launches"]
-    assert np.array_equal(got, one) and st["survivors"] == s1["survivors"]
-    assert np.array_equal(one, oracle.self_join_banded(c.offsets, c.tokens, 7, 10)[0])
+    assert st["survivors"] == s1["survivors"] > 4096
+    for c, a, b, x, y in zip(cols, one, got, p, q):
+        want = oracle.self_join(c.offsets, c.tokens, x, y)
+        assert np.array_equal(a, want) and np.array_equal(b, want)
+
+
+@pytest.fixture(scope="module")
+def sparse():
+    """600 sets of 33 .. 1,500 tokens: hardly two of one size, so that nearly every
+    step of the filter covers columns of several sizes."""
+    c = gen.generate(n_sets=600, universe=6000, zipf_s=0.8, size_dist=gen.SIZE_UNIFORM,
+                     size_lo=33, size_hi=1500, planted_frac=0.5, seed=80)
+    return c, ssj.to_device(c.offsets, c.tokens)
+
+
+# 64 bits saturate (thresholds below every dot product: whole steps survive),
+# 512 keep few; a 4,096-slot queue resumes inside such steps
+@pytest.mark.parametrize("flags", [ssj.SSJ_FLAG_MFMA, ssj.SSJ_FLAG_VALU])
+@pytest.mark.parametrize("b", [64, 128, 256, 512, 1024])
+@pytest.mark.parametrize("sim,p,q", [(ssj.SSJ_SIM_JACCARD, 1, 2), (ssj.SSJ_SIM_JACCARD, 9, 10),
+                                     (ssj.SSJ_SIM_DICE, 2, 3), (ssj.SSJ_SIM_COSINE, 3, 5),
+                                     (ssj.SSJ_SIM_COSINE, 65537, 70001),
+                                     (ssj.SSJ_SIM_OVERLAP, 200, 1)])
+def test_steps_of_several_sizes(sparse, sim, p, q, b, flags):
+    c, d = sparse
+    bm = oracle.bitmaps(c.offsets, c.tokens, b, oracle.BM_XOR)
+    cnt, band, want = oracle.survivors(c.offsets, bm, b, p, q, listing=True, sim=sim)
+    for cap in (0, 4096):
+        got, st = ssj.ssj_self_join(d, p, q, b_bits=b, sim=sim, queue_capacity=cap,
+                                    flags=flags | ssj.SSJ_FLAG_SURVIVORS_ONLY)
+        assert st["survivors"] == cnt and st["band_pairs"] == band
+        assert np.array_equal(got, want)
