@@ -29,115 +29,117 @@
 namespace ssj {
 namespace {
 
-constexpr int kWin = 8;  // tokens per merge window
+// Tokens per merge window.  A step compares two windows in kWin^2 compares
+// and drops kWin tokens or more, so a small window does less work per token;
+// four tokens are one 16-byte load (a load per token, each lane in another
+// cache line, kept the memory pipeline busy for most of the kernel), and the
+// windows after the current ones are already on their way.
+constexpr int kWin = 4;
 
-// Load tokens [at, at + kWin) of a set of n tokens; slots past the end are
-// marked invalid.  The loads are independent, so a refill costs one round trip.
-__host__ __device__ __forceinline__ void load_window(const uint32_t *__restrict__ t, uint32_t n,
-                                            uint32_t at, uint32_t (&w)[kWin]) {
-#pragma unroll
-  for (int k = 0; k < kWin; ++k) w[k] = at + k < n ? t[at + k] : 0u;
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4), aligned(4)));
+
+// A set's tokens in a CSR array: `left` tokens of the array from its first on
+// (at least its size n): a window may be read whole as long as it stays in
+// the array.
+struct Tokens {
+  const uint32_t *t;
+  uint32_t n, left;
+};
+
+__device__ __forceinline__ Tokens tokens_of(const uint32_t *tokens, uint64_t first, uint32_t n,
+                                            uint64_t n_tokens) {
+  return Tokens{tokens + first, n, (uint32_t)min(n_tokens - first, (uint64_t)0xFFFFFFFFu)};
 }
 
-// |r n s| >= need for two strictly increasing token lists, by a windowed
+// Tokens [at, at + kWin); slots past the set's end hold anything.
+__device__ __forceinline__ void load_window(const Tokens &s, uint32_t at, uint32_t (&w)[kWin]) {
+  static_assert(kWin == 4, "one 16-byte load");
+  if ((uint64_t)at + kWin <= s.left) {
+    const u32x4 q = *reinterpret_cast<const u32x4 *>(s.t + at);
+#pragma unroll
+    for (int k = 0; k < kWin; ++k) w[k] = q[k];
+  } else {
+#pragma unroll
+    for (int k = 0; k < kWin; ++k) w[k] = (uint64_t)at + k < s.n ? s.t[at + k] : 0u;
+  }
+}
+
+// Common tokens of two strictly increasing token lists, by a windowed
 // merge: count the common tokens of the current windows, then drop the
 // window whose last token is smaller (both when equal).  A common token sits
 // in both current windows at some step and leaves with the dropped window,
-// so it is counted once.  Stops as soon as the count reaches need, or the
-// tokens left cannot reach it.
-__host__ __device__ __forceinline__ bool overlap_reaches(const uint32_t *__restrict__ rp, uint32_t a,
-                                                const uint32_t *__restrict__ sp, uint32_t c,
-                                                uint32_t need) {
+// so it is counted once.  ENOUGH: stops as soon as the count reaches need, or
+// the tokens left cannot reach it (the count is then short of it).
+template <bool ENOUGH>
+__device__ __forceinline__ uint32_t merge_count(const Tokens &r, const Tokens &s, uint32_t need) {
   uint32_t ia = 0, ic = 0, o = 0;
-  uint32_t rw[kWin], sw[kWin];
-  load_window(rp, a, 0, rw);
-  load_window(sp, c, 0, sw);
-  while (ia < a && ic < c) {
-    if (o >= need) return true;
-    if (o + min(a - ia, c - ic) < need) return false;
-    const uint32_t nr = min(a - ia, (uint32_t)kWin), ns = min(c - ic, (uint32_t)kWin);
+  uint32_t rw[kWin], sw[kWin], rn[kWin], sn[kWin];
+  load_window(r, 0, rw);
+  load_window(s, 0, sw);
+  load_window(r, kWin, rn);
+  load_window(s, kWin, sn);
+  while (ia < r.n && ic < s.n) {
+    const uint32_t la = r.n - ia, lc = s.n - ic;
+    if (ENOUGH && (o >= need || o + min(la, lc) < need)) break;
 #pragma unroll
     for (int x = 0; x < kWin; ++x)
 #pragma unroll
       for (int y = 0; y < kWin; ++y)
-        o += ((uint32_t)x < nr && (uint32_t)y < ns && rw[x] == sw[y]) ? 1u : 0u;
+        o += ((uint32_t)x < la && (uint32_t)y < lc && rw[x] == sw[y]) ? 1u : 0u;
     // last valid token of each window
     uint32_t rmax = rw[0], smax = sw[0];
 #pragma unroll
     for (int k = 1; k < kWin; ++k) {
-      if ((uint32_t)k < nr) rmax = rw[k];
-      if ((uint32_t)k < ns) smax = sw[k];
+      if ((uint32_t)k < la) rmax = rw[k];
+      if ((uint32_t)k < lc) smax = sw[k];
     }
     if (rmax <= smax) {
-      ia += nr;
-      load_window(rp, a, ia, rw);
+      ia += min(la, (uint32_t)kWin);
+#pragma unroll
+      for (int k = 0; k < kWin; ++k) rw[k] = rn[k];
+      load_window(r, ia + kWin, rn);
     }
     if (smax <= rmax) {
-      ic += ns;
-      load_window(sp, c, ic, sw);
+      ic += min(lc, (uint32_t)kWin);
+#pragma unroll
+      for (int k = 0; k < kWin; ++k) sw[k] = sn[k];
+      load_window(s, ic + kWin, sn);
     }
   }
-  return o >= need;
+  return o;
 }
 
-// |r n s| with the whole wave, for one pair of long sets (the same on every
-// lane).  Lane l takes r's tokens [a l / 64, a (l + 1) / 64) and counts
-// those that s holds.  s is cut by 64 splitters s[c j / 64], one load per
-// lane; a lane finds the last splitter not above its first token by a
-// binary search over the lanes' splitters (six shuffles) and merges its
-// tokens with s from there.  Tokens of s before that splitter are smaller
-// than every token of the lane's, so each token of r is counted exactly
-// when s holds it.  About four memory round trips, against one per eight
-// tokens for a lane's own merge.
-__device__ __forceinline__ uint32_t wave_overlap(const uint32_t *__restrict__ rp, uint32_t a,
-                                                 const uint32_t *__restrict__ sp, uint32_t c) {
-  const uint32_t lane = threadIdx.x & 63;
-  const uint32_t lo = (uint32_t)(((uint64_t)a * lane) >> 6);
-  const uint32_t hi = (uint32_t)(((uint64_t)a * (lane + 1)) >> 6);
-  const uint32_t sj = (uint32_t)(((uint64_t)c * lane) >> 6);  // < c
-  const uint32_t sv = sp[sj];
-  const bool has = lo < hi;
-  const uint32_t first = has ? rp[lo] : 0u;
+// |r n s| with a group of G lanes of the wave (one pair per group).  Lane l of
+// the group takes r's tokens [a l / G, a (l + 1) / G) and counts those that
+// s holds.  s is cut by G splitters s[c j / G], one load per lane; a lane
+// finds the last splitter not above its first token by a binary search over
+// the group's splitters (shuffles) and merges its tokens with s from there.
+// Tokens of s before that splitter are smaller than every token of the
+// lane's, so each token of r is counted exactly when s holds it.  Every lane
+// of the wave calls it; a group without a pair has r.n = 0.
+template <int G>
+__device__ __forceinline__ uint32_t group_overlap(const Tokens &r, const Tokens &s) {
+  const uint32_t lane = threadIdx.x & 63, l = lane % G, base = lane - l;
+  const uint32_t lo = (uint32_t)(((uint64_t)r.n * l) / G);
+  const uint32_t hi = (uint32_t)(((uint64_t)r.n * (l + 1)) / G);
+  const uint32_t sj = (uint32_t)(((uint64_t)s.n * l) / G);  // < s.n
+  const bool has = lo < hi && s.n != 0;
+  const uint32_t sv = s.n ? s.t[sj] : 0u;
+  const uint32_t first = has ? r.t[lo] : 0u;
   int j = 0;
 #pragma unroll
-  for (int step = 32; step >= 1; step >>= 1) {
-    const uint32_t cand = (uint32_t)__shfl((int)sv, j + step, 64);
+  for (int step = G / 2; step >= 1; step >>= 1) {
+    const uint32_t cand = (uint32_t)__shfl((int)sv, (int)base + j + step, 64);
     if (cand <= first) j += step;
   }
-  const uint32_t from = (uint32_t)(((uint64_t)c * (uint32_t)j) >> 6);
   uint32_t o = 0;
   if (has) {
-    const uint32_t na = hi - lo, nc = c - from;
-    const uint32_t *__restrict__ r = rp + lo, *__restrict__ t = sp + from;
-    uint32_t ia = 0, ic = 0;
-    uint32_t rw[kWin], sw[kWin];
-    load_window(r, na, 0, rw);
-    load_window(t, nc, 0, sw);
-    while (ia < na && ic < nc) {
-      const uint32_t nr = min(na - ia, (uint32_t)kWin), ns = min(nc - ic, (uint32_t)kWin);
-#pragma unroll
-      for (int x = 0; x < kWin; ++x)
-#pragma unroll
-        for (int y = 0; y < kWin; ++y)
-          o += ((uint32_t)x < nr && (uint32_t)y < ns && rw[x] == sw[y]) ? 1u : 0u;
-      uint32_t rmax = rw[0], smax = sw[0];
-#pragma unroll
-      for (int k = 1; k < kWin; ++k) {
-        if ((uint32_t)k < nr) rmax = rw[k];
-        if ((uint32_t)k < ns) smax = sw[k];
-      }
-      if (rmax <= smax) {
-        ia += nr;
-        load_window(r, na, ia, rw);
-      }
-      if (smax <= rmax) {
-        ic += ns;
-        load_window(t, nc, ic, sw);
-      }
-    }
+    const uint32_t from = (uint32_t)(((uint64_t)s.n * (uint32_t)j) / G);
+    const Tokens pr{r.t + lo, hi - lo, r.left - lo}, ps{s.t + from, s.n - from, s.left - from};
+    o = merge_count<false>(pr, ps, 0);
   }
 #pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) o += (uint32_t)__shfl_xor((int)o, d, 64);
+  for (int d = G / 2; d >= 1; d >>= 1) o += (uint32_t)__shfl_xor((int)o, d, 64);
   return o;
 }
 
@@ -173,8 +175,8 @@ __device__ __forceinline__ uint32_t wide_distance(const uint64_t *__restrict__ x
 }
 
 // Pairs whose sizes sum to more than kLongMerge, and that pass the cascade
-// test, are merged by a whole wave (wave_overlap) in a second launch: a
-// lane's own merge takes a memory round trip per eight tokens, and one long
+// test, are merged by groups of lanes (group_overlap) in a second launch: a
+// lane's own merge takes a memory round trip per four tokens, and one long
 // true pair would hold its whole round that long.
 constexpr uint32_t kLongMerge = 128;
 
@@ -206,6 +208,7 @@ struct OneTask {
   TaskDesc td;
   const uint64_t *r_off, *c_off;
   const uint32_t *r_tok, *c_tok;
+  uint64_t r_ntok, c_ntok;
   uint32_t r_wlo, c_wlo, r_wslot, c_wslot;
 };
 
@@ -215,8 +218,10 @@ __device__ __forceinline__ OneTask one_task(const VerifyArgs &va) {
   const SideDesc &dr = va.rows.sides[one.td.row_side], &dc = va.cols.sides[one.td.col_side];
   one.r_off = dr.offsets;
   one.r_tok = dr.tokens;
+  one.r_ntok = dr.n_tokens;
   one.c_off = dc.offsets;
   one.c_tok = dc.tokens;
+  one.c_ntok = dc.n_tokens;
   if (va.rows.bmw) {
     one.r_wlo = va.rows.wide_lo[one.td.row_side];
     one.c_wlo = va.cols.wide_lo[one.td.col_side];
@@ -303,9 +308,11 @@ __device__ __forceinline__ bool verify_entry(uint32_t x, uint32_t y, const Verif
         r0 = rows.sides[sr].offsets[px];
         s0 = cols.sides[sc].offsets[py];
       }
-      const uint32_t *rt = ONE ? one.r_tok : rows.sides[sr].tokens;
-      const uint32_t *ct = ONE ? one.c_tok : cols.sides[sc].tokens;
-      hit = overlap_reaches(rt + r0, a, ct + s0, c, need);
+      const Tokens r = tokens_of(ONE ? one.r_tok : rows.sides[sr].tokens, r0, a,
+                                 ONE ? one.r_ntok : rows.sides[sr].n_tokens);
+      const Tokens s = tokens_of(ONE ? one.c_tok : cols.sides[sc].tokens, s0, c,
+                                 ONE ? one.c_ntok : cols.sides[sc].n_tokens);
+      hit = merge_count<true>(r, s, need) >= need;
     }
   }
   if (hit) key = result_key(px, py, td, task, va.ib, va.jb);
@@ -481,13 +488,53 @@ __global__ __launch_bounds__(kVerifyBlock) void k_verify(
 }
 
 // The deferred long pairs (their bitmap tests passed).  A few of them (up to
-// kLaneMode per wave): one wave per pair, the pairs dealt to the waves in
-// turn, so that each takes a few round trips.  Many: a lane per pair, 64 at
-// a time, which takes longer per pair but costs the wave less (a wave's
-// merge of one pair is about eight times the work of a lane's).
+// kGroupMode per wave): one wave per pair, the pairs dealt to the waves in
+// turn, so that each takes a few round trips.  Many: eight lanes per pair,
+// eight pairs at a time (a lane per pair took as long as its longest pair,
+// 380 us for pairs of up to 4,000 tokens; a wave per pair spends most of its
+// lanes' steps on the splitters).
+//
 // Result keys are staged per wave as in k_verify: with one atomic per pair the
 // 1,000,000-set join at 4/5 spent 124 us here, most of it waiting for them.
-constexpr uint32_t kLaneMode = 8;
+constexpr uint32_t kGroupMode = 4;
+
+// The deferred pairs e0, e0 + step, ... by groups of G lanes: group k of wave w
+// starts at pair w * (64 / G) + k.
+template <int G, bool ONE, class Stage>
+__device__ __forceinline__ void verify_long_pairs(unsigned long long count, unsigned long long wave,
+                                                  unsigned long long n_waves, const VerifyArgs &va,
+                                                  const OneTask &one, Stage &&stage) {
+  const uint32_t lane = threadIdx.x & 63;
+  const VerifySpace &rows = va.rows, &cols = va.cols;
+  constexpr unsigned long long kPairs = 64 / G;
+  for (unsigned long long e0 = wave * kPairs; e0 < count; e0 += n_waves * kPairs) {
+    const unsigned long long e = e0 + lane / G;
+    const bool real = e < count;
+    uint32_t need = 0xFFFFFFFFu;
+    unsigned long long key = 0;
+    Tokens r{nullptr, 0, 0}, s{nullptr, 0, 0};
+    if (real) {
+      const uint2 qe = va.longq[e];
+      const uint32_t x = qe.x, y = qe.y;
+      const uint32_t sr = ONE ? 0u : rows.side_of[x], sc = ONE ? 0u : cols.side_of[y];
+      const uint32_t px = rows.perm[x], py = cols.perm[y];
+      const uint32_t a = rows.sizes[x], c = cols.sizes[y];
+      const uint32_t task = ONE ? 0u : va.side_task[sr];
+      const TaskDesc td = ONE ? one.td : va.tasks[task];
+      need = td.sim == SSJ_SIM_COSINE ? cosine_omin(a, c, td.p, td.q)
+                                      : va.tables[td.omin_off + a + c];
+      const uint64_t r0 = ONE ? one.r_off[px] : rows.sides[sr].offsets[px];
+      const uint64_t s0 = ONE ? one.c_off[py] : cols.sides[sc].offsets[py];
+      r = tokens_of(ONE ? one.r_tok : rows.sides[sr].tokens, r0, a,
+                    ONE ? one.r_ntok : rows.sides[sr].n_tokens);
+      s = tokens_of(ONE ? one.c_tok : cols.sides[sc].tokens, s0, c,
+                    ONE ? one.c_ntok : cols.sides[sc].n_tokens);
+      key = result_key(px, py, td, task, va.ib, va.jb);
+    }
+    const uint32_t o = group_overlap<G>(r, s);
+    stage(real && lane % G == 0 && o >= need, key);
+  }
+}
 
 template <bool ONE>
 __global__ __launch_bounds__(kBlock) void k_verify_long(unsigned long long cap, VerifyArgs va,
@@ -517,51 +564,10 @@ __global__ __launch_bounds__(kBlock) void k_verify_long(unsigned long long cap, 
   const unsigned long long n_waves = (unsigned long long)gridDim.x * (kBlock / 64);
   const unsigned long long wave = (unsigned long long)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
   const OneTask one = ONE ? one_task(va) : OneTask{};
-  const VerifySpace &rows = va.rows, &cols = va.cols;
-  if (count >= (unsigned long long)kLaneMode * n_waves) {
-    for (unsigned long long e0 = wave * 64; e0 < count; e0 += n_waves * 64) {
-      const unsigned long long e = e0 + lane;
-      bool hit = false;
-      unsigned long long key = 0;
-      if (e < count) {
-        const uint2 qe = va.longq[e];
-        const uint32_t x = qe.x, y = qe.y;
-        const uint32_t sr = ONE ? 0u : rows.side_of[x], sc = ONE ? 0u : cols.side_of[y];
-        const uint32_t px = rows.perm[x], py = cols.perm[y];
-        const uint32_t a = rows.sizes[x], c = cols.sizes[y];
-        const uint32_t task = ONE ? 0u : va.side_task[sr];
-        const TaskDesc td = ONE ? one.td : va.tasks[task];
-        const uint32_t need = td.sim == SSJ_SIM_COSINE ? cosine_omin(a, c, td.p, td.q)
-                                                       : va.tables[td.omin_off + a + c];
-        const uint64_t r0 = ONE ? one.r_off[px] : rows.sides[sr].offsets[px];
-        const uint64_t s0 = ONE ? one.c_off[py] : cols.sides[sc].offsets[py];
-        const uint32_t *rt = ONE ? one.r_tok : rows.sides[sr].tokens;
-        const uint32_t *ct = ONE ? one.c_tok : cols.sides[sc].tokens;
-        hit = overlap_reaches(rt + r0, a, ct + s0, c, need);
-        if (hit) key = result_key(px, py, td, task, va.ib, va.jb);
-      }
-      stage(hit, key);
-    }
-    count = 0;  // all done
-  }
-  for (unsigned long long e = wave; e < count; e += n_waves) {
-    const uint2 qe = va.longq[e];
-    const uint32_t x = (uint32_t)__builtin_amdgcn_readfirstlane((int)qe.x);
-    const uint32_t y = (uint32_t)__builtin_amdgcn_readfirstlane((int)qe.y);
-    const uint32_t sr = ONE ? 0u : rows.side_of[x], sc = ONE ? 0u : cols.side_of[y];
-    const uint32_t px = rows.perm[x], py = cols.perm[y];
-    const uint32_t a = rows.sizes[x], c = cols.sizes[y];
-    const uint32_t task = ONE ? 0u : va.side_task[sr];
-    const TaskDesc td = ONE ? one.td : va.tasks[task];
-    const uint32_t need = td.sim == SSJ_SIM_COSINE ? cosine_omin(a, c, td.p, td.q)
-                                                   : va.tables[td.omin_off + a + c];
-    const uint64_t r0 = ONE ? one.r_off[px] : rows.sides[sr].offsets[px];
-    const uint64_t s0 = ONE ? one.c_off[py] : cols.sides[sc].offsets[py];
-    const uint32_t *rt = ONE ? one.r_tok : rows.sides[sr].tokens;
-    const uint32_t *ct = ONE ? one.c_tok : cols.sides[sc].tokens;
-    const uint32_t o = wave_overlap(rt + r0, a, ct + s0, c);
-    stage(o >= need && lane == 0, result_key(px, py, td, task, va.ib, va.jb));
-  }
+  if (count >= (unsigned long long)kGroupMode * n_waves)
+    verify_long_pairs<8, ONE>(count, wave, n_waves, va, one, stage);
+  else
+    verify_long_pairs<64, ONE>(count, wave, n_waves, va, one, stage);
   const unsigned long long base = append_block<kWaves>(rfill, rpart, &ctr->results);
   for (uint32_t x = lane; x < rfill; x += 64)
     if (base + x < results_cap) results[base + x] = rk[x];
@@ -662,12 +668,8 @@ hipError_t launch_verify(const uint2 *queue, uint2 *longq, unsigned long long ca
   if (!rows.bm2) w2 = 0;
   if (w2 != 0 && w2 != 2 && w2 != 4 && w2 != 8) return hipErrorInvalidValue;
   if (n_tasks == 0 || stripes == 0 || stripes > kQueueStripes) return hipErrorInvalidValue;
-  // only pairs that passed a cascade test are deferred: they are nearly all
-  // true pairs, which a lane's merge cannot leave early; without a cascade
-  // most survivors are false, and a lane's merge rejects them in a few
-  // windows
   const VerifyArgs va{rows, cols, side_task, tasks, tables, ib, jb, survivors_only,
-                      survivors_only || !rows.bm2 ? nullptr : longq};
+                      survivors_only ? nullptr : longq};
   const bool one = n_tasks == 1;
   switch (w2 * 2 + (one ? 1 : 0)) {
     case 0: launch_verify_as<0, false>(queue, cap, stripes, va, results, results_cap, ctr, st); break;

@@ -1323,6 +1323,7 @@ struct JoinRun {
   unsigned long long *results = nullptr;
   int ib = 1, jb = 1, tb = 0;
   uint32_t w2 = 0;
+  bool defer_long = false;        // pairs of long sets go to the group merge
   VerifySpace vrows{}, vcols{};
   FilterConfig cfg{};
   std::vector<PrefixRun> runs;    // rows past the cutoff
@@ -1389,8 +1390,9 @@ void launch_round(const JoinRun &jr, FilterConfig cfg, uint2 *queue, uint64_t qc
   const int ib = jr.ib, jb = jr.jb;
   const uint32_t so = jr.jc.survivors_only ? 1u : 0u;
   JoinCounters *ctr = jr.ctr;
+  uint2 *longq = jr.defer_long ? queue + qcap : nullptr;
   go(L, st, [=](hipStream_t s) {
-    return launch_verify(queue, queue + qcap, scap, stripes, vr, vc, side_task, tasks, n_tasks, tables,
+    return launch_verify(queue, longq, scap, stripes, vr, vc, side_task, tasks, n_tasks, tables,
                          ib, jb, so, w2, results, res_cap, ctr, s);
   });
   if (tm) check(hipEventRecord(tm->verify.back().ev[1], st));
@@ -1773,13 +1775,18 @@ void join_begin(Space &R, Space &C, const std::vector<TaskIn> &tasks, const Join
     if (R.bm_words[k] > w2 && R.bm_words[k] <= kCascadeWords && C.bitmaps(R.bm_words[k]))
       w2 = R.bm_words[k];
   const bool cascade = automatic && !jc.survivors_only && pl.n_slots > 0 && w2 > pl.slot_words[0];
-  // wide bitmaps for pairs of large sets (automatic mode, as the cascade);
-  // an index holds its own
-  if (cascade) {
+  // In automatic mode every survivor has passed a test at the cascade width or
+  // a wider one, so most are true pairs, which a lane's merge cannot leave
+  // early: pairs of long sets go to the group merge, and pairs of large sets
+  // are first tested at the wide width (an index holds its own wide bitmaps).
+  // With a fixed width most survivors can be false, and a lane's merge rejects
+  // them in a few windows.
+  const bool tested = automatic && !jc.survivors_only && pl.n_slots > 0;
+  if (tested) {
     space_wide(R, ar, st, L);
     if (!jc.cols_resident) space_wide(C, ar, st, L);
   }
-  const bool wide = cascade && R.bmw && C.bmw;
+  const bool wide = tested && R.bmw && C.bmw;
   const VerifySpace vrows{R.d_sides, R.side_of, R.perm, R.sizes, cascade ? R.bitmaps(w2) : nullptr,
                           (uint32_t)R.n, wide ? R.bmw : nullptr, R.wide_lo, R.wide_slot};
   const VerifySpace vcols{C.d_sides, C.side_of, C.perm, C.sizes, cascade ? C.bitmaps(w2) : nullptr,
@@ -1806,6 +1813,7 @@ void join_begin(Space &R, Space &C, const std::vector<TaskIn> &tasks, const Join
   jr.jb = jb;
   jr.tb = tb;
   jr.w2 = w2;
+  jr.defer_long = tested;
   jr.vrows = vrows;
   jr.vcols = vcols;
   FilterConfig &cfg = jr.cfg;
@@ -1960,7 +1968,7 @@ void join_end(const JoinRun &jr, Arena &ar, hipStream_t st, RoundTimes &tm, Time
           results = nr;
           res_cap = ncap;
         }
-        check(launch_verify(pqueue, pqueue + ccap, ccap, 1, vrows, vcols, d_side_task, d_tasks,
+        check(launch_verify(pqueue, jr.defer_long ? pqueue + ccap : nullptr, ccap, 1, vrows, vcols, d_side_task, d_tasks,
                             n_tasks, d_tables, ib, jb, jc.survivors_only ? 1u : 0u, w2, results,
                             res_cap, ctr, st));
         d2h(&ctr_h, ctr, 1, st);

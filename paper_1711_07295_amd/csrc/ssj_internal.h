@@ -396,7 +396,7 @@ struct VerifySpace {
 // the wide test.  n_tasks: tasks of the call (>= 1); the column of an entry
 // lies in its task's column side.
 // longq (optional, stripes * cap entries, ctr->long_count zero): the pairs of long
-// sets that pass the bitmap tests are merged there by whole waves, in a
+// sets that pass the bitmap tests are merged there by groups of lanes, in a
 // second launch on the same stream.
 // The queue has `stripes` stripes of cap slots each.
 hipError_t launch_verify(const uint2 *queue, uint2 *longq, unsigned long long cap,
