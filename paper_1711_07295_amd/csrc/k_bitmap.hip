@@ -53,7 +53,7 @@ __global__ __launch_bounds__(kBlock) void k_build_bitmaps(
   const uint32_t sid = perm ? side_of[x] : side_of_index(sides, n_sides, x);
   const SideDesc sd = sides[sid];
   const uint64_t k = perm ? perm[x] : x - sd.base;
-  if (k >= sd.n) return;
+  if (k >= sd.n || (ctr->error & (kErrOffsets | kErrTooBig))) return;
   const uint32_t *__restrict__ tokens = sd.tokens;
   const uint64_t o0 = sd.offsets[k], o1 = sd.offsets[k + 1];
   const uint32_t nt = (uint32_t)(o1 - o0);
@@ -119,6 +119,8 @@ __global__ __launch_bounds__(kBlock) void k_build_bitmaps_seg(
   const SideDesc sd = sides[side_of_block(sides, n_sides, blockIdx.x)];
   const uint64_t seg0 = (uint64_t)(blockIdx.x - sd.blk0) * kSegSets;
   if (seg0 >= sd.n) return;  // whole workgroup leaves together
+  // malformed offsets, found by the launch before and not yet seen by the host
+  if (ctr->error & (kErrOffsets | kErrTooBig)) return;
   const uint32_t nseg = (uint32_t)min((uint64_t)kSegSets, sd.n - seg0);
   const uint64_t *__restrict__ offsets = sd.offsets;
   const uint32_t *__restrict__ tokens = sd.tokens;

@@ -152,6 +152,59 @@ class HostPairs {
   size_t idle_bytes_ = 0;
 };
 
+// Page-locked host blocks of 4 KiB to 1 MiB (powers of two) for a call's
+// small uploads and for what its kernels write to the host: a copy from or to
+// pageable memory holds the calling thread, and a kernel can only write to
+// page-locked memory.  A call gives its blocks back after its last
+// synchronisation; at most kIdleMax bytes stay idle.
+class PinnedPool {
+ public:
+  static constexpr size_t kMin = size_t(1) << 12, kMax = size_t(1) << 20;
+  static PinnedPool &get() {
+    static PinnedPool *h = new PinnedPool;  // never destroyed, as HostPairs
+    return *h;
+  }
+  static size_t rounded(size_t bytes) {
+    size_t cap = kMin;
+    while (cap < bytes) cap *= 2;
+    return cap;
+  }
+  // a block of `cap` bytes (from rounded()), nullptr when there is none
+  void *take(size_t cap) {
+    {
+      std::lock_guard<std::mutex> lk(mu_);
+      auto &v = idle_[cap];
+      if (!v.empty()) {
+        void *p = v.back();
+        v.pop_back();
+        idle_bytes_ -= cap;
+        return p;
+      }
+    }
+    void *p = nullptr;
+    if (hipHostMalloc(&p, cap, hipHostMallocDefault) == hipSuccess && p) return p;
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  void give(void *p, size_t cap) {
+    {
+      std::lock_guard<std::mutex> lk(mu_);
+      if (idle_bytes_ + cap <= kIdleMax) {
+        idle_[cap].push_back(p);
+        idle_bytes_ += cap;
+        return;
+      }
+    }
+    (void)hipHostFree(p);
+  }
+
+ private:
+  static constexpr size_t kIdleMax = size_t(64) << 20;
+  std::mutex mu_;
+  std::map<size_t, std::vector<void *>> idle_;
+  size_t idle_bytes_ = 0;
+};
+
 // Device memory chunks kept between calls, per device.  A call takes chunks
 // at its start and gives them back only after its final stream
 // synchronisation, so a chunk is never in use by two calls.  Chunk sizes are
@@ -257,13 +310,34 @@ class Arena {
     // an owned arena's work has finished by now: its owner synchronised
     // after the uploads, and hipFree waits for the device
     for (void *p : staged_) HostPairs::get().release(p);
+    for (auto &b : pinned_) PinnedPool::get().give(b.first, b.second);
   }
-  // Host memory for an upload from this arena's stream: page-locked when
-  // large (the copy then runs asynchronously, without a staged copy that
-  // waits for the work queued before it), kept until the arena ends.
+  // Page-locked host memory that the device may read and write, kept until
+  // the arena ends; nullptr when there is none (or more than 1 MiB).
+  template <class T>
+  T *pinned(uint64_t n) {
+    const uint64_t bytes = (std::max<uint64_t>(n, 1) * sizeof(T) + 63) & ~63ull;
+    if (bytes > PinnedPool::kMax) return nullptr;
+    if (bytes > pin_left_) {
+      const size_t cap = PinnedPool::rounded(bytes);
+      void *p = PinnedPool::get().take(cap);
+      if (!p) return nullptr;
+      pinned_.push_back({p, cap});
+      pin_next_ = static_cast<char *>(p);
+      pin_left_ = cap;
+    }
+    T *out = reinterpret_cast<T *>(pin_next_);
+    pin_next_ += bytes;
+    pin_left_ -= bytes;
+    return out;
+  }
+  // Host memory for an upload from this arena's stream, page-locked (the copy
+  // then runs asynchronously, without a staged copy that waits for the work
+  // queued before it), kept until the arena ends.
   template <class T>
   T *stage(uint64_t n) {
     const uint64_t bytes = std::max<uint64_t>(n, 1) * sizeof(T);
+    if (T *q = pinned<T>(n)) return q;
     void *p = HostPairs::get().alloc((bytes + sizeof(ssj_pair) - 1) / sizeof(ssj_pair));
     if (!p) throw std::bad_alloc();
     staged_.push_back(p);
@@ -307,6 +381,9 @@ class Arena {
   int dev_ = 0;
   std::vector<std::pair<void *, uint64_t>> chunks_;
   std::vector<void *> staged_;  // host upload buffers (HostPairs)
+  std::vector<std::pair<void *, size_t>> pinned_;  // ... and PinnedPool blocks
+  char *pin_next_ = nullptr;
+  uint64_t pin_left_ = 0;
   char *next_ = nullptr;
   uint64_t left_ = 0;
 };
@@ -392,7 +469,10 @@ struct Space {
   std::vector<uint32_t> sstart_h;
   std::vector<uint32_t> side_max; // largest size of each side
   JoinCounters *ctr = nullptr;    // preparation counters
-  JoinCounters ctr_h{};
+  // page-locked memory: the counters' error and max_size, or what the
+  // one-launch preparation (space_small) writes; the group starts
+  SmallHead *h_head = nullptr;
+  uint32_t *h_sstart = nullptr;
   // bitmaps in size order, one array per width
   uint32_t n_bm = 0;
   // a build of every set (which checks the token order) is enqueued
@@ -419,10 +499,8 @@ struct Space {
   }
 };
 
-// Side table, sizes and offset checks of every side.  The caller
-// synchronises before space_sort (ctr_h holds the largest size).
-void space_begin(Space &sp, const ssj_sets *const *sides, uint32_t n_sides, Arena &ar,
-                 hipStream_t st) {
+// The side table of a space.
+void space_sides(Space &sp, const ssj_sets *const *sides, uint32_t n_sides) {
   sp.n_sides = n_sides;
   sp.h_sides.resize(n_sides);
   uint64_t base = 0, blk = 0;
@@ -441,14 +519,59 @@ void space_begin(Space &sp, const ssj_sets *const *sides, uint32_t n_sides, Aren
   if (base >= 0xFFFFFFFFull || blk >= 0xFFFFFFFFull) throw Fail{SSJ_E_UNSUPPORTED};
   sp.n = base;
   sp.seg_blocks = (uint32_t)blk;
+}
+
+// Prepares a space of few sets (kSmallSets) in one launch, when its group
+// starts are bound to fit kSmallStarts entries (the sides' token counts bound
+// the sizes); false when it is larger.  `ctr`, the call's counters, is
+// cleared on the way.  The caller waits for the stream before space_finish.
+constexpr uint64_t kSmallStarts = 1ull << 17;
+bool space_small(Space &sp, Arena &ar, JoinCounters *ctr, hipStream_t st) {
+  uint64_t most = 0;  // tokens of a side: no size is larger
+  for (const SideDesc &d : sp.h_sides) most = std::max(most, d.n_tokens);
+  if (sp.n == 0 || sp.n > kSmallSets || sp.n_sides > kSmallSides || most >= kSmallStarts ||
+      sp.n_sides * (most + 2) > kSmallStarts ||
+      std::max(1, bits_for(most)) + bits_for(sp.n_sides - 1) > 32)
+    return false;
+  const uint64_t entries = sp.n_sides * (most + 2);
+  SideDesc *h_sides = ar.pinned<SideDesc>(sp.n_sides);
+  sp.h_head = ar.pinned<SmallHead>(1);
+  sp.h_sstart = ar.pinned<uint32_t>(entries);
+  if (!h_sides || !sp.h_head || !sp.h_sstart) {
+    sp.h_head = nullptr;
+    return false;
+  }
+  std::memcpy(h_sides, sp.h_sides.data(), sp.n_sides * sizeof(SideDesc));
+  sp.d_sides = ar.alloc<SideDesc>(sp.n_sides);
+  sp.sizes = ar.alloc<uint32_t>(sp.n);
+  sp.side_of = ar.alloc<uint32_t>(sp.n);
+  sp.perm = ar.alloc<uint32_t>(sp.n);
+  sp.rank = ar.alloc<uint32_t>(sp.n);
+  sp.sstart = ar.alloc<uint32_t>(entries);
+  check(launch_prepare_small(SmallSpace{h_sides, sp.d_sides, sp.n_sides, (uint32_t)sp.n, sp.sizes,
+                                        sp.side_of, sp.perm, sp.rank, sp.sstart, sp.h_sstart,
+                                        sp.h_head, ctr},
+                             st));
+  return true;
+}
+
+// Side table (space_sides), sizes and offset checks of every side.  The caller
+// synchronises before space_sort (h_head holds the largest size).
+void space_begin(Space &sp, Arena &ar, hipStream_t st) {
+  const uint32_t n_sides = sp.n_sides;
   sp.d_sides = ar.alloc<SideDesc>(n_sides);
-  h2d(sp.d_sides, sp.h_sides.data(), n_sides, st);
+  SideDesc *h_sides = ar.stage<SideDesc>(n_sides);
+  std::memcpy(static_cast<void *>(h_sides), sp.h_sides.data(), n_sides * sizeof(SideDesc));
+  h2d(sp.d_sides, h_sides, n_sides, st);
   sp.ctr = ar.alloc<JoinCounters>(1);
   check(launch_reset_all(sp.ctr, st));
   sp.sizes = ar.alloc<uint32_t>(sp.n);
   sp.side_of = ar.alloc<uint32_t>(sp.n);
   check(launch_set_sizes(sp.d_sides, n_sides, sp.n, sp.sizes, sp.side_of, sp.ctr, st));
-  d2h(&sp.ctr_h, sp.ctr, 1, st);
+  static_assert(offsetof(JoinCounters, max_size) == offsetof(JoinCounters, error) + 4 &&
+                    sizeof(SmallHead) == 8, "error and max_size side by side");
+  sp.h_head = ar.stage<SmallHead>(1);
+  d2h(reinterpret_cast<uint32_t *>(sp.h_head), &sp.ctr->error, 2, st);
 }
 
 // Stable sort by (side, size), group starts of every side (copied to the
@@ -456,8 +579,8 @@ void space_begin(Space &sp, const ssj_sets *const *sides, uint32_t n_sides, Aren
 // permutation when bitmaps are to be built.
 // Arrays the space keeps come from `ar`, the sort's temporaries from `tmp_ar`.
 void space_sort(Space &sp, bool need_rank, Arena &ar, Arena &tmp_ar, hipStream_t st) {
-  if (sp.ctr_h.error & (kErrOffsets | kErrTooBig)) throw Fail{SSJ_E_INVALID};
-  sp.max_size = sp.ctr_h.max_size;
+  if (sp.h_head->error & (kErrOffsets | kErrTooBig)) throw Fail{SSJ_E_INVALID};
+  sp.max_size = sp.h_head->max_size;
   if ((uint64_t)sp.max_size * 2 + 2 > kMaxTable) throw Fail{SSJ_E_UNSUPPORTED};
   sp.stride = sp.max_size + 2;
   const int size_bits = std::max(1, bits_for(sp.max_size));
@@ -483,12 +606,18 @@ void space_sort(Space &sp, bool need_rank, Arena &ar, Arena &tmp_ar, hipStream_t
     sp.rank = ar.alloc<uint32_t>(n);
     check(launch_invert_perm(sp.d_sides, sp.perm, sp.side_of, n, sp.rank, st));
   }
-  sp.sstart_h.assign((size_t)sp.n_sides * sp.stride, 0);
-  d2h(sp.sstart_h.data(), sp.sstart, sp.sstart_h.size(), st);
+  const uint64_t entries = (uint64_t)sp.n_sides * sp.stride;
+  sp.h_sstart = tmp_ar.stage<uint32_t>(entries);
+  d2h(sp.h_sstart, sp.sstart, entries, st);
 }
 
-// Largest size of every side, from its group starts.
+// The group starts and with them the largest size of every side; the stream
+// has been waited for.
 void space_finish(Space &sp) {
+  if (sp.h_head->error & (kErrOffsets | kErrTooBig)) throw Fail{SSJ_E_INVALID};
+  sp.max_size = sp.h_head->max_size;
+  sp.stride = sp.max_size + 2;
+  sp.sstart_h.assign(sp.h_sstart, sp.h_sstart + (size_t)sp.n_sides * sp.stride);
   sp.side_max.assign(sp.n_sides, 0);
   for (uint32_t s = 0; s < sp.n_sides; ++s) {
     const uint32_t *t = sp.ss(s);
@@ -532,11 +661,12 @@ void space_signs(Space &sp, uint32_t words, Arena &ar, hipStream_t st, Launcher 
     uint4 *planes = ar.alloc<uint4>((sp.n + kSignPad) * words * 2);
     const uint64_t *bm = sp.bm[k];
     const uint64_t n = sp.n;
-    if (ranges && !ranges->empty()) {
-      const PosRange *d_ranges = nullptr;
-      PosRange *up = ar.alloc<PosRange>(ranges->size());
-      h2d(up, ranges->data(), ranges->size(), st);
-      d_ranges = up;
+    // (few sets: all of them cost less than the list's upload)
+    if (ranges && !ranges->empty() && n > kSmallSets) {
+      PosRange *h_ranges = ar.stage<PosRange>(ranges->size());
+      std::memcpy(h_ranges, ranges->data(), ranges->size() * sizeof(PosRange));
+      PosRange *d_ranges = ar.alloc<PosRange>(ranges->size());
+      h2d(d_ranges, h_ranges, ranges->size(), st);
       const uint32_t nr = (uint32_t)ranges->size();
       const uint64_t total = (uint64_t)ranges->back().first + kSignPad;
       go(L, st, [=](hipStream_t s) {
@@ -1259,21 +1389,69 @@ std::vector<PosRange> sign_ranges(const Plan &pl, const std::vector<TaskIn> &tas
   return out;
 }
 
+// Timing events kept between calls, per device (making and destroying the
+// dozen of a call takes longer than recording them); at most kIdleMax idle.
+class EventPool {
+ public:
+  static EventPool &get() {
+    static EventPool *p = new EventPool;  // never destroyed, as HostPairs
+    return *p;
+  }
+  hipEvent_t take(int dev) {
+    {
+      std::lock_guard<std::mutex> lk(mu_);
+      auto &v = idle_[dev];
+      if (!v.empty()) {
+        hipEvent_t e = v.back();
+        v.pop_back();
+        return e;
+      }
+    }
+    hipEvent_t e = nullptr;
+    check(hipEventCreate(&e));
+    return e;
+  }
+  void give(int dev, hipEvent_t e) {
+    {
+      std::lock_guard<std::mutex> lk(mu_);
+      auto &v = idle_[dev];
+      if (v.size() < kIdleMax) {
+        v.push_back(e);
+        return;
+      }
+    }
+    (void)hipEventDestroy(e);
+  }
+
+ private:
+  static constexpr size_t kIdleMax = 256;
+  std::mutex mu_;
+  std::map<int, std::vector<hipEvent_t>> idle_;
+};
+
+// An event of the current device, back in the pool when it goes.  Its holder
+// has waited for the work it marks.
+struct Event {
+  hipEvent_t ev = nullptr;
+  int dev = 0;
+  Event() {
+    check(hipGetDevice(&dev));
+    ev = EventPool::get().take(dev);
+  }
+  ~Event() {
+    if (ev) EventPool::get().give(dev, ev);
+  }
+  Event(const Event &) = delete;
+  Event &operator=(const Event &) = delete;
+  void record(hipStream_t st) { check(hipEventRecord(ev, st)); }
+  void wait() { check(hipEventSynchronize(ev)); }
+};
+
 struct Timer {
-  hipEvent_t ev[2] = {nullptr, nullptr};
-  Timer(const Timer &) = delete;
-  Timer &operator=(const Timer &) = delete;
-  Timer() {
-    check(hipEventCreate(&ev[0]));
-    check(hipEventCreate(&ev[1]));
-  }
-  ~Timer() {
-    if (ev[0]) (void)hipEventDestroy(ev[0]);
-    if (ev[1]) (void)hipEventDestroy(ev[1]);
-  }
+  Event a, b;
   float ms() const {
     float v = 0;
-    (void)hipEventElapsedTime(&v, ev[0], ev[1]);
+    (void)hipEventElapsedTime(&v, a.ev, b.ev);
     return v;
   }
 };
@@ -1331,12 +1509,28 @@ struct JoinRun {
   uint64_t n_probe = 0;
 };
 
-// Kernel timings of a join's rounds (events must not move).
+// Kernel timings of a join's rounds: one event at every boundary (events must
+// not move).
 struct RoundTimes {
-  std::deque<Timer> filter, verify;
-  std::vector<uint32_t> filter_slot;
+  enum { kStart = -1, kVerify = -2, kFinish = -3 };
+  struct Mark {
+    Event ev;
+    int what = kStart;  // the step that ends here: a width slot, kVerify, kFinish; or a round's start
+  };
+  std::deque<Mark> marks;
   uint32_t launches = 0;
   hipEvent_t graph_ev[2] = {nullptr, nullptr};  // around a prepared join's graph
+  void mark(int what, hipStream_t st) {
+    marks.emplace_back();
+    marks.back().what = what;
+    marks.back().ev.record(st);
+  }
+  // milliseconds of mark k's step, from the mark before it
+  float ms(size_t k) const {
+    float v = 0;
+    if (k) (void)hipEventElapsedTime(&v, marks[k - 1].ev.ev, marks[k].ev.ev);
+    return v;
+  }
 };
 
 // Whether the tiles of width slot k get a wave each (kDirectTiles).
@@ -1354,6 +1548,7 @@ void launch_round(const JoinRun &jr, FilterConfig cfg, uint2 *queue, uint64_t qc
   const uint32_t stripes = queue_stripes(qcap);
   const uint64_t scap = qcap / stripes;  // slots of one stripe
   cfg.cap = (uint32_t)scap;
+  if (tm) tm->mark(RoundTimes::kStart, st);
   cfg.stripes = stripes;
   // one launch per width slot; after an overflow the later launches of
   // the round leave at once and resume in the next round
@@ -1370,18 +1565,9 @@ void launch_round(const JoinRun &jr, FilterConfig cfg, uint2 *queue, uint64_t qc
     const FilterArgs fa{R.bitmaps(w), C.bitmaps(w), mf ? R.signs(w) : nullptr,
                         mf ? C.signs(w) : nullptr, R.sizes, C.sizes, C.sstart, jr.d_tables,
                         jr.d_tasks, jr.d_blocks, jr.d_tile_block, queue, jr.ctr, rin, rout, cfg};
-    if (tm) {
-      tm->filter.emplace_back();
-      tm->filter_slot.push_back(k);
-      ++tm->launches;
-      check(hipEventRecord(tm->filter.back().ev[0], st));
-    }
+    if (tm) ++tm->launches;
     go(L, st, [=](hipStream_t s) { return launch_filter(w, cos, fa, s); });
-    if (tm) check(hipEventRecord(tm->filter.back().ev[1], st));
-  }
-  if (tm) {
-    tm->verify.emplace_back();
-    check(hipEventRecord(tm->verify.back().ev[0], st));
+    if (tm) tm->mark((int)k, st);
   }
   const VerifySpace vr = jr.vrows, vc = jr.vcols;
   const uint32_t *side_task = jr.d_side_task, *tables = jr.d_tables, w2 = jr.w2;
@@ -1395,7 +1581,7 @@ void launch_round(const JoinRun &jr, FilterConfig cfg, uint2 *queue, uint64_t qc
     return launch_verify(queue, longq, scap, stripes, vr, vc, side_task, tasks, n_tasks, tables,
                          ib, jb, so, w2, results, res_cap, ctr, s);
   });
-  if (tm) check(hipEventRecord(tm->verify.back().ev[1], st));
+  if (tm) tm->mark(RoundTimes::kVerify, st);
 }
 
 // Plans the tasks over prepared spaces R (rows) and C (columns; C may be
@@ -1716,22 +1902,32 @@ void join_begin(Space &R, Space &C, const std::vector<TaskIn> &tasks, const Join
   constexpr uint64_t kBlockWords = sizeof(RowBlock) / 4, kTaskWords = sizeof(TaskDesc) / 4;
   static_assert(sizeof(RowBlock) % 8 == 0 && sizeof(TaskDesc) % 8 == 0, "8-byte layout");
   const uint64_t nB = pl.blocks.size(), nT = pl.tasks.size(), nS = side_task.size();
-  const uint64_t n_packed = kBlockWords * nB + kTaskWords * nT + nS + pl.tables.size();
+  // ... and a short tile list (tile -> block), which else a kernel expands
+  constexpr uint32_t kUploadTiles = 4096;
+  const uint32_t n_list = pl.n_tiles <= kUploadTiles ? pl.n_tiles : 0;
+  const uint64_t list_at = kBlockWords * nB + kTaskWords * nT + nS + pl.tables.size();
+  const uint64_t n_packed = list_at + n_list;
   uint32_t *hp = ar.stage<uint32_t>(n_packed);
   std::memcpy(hp, pl.blocks.data(), nB * sizeof(RowBlock));
   std::memcpy(hp + kBlockWords * nB, pl.tasks.data(), nT * sizeof(TaskDesc));
   std::memcpy(hp + kBlockWords * nB + kTaskWords * nT, side_task.data(), nS * 4);
   std::memcpy(hp + kBlockWords * nB + kTaskWords * nT + nS, pl.tables.data(),
               pl.tables.size() * 4);
+  for (uint64_t b = 0; n_list && b < nB; ++b)
+    std::fill(hp + list_at + pl.blocks[b].tile_begin,
+              hp + list_at + (b + 1 < nB ? pl.blocks[b + 1].tile_begin : pl.n_tiles), (uint32_t)b);
   uint32_t *d_packed = ar.alloc<uint32_t>(n_packed);
   h2d(d_packed, hp, n_packed, st);
   const RowBlock *d_blocks = reinterpret_cast<const RowBlock *>(d_packed);
   const TaskDesc *d_tasks = reinterpret_cast<const TaskDesc *>(d_packed + kBlockWords * nB);
   const uint32_t *d_side_task = d_packed + kBlockWords * nB + kTaskWords * nT;
   const uint32_t *d_tables = d_side_task + nS;
-  uint32_t *d_tile_block = ar.alloc<uint32_t>(pl.n_tiles);
-  check(launch_expand_tiles(d_blocks, (uint32_t)nB, pl.n_tiles, d_tile_block, st));
-  if (t_prep) check(hipEventRecord(t_prep->ev[1], st));
+  uint32_t *d_tile_block = d_packed + list_at;
+  if (!n_list) {
+    d_tile_block = ar.alloc<uint32_t>(pl.n_tiles);
+    check(launch_expand_tiles(d_blocks, (uint32_t)nB, pl.n_tiles, d_tile_block, st));
+  }
+  if (t_prep) t_prep->b.record(st);
 
   // filter / verify rounds.  A wave reserves queue slots a chunk at a time
   // and writes staged runs (at most kFilterStage pairs) into its chunk; the
@@ -1860,10 +2056,28 @@ void join_end(const JoinRun &jr, Arena &ar, hipStream_t st, RoundTimes &tm, Time
   uint64_t prefix_candidates = 0;
   uint64_t results_n = 0, queue_slots = 0;
   JoinCounters ctr_h{};
+  // A round ends with the counters on the host, and with them the sorted
+  // pairs when there are few and no later step adds to them.
+  constexpr size_t kCtrBytes = offsetof(JoinCounters, queue_next);
+  FinishArgs fin{};
+  fin.ctr = ctr;
+  fin.n_tasks = n_tasks;
+  fin.ib = ib;
+  fin.jb = jb;
+  fin.bits = tb + ib + jb;
+  fin.h_ctr = ar.pinned<uint32_t>(kCtrBytes / 4);
+  if (!fin.h_ctr) throw Fail{SSJ_E_NOMEM};
+  fin.h_start = ar.pinned<uint64_t>((uint64_t)n_tasks + 1);
+  fin.h_pairs = ar.pinned<ssj_pair>(kSmallResults);
+  fin.max_results = n_probe || !fin.h_start || !fin.h_pairs ? 0 : kSmallResults;
   if (pl.n_tiles) {
     for (;;) {
-      d2h(&ctr_h, ctr, 1, st);
+      fin.keys = results;
+      if (tm.marks.empty()) tm.mark(RoundTimes::kStart, st);
+      check(launch_finish(fin, st));
+      tm.mark(RoundTimes::kFinish, st);
       sync(st);
+      std::memcpy(static_cast<void *>(&ctr_h), fin.h_ctr, kCtrBytes);
       if (ctr_h.error & kErrUnsorted) throw Fail{SSJ_E_UNSORTED};
       queue_slots += std::min<uint64_t>(ctr_h.queue_count, qcap);
       results_n = ctr_h.results;
@@ -1902,7 +2116,7 @@ void join_end(const JoinRun &jr, Arena &ar, hipStream_t st, RoundTimes &tm, Time
   // verify, chunk by chunk so that each chunk's candidates fit one queue
   if (n_probe) {
     Timer t_index, t_pver;
-    check(hipEventRecord(t_index.ev[0], st));
+    t_index.a.record(st);
     uint32_t *d_ilen = ar.alloc<uint32_t>(ilen.size());
     h2d(d_ilen, ilen.data(), ilen.size(), st);
     uint32_t *len = ar.alloc<uint32_t>(C.n);
@@ -1933,7 +2147,7 @@ void join_end(const JoinRun &jr, Arena &ar, hipStream_t st, RoundTimes &tm, Time
     std::vector<unsigned long long> off_h(n_probe + 1);
     d2h(off_h.data(), row_off, n_probe, st);
     d2h(&off_h[n_probe], d_tot + 1, 1, st);
-    check(hipEventRecord(t_index.ev[1], st));
+    t_index.b.record(st);
     sync(st);
     uint64_t biggest = 0;
     for (uint64_t x = 0; x < n_probe; ++x) {
@@ -1950,7 +2164,7 @@ void join_end(const JoinRun &jr, Arena &ar, hipStream_t st, RoundTimes &tm, Time
     const int bs = std::max(1, bits_for(C.n ? C.n - 1 : 0)), br = std::max(1, bits_for(R.n ? R.n - 1 : 0));
     for (int b = 0; b < bs; b += 8) cshifts[ncs++] = b;
     for (int b = 0; b < br; b += 8) cshifts[ncs++] = 32 + b;
-    check(hipEventRecord(t_pver.ev[0], st));
+    t_pver.a.record(st);
     for (uint64_t x0 = 0; x0 < n_probe;) {
       uint64_t x1 = x0 + 1;
       while (x1 < n_probe && off_h[x1 + 1] - off_h[x0] <= ccap) ++x1;
@@ -1979,7 +2193,7 @@ void join_end(const JoinRun &jr, Arena &ar, hipStream_t st, RoundTimes &tm, Time
       }
       x0 = x1;
     }
-    check(hipEventRecord(t_pver.ev[1], st));
+    t_pver.b.record(st);
     sync(st);
     prefix_ms_index = t_index.ms();
     prefix_ms_verify = t_pver.ms();
@@ -1987,10 +2201,19 @@ void join_end(const JoinRun &jr, Arena &ar, hipStream_t st, RoundTimes &tm, Time
   }
 
   // emit: sort the keys (task, i, j) on all their digits, split, copy out
-  Timer t_emit;
-  check(hipEventRecord(t_emit.ev[0], st));
+  float emit_ms = 0;
   jo.task_start.assign(n_tasks + 1, 0);
-  if (results_n) {
+  if (results_n && results_n <= fin.max_results && pl.n_tiles) {
+    // sorted on the host already
+    jo.pairs = HostPairs::get().alloc(results_n);
+    if (!jo.pairs) throw Fail{SSJ_E_NOMEM};
+    jo.count = results_n;
+    std::memcpy(jo.pairs, fin.h_pairs, results_n * sizeof(ssj_pair));
+    std::memcpy(jo.task_start.data(), fin.h_start, ((size_t)n_tasks + 1) * 8);
+    emit_ms = tm.ms(tm.marks.size() - 1);
+  } else if (results_n) {
+    Timer t_emit;
+    t_emit.a.record(st);
     unsigned long long *tmp = ar.alloc<unsigned long long>(results_n);
     uint32_t *scr = ar.alloc<uint32_t>(radix_scratch_words(results_n));
     int shifts[8], ns = 0;
@@ -2003,11 +2226,17 @@ void join_end(const JoinRun &jr, Arena &ar, hipStream_t st, RoundTimes &tm, Time
     jo.pairs = HostPairs::get().alloc(results_n);
     if (!jo.pairs) throw Fail{SSJ_E_NOMEM};
     jo.count = results_n;
-    d2h(jo.pairs, dpairs, results_n, st);
-    d2h(jo.task_start.data(), dstart, n_tasks + 1, st);
+    // short lists are in pageable memory: through a page-locked block
+    ssj_pair *h_pairs = ar.pinned<ssj_pair>(results_n);
+    d2h(h_pairs ? h_pairs : jo.pairs, dpairs, results_n, st);
+    uint64_t *h_start = ar.stage<uint64_t>((uint64_t)n_tasks + 1);
+    d2h(h_start, dstart, n_tasks + 1, st);
+    t_emit.b.record(st);
+    sync(st);
+    if (h_pairs) std::memcpy(jo.pairs, h_pairs, results_n * sizeof(ssj_pair));
+    std::memcpy(jo.task_start.data(), h_start, ((size_t)n_tasks + 1) * 8);
+    emit_ms = t_emit.ms();
   }
-  check(hipEventRecord(t_emit.ev[1], st));
-  sync(st);
   if (stats) {
     stats->band_pairs = pl.band_pairs;
     for (const auto &v : ctr_h.survivors) stats->survivors += v[0];
@@ -2027,18 +2256,19 @@ void join_end(const JoinRun &jr, Arena &ar, hipStream_t st, RoundTimes &tm, Time
     float gms = 0;
     if (tm.graph_ev[0]) (void)hipEventElapsedTime(&gms, tm.graph_ev[0], tm.graph_ev[1]);
     stats->ms_filter = gms;
-    for (size_t k = 0; k < tm.filter.size(); ++k) {
-      const float ms = tm.filter[k].ms();
-      stats->ms_filter += ms;
-      stats->class_ms[tm.filter_slot[k]] += ms;
+    for (size_t k = 0; k < tm.marks.size(); ++k) {
+      const int what = tm.marks[k].what;
+      if (what == RoundTimes::kVerify) stats->ms_verify += tm.ms(k);
+      if (what < 0) continue;
+      stats->ms_filter += tm.ms(k);
+      stats->class_ms[what] += tm.ms(k);
     }
-    for (auto &t : tm.verify) stats->ms_verify += t.ms();
     // prefix-filtered rows: index and probe count as filtering, the
     // deduplication and verification of their candidates as verification
     stats->ms_filter += prefix_ms_index;
     stats->ms_verify += prefix_ms_verify;
     (void)prefix_candidates;
-    stats->ms_emit = t_emit.ms();
+    stats->ms_emit = emit_ms;
   }
 }
 
@@ -2095,27 +2325,22 @@ float ms_since(std::chrono::steady_clock::time_point t0) {
 
 // ssj_self_join / ssj_rs_join: one task, each side in its own space (the
 // self-join's row and column space are one).
-// A point in a stream the host can wait for without waiting for the work
-// enqueued after it.
-struct Marker {
-  hipEvent_t ev = nullptr;
-  Marker() { check(hipEventCreateWithFlags(&ev, hipEventDisableTiming)); }
-  ~Marker() {
-    if (ev) (void)hipEventDestroy(ev);
-  }
-  Marker(const Marker &) = delete;
-  Marker &operator=(const Marker &) = delete;
-  void record(hipStream_t st) { check(hipEventRecord(ev, st)); }
-  void wait() { check(hipEventSynchronize(ev)); }
-};
-
 // In automatic mode the bitmaps up to the cascade width (one build pass,
-// the narrower widths folded from it) do not depend on the plan: they are
-// enqueued before the host waits for the group starts, so that the device
-// builds them while the host plans.
+// the narrower widths folded from it) do not depend on the plan, nor does a
+// fixed width: they are enqueued before the host waits for the group starts,
+// so that the device builds them while the host plans.  (After the one-launch
+// preparation the host has not seen its checks of the offsets yet; the
+// build leaves at once when they failed.)
 void early_bitmaps(Space &sp, const JoinConfig &jc, Arena &ar, JoinCounters *ctr,
                    hipStream_t st) {
-  if (jc.b_bits != 0 || jc.survivors_only || !sp.rank) return;
+  if (!sp.rank) return;
+  if (jc.b_bits != 0) {
+    if (jc.cutoff) return;  // the cutoff may leave no row to the filter
+    const uint32_t w = filter_padded_words(jc.b_bits / 64);
+    if (w) space_bitmaps(sp, w, jc.b_bits, ar, ctr, st);
+    return;
+  }
+  if (jc.survivors_only) return;
   static constexpr uint32_t words[4] = {1, 2, 4, kCascadeWords}, bits[4] = {64, 128, 256, 512};
   static_assert(kCascadeWords == 8, "the cascade width is the widest of one fold pass");
   space_bitmaps_multi(sp, words, bits, 4, ar, ctr, st);
@@ -2144,19 +2369,26 @@ int join_one(const ssj_sets *R, const uint64_t *r_bm, const ssj_sets *S, const u
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     Arena ar(st);
     Timer t_prep;
-    check(hipEventRecord(t_prep.ev[0], st));
+    t_prep.a.record(st);
     JoinCounters *ctr = ar.alloc<JoinCounters>(1);
-    check(launch_reset_all(ctr, st));
     Space A, B;
-    space_begin(A, &R, 1, ar, st);
-    if (!self) space_begin(B, &S, 1, ar, st);
-    sync(st);
-    space_sort(A, r_bm == nullptr, ar, ar, st);
+    space_sides(A, &R, 1);
+    if (!self) space_sides(B, &S, 1);
+    const bool small = space_small(A, ar, ctr, st);
+    if (!small) {
+      check(launch_reset_all(ctr, st));
+      space_begin(A, ar, st);
+    }
+    if (!self) space_begin(B, ar, st);
+    if (!small || !self) sync(st);
+    if (!small) space_sort(A, r_bm == nullptr, ar, ar, st);
     if (!self) space_sort(B, s_bm == nullptr, ar, ar, st);
-    Marker sorted;
+    Event sorted;
     sorted.record(st);
-    early_bitmaps(A, jc, ar, ctr, st);
-    if (!self) early_bitmaps(B, jc, ar, ctr, st);
+    if (!r_bm) {
+      early_bitmaps(A, jc, ar, ctr, st);
+      if (!self) early_bitmaps(B, jc, ar, ctr, st);
+    }
     sorted.wait();
     space_finish(A);
     if (!self) space_finish(B);
@@ -2259,14 +2491,17 @@ int join_tasks(const ssj_sets *rows, uint32_t n, const uint32_t *p, const uint32
     }
     Arena ar(st);
     Timer t_prep;
-    check(hipEventRecord(t_prep.ev[0], st));
+    t_prep.a.record(st);
     JoinCounters *ctr = ar.alloc<JoinCounters>(1);
-    check(launch_reset_all(ctr, st));
     Space A;
-    space_begin(A, sides.data(), n, ar, st);
-    sync(st);
-    space_sort(A, true, ar, ar, st);
-    Marker sorted;
+    space_sides(A, sides.data(), n);
+    if (!space_small(A, ar, ctr, st)) {
+      check(launch_reset_all(ctr, st));
+      space_begin(A, ar, st);
+      sync(st);
+      space_sort(A, true, ar, ar, st);
+    }
+    Event sorted;
     sorted.record(st);
     early_bitmaps(A, jc, ar, ctr, st);
     sorted.wait();
@@ -2498,7 +2733,8 @@ int ssj_index_create(const ssj_sets *s, uint32_t b_bits, ssj_index **out, void *
     const ssj_sets *side = &idx->sets;
     {
       Arena tmp(st);
-      space_begin(idx->S, &side, 1, idx->ar, st);
+      space_sides(idx->S, &side, 1);
+      space_begin(idx->S, idx->ar, st);
       sync(st);
       space_sort(idx->S, true, idx->ar, tmp, st);
       sync(st);
@@ -2518,9 +2754,10 @@ int ssj_index_create(const ssj_sets *s, uint32_t b_bits, ssj_index **out, void *
         if (filter_shape(idx->S.bm_words[k], true).mfma)
           space_signs(idx->S, idx->S.bm_words[k], idx->ar, st);
       space_wide(idx->S, idx->ar, st);
-      d2h(&idx->S.ctr_h, ctr, 1, st);
+      uint32_t *h_error = tmp.stage<uint32_t>(1);
+      d2h(h_error, &ctr->error, 1, st);
       sync(st);
-      if (idx->S.ctr_h.error & kErrUnsorted) throw Fail{SSJ_E_UNSORTED};
+      if (*h_error & kErrUnsorted) throw Fail{SSJ_E_UNSORTED};
     }
   } catch (const Fail &f) {
     (void)hipGetLastError();
@@ -2578,7 +2815,8 @@ int ssj_plan_self_join_batch(const ssj_sets *sets, uint32_t n_instances, const u
     check(launch_reset_all(ctr, st));
     {
       Arena tmp(st);  // the size sort's temporaries
-      space_begin(plan->S, sides.data(), n_instances, plan->ar, st);
+      space_sides(plan->S, sides.data(), n_instances);
+      space_begin(plan->S, plan->ar, st);
       sync(st);
       space_sort(plan->S, true, plan->ar, tmp, st);
       sync(st);

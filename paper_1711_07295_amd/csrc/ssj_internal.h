@@ -412,6 +412,47 @@ hipError_t launch_split_results(const unsigned long long *keys, uint64_t n, int 
                                 uint32_t n_tasks, ssj_pair *out, uint64_t *task_start,
                                 hipStream_t st);
 
+// ------------------------------------------------------------- small calls
+// Preparation of a space of few sets in one launch and one workgroup (what
+// launch_set_sizes .. launch_invert_perm do in ten): at most kSmallSets sets
+// over at most kSmallSides sides, sizes and side numbers within 32 bits
+// together (n_tokens of a side bounds its sizes).  The counters are cleared;
+// offset errors go to them and to the host.
+constexpr uint32_t kSmallSets = 8192;
+constexpr uint32_t kSmallSides = 1024;
+struct SmallHead {
+  uint32_t error, max_size;
+};
+struct SmallSpace {
+  const SideDesc *h_sides;  // page-locked
+  SideDesc *d_sides;
+  uint32_t n_sides, n;
+  uint32_t *sizes, *side_of, *perm, *rank;
+  uint32_t *sstart;         // [n_sides][max_size + 2], and its copy in page-locked memory
+  uint32_t *h_sstart;
+  SmallHead *h_head;        // page-locked
+  JoinCounters *ctr;
+};
+hipError_t launch_prepare_small(const SmallSpace &a, hipStream_t st);
+
+// The end of a round: the counters up to queue_next go to h_ctr, and when the
+// queue did not fill and there are 1 .. max_results (<= kSmallResults)
+// results, their keys (`bits` bits) are sorted and written as pairs, with
+// the first result of every task (n_tasks + 1 entries).  All h_ pointers are
+// page-locked memory.
+constexpr uint32_t kSmallResults = 4096;
+struct FinishArgs {
+  const unsigned long long *keys;
+  JoinCounters *ctr;
+  uint32_t max_results;
+  uint32_t n_tasks;
+  int ib, jb, bits;
+  uint32_t *h_ctr;
+  ssj_pair *h_pairs;
+  uint64_t *h_start;
+};
+hipError_t launch_finish(const FinishArgs &a, hipStream_t st);
+
 // ------------------------------------------------ prefix-filter candidates
 // Rows [row_begin, row_end) (global row indices) of one task, past its
 // cutoff point; `first` counts the rows of earlier runs, so that run k's
