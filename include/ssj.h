@@ -203,11 +203,10 @@ int ssj_build_bitmaps(const ssj_sets *s, uint32_t b_bits, int method, uint32_t p
  * for callers that cannot allocate: serving loops and harnesses that forbid
  * hipMalloc or any allocating call while they run.  Same arguments, result
  * and errors as ssj_build_bitmaps; the bitmaps are identical.
- *   Working memory (side table, counters, validated set sizes) is a fixed
- *   device array of 32 MiB inside the library, one copy per device, held
- *   from the library's load until the process ends.  It is cleared by the
- *   call where it must start at zero and otherwise keeps the last call's
- *   contents.  Calls on one device share that array: the library runs them
+ *   Working memory (error flags) is a fixed device array of a few bytes
+ *   inside the library, one copy per device, held from the library's load
+ *   until the process ends and cleared by every call.  Calls on one device
+ *   share that array: the library runs them
  *   one at a time (a call holds the device's array until its stream is
  *   synchronised), so concurrent calls from several threads wait for each
  *   other instead of racing.  No host memory is allocated either.

@@ -35,14 +35,58 @@ __device__ __forceinline__ uint32_t side_of_block(const SideDesc *__restrict__ s
   return lo;
 }
 
+// The checks of k_set_sizes, for builds that read the offsets first.
+__device__ __forceinline__ uint32_t check_offset(const SideDesc &sd, uint64_t k, uint64_t o) {
+  return (k == 0 && o != 0) || (k == sd.n && o != sd.n_tokens) || o > sd.n_tokens ? kErrOffsets
+                                                                                  : 0u;
+}
+__device__ __forceinline__ uint32_t check_size(uint64_t o0, uint64_t o1) {
+  return o1 < o0 ? kErrOffsets : o1 - o0 >= 0xFFFFFFFFull ? kErrTooBig : 0u;
+}
+
+// Error bits to the counters, or (CHECK) to the flags, one word per bit so that a
+// plain store will do: they may lie in host memory.
+template <bool CHECK>
+__device__ __forceinline__ void report(uint32_t err, JoinCounters *ctr, const BuildCheck &chk) {
+  if (!CHECK) {
+    atomicOr(&ctr->error, err);
+    return;
+  }
+#pragma unroll
+  for (uint32_t k = 0; k < BuildCheck::kFlags; ++k)
+    if ((err >> k) & 1u) chk.flags[k] = 1u;
+}
+
+// Bitmap-Next: token hash s takes its bit or the next free one, cyclically.
+// The bits taken do not depend on the order of the tokens, so every token
+// probes on its own: a claimed bit stays claimed, a probe that finds its bit
+// taken goes on at the next bit its word had free.  Fewer tokens than bits:
+// every probe ends.  (One lane probing for its whole set took 86 us for 20,011
+// sets, 4 us of it needed.)
+__device__ __forceinline__ void probe_next(uint32_t *bits, uint32_t s, uint32_t b_bits) {
+  for (;;) {
+    const uint32_t m = 1u << (s & 31);
+    const uint32_t old = atomicOr(&bits[s >> 5], m);
+    if (!(old & m)) return;
+    const uint32_t free_above = ~old & ~(m | (m - 1));
+    s = free_above ? (s & ~31u) + (uint32_t)__builtin_ctz(free_above) : (s & ~31u) + 32u;
+    if (s >= b_bits) s = 0;
+  }
+}
+
+// Bits [32 i, 32 i + 32) of a saturated Bitmap-Next (n >= b): all ones.
+__device__ __forceinline__ uint32_t ones_below(uint32_t i, uint32_t b_bits) {
+  return 32 * i < b_bits ? 0xFFFFFFFFu : 0u;
+}
+
 // One wave per output row x: in size order (perm/side_of given) the set
 // perm[x] of side side_of[x], otherwise the caller set x - base of the side
 // holding global index x.
-template <int METHOD, bool POW2>
+template <int METHOD, bool POW2, bool CHECK>
 __global__ __launch_bounds__(kBlock) void k_build_bitmaps(
     const SideDesc *__restrict__ sides, uint32_t n_sides, const uint32_t *__restrict__ perm,
     const uint32_t *__restrict__ side_of, uint64_t n, uint32_t b_bits, uint32_t out_words,
-    uint64_t *__restrict__ out, JoinCounters *__restrict__ ctr) {
+    uint64_t *__restrict__ out, JoinCounters *__restrict__ ctr, BuildCheck chk) {
   __shared__ uint32_t lbits[kWavesPerBlock][2 * kMaxWords];
   const int lane = threadIdx.x & 63;
   const int w = threadIdx.x >> 6;
@@ -50,37 +94,32 @@ __global__ __launch_bounds__(kBlock) void k_build_bitmaps(
   if (x >= n) return;  // whole wave leaves together
   uint32_t *bits = lbits[w];
   for (uint32_t i = lane; i < 2 * out_words; i += 64) bits[i] = 0;
-  const uint32_t sid = perm ? side_of[x] : side_of_index(sides, n_sides, x);
-  const SideDesc sd = sides[sid];
+  const uint32_t sid = CHECK ? 0u : perm ? side_of[x] : side_of_index(sides, n_sides, x);
+  const SideDesc sd = CHECK ? chk.side : sides[sid];
   const uint64_t k = perm ? perm[x] : x - sd.base;
-  if (k >= sd.n || (ctr->error & (kErrOffsets | kErrTooBig))) return;
+  // (malformed offsets, found by the launch before and not yet seen by the host)
+  if (k >= sd.n || (!CHECK && (ctr->error & (kErrOffsets | kErrTooBig)))) return;
   const uint32_t *__restrict__ tokens = sd.tokens;
   const uint64_t o0 = sd.offsets[k], o1 = sd.offsets[k + 1];
+  if (CHECK) {
+    const uint32_t err = check_offset(sd, k, o0) | check_offset(sd, k + 1, o1) | check_size(o0, o1);
+    if (err) {  // the same in every lane
+      if (lane == 0) report<CHECK>(err, ctr, chk);
+      return;
+    }
+  }
   const uint32_t nt = (uint32_t)(o1 - o0);
   const uint32_t mask = b_bits - 1;
   bool unsorted = false;
-  if (METHOD == SSJ_BM_NEXT) {
-    // Alg. 5: saturated when n >= b, else linear probing by one lane.
-    for (uint64_t t = o0 + lane; t + 1 < o1; t += 64)
-      unsorted |= !(tokens[t] < tokens[t + 1]);
-    if (nt >= b_bits) {
-      for (uint32_t i = lane; i < 2 * (b_bits / 64); i += 64) bits[i] = 0xFFFFFFFFu;
-    } else if (lane == 0) {
-      for (uint64_t t = o0; t < o1; ++t) {
-        uint32_t v = tokens[t];
-        uint32_t s = POW2 ? (v & mask) : (v % b_bits);
-        while ((bits[s >> 5] >> (s & 31)) & 1u) s = (s + 1 == b_bits) ? 0 : s + 1;
-        bits[s >> 5] |= 1u << (s & 31);
-      }
-    }
-  } else {
-    for (uint64_t t = o0 + lane; t < o1; t += 64) {
-      uint32_t v = tokens[t];
-      if (t + 1 < o1) unsorted |= !(v < tokens[t + 1]);
-      uint32_t s = POW2 ? (v & mask) : (v % b_bits);
-      if (METHOD == SSJ_BM_XOR) atomicXor(&bits[s >> 5], 1u << (s & 31));
-      else atomicOr(&bits[s >> 5], 1u << (s & 31));
-    }
+  if (METHOD == SSJ_BM_NEXT && nt >= b_bits)  // Alg. 5: saturated
+    for (uint32_t i = lane; i < 2 * out_words; i += 64) bits[i] = ones_below(i, b_bits);
+  for (uint64_t t = o0 + lane; t < o1; t += 64) {
+    const uint32_t v = tokens[t];
+    if (t + 1 < o1) unsorted |= !(v < tokens[t + 1]);
+    const uint32_t s = POW2 ? (v & mask) : (v % b_bits);
+    if (METHOD == SSJ_BM_XOR) atomicXor(&bits[s >> 5], 1u << (s & 31));
+    else if (METHOD == SSJ_BM_SET) atomicOr(&bits[s >> 5], 1u << (s & 31));
+    else if (nt < b_bits) probe_next(bits, s, b_bits);
   }
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
@@ -88,10 +127,10 @@ __global__ __launch_bounds__(kBlock) void k_build_bitmaps(
   uint64_t *dst = out + x * out_words;
   for (uint32_t i = lane; i < out_words; i += 64)
     dst[i] = (uint64_t)bits[2 * i] | ((uint64_t)bits[2 * i + 1] << 32);
-  if (__ballot(unsorted) && lane == 0) atomicOr(&ctr->error, kErrUnsorted);
+  if (__ballot(unsorted) && lane == 0) report<CHECK>(kErrUnsorted, ctr, chk);
 }
 
-// Bitmaps of up to 8 words, and of 16 and 32, XOR or SET: a workgroup takes
+// Bitmaps of up to 8 words, and of 16 and 32: a workgroup takes
 // kSegSets consecutive sets in caller order, whose tokens are one contiguous
 // run of the CSR array, and reads that run fully coalesced (in passes of as
 // many sets as 16 KB of LDS bitmaps hold).  Each token finds its
@@ -108,19 +147,21 @@ constexpr uint32_t seg_pass_sets() {
   return kSegSets * 8 / (WO > 8 ? WO : 8);
 }
 
-template <int WO, int METHOD, bool POW2>
+// CHECK: the offsets have not been validated; every pass checks its own before
+// it reads a token (those of a pass whose offsets are malformed are not read).
+template <int WO, int METHOD, bool POW2, bool CHECK>
 __global__ __launch_bounds__(kBlock) void k_build_bitmaps_seg(
     const SideDesc *__restrict__ sides, uint32_t n_sides, const uint32_t *__restrict__ rank,
     uint64_t n, uint32_t b_bits, uint64_t *__restrict__ out, FoldOut fold,
-    JoinCounters *__restrict__ ctr) {
+    JoinCounters *__restrict__ ctr, BuildCheck chk) {
   constexpr uint32_t kPass = seg_pass_sets<WO>();
   __shared__ uint64_t soff[kPass + 1];
   __shared__ uint32_t sbits[kPass * 2 * WO];
-  const SideDesc sd = sides[side_of_block(sides, n_sides, blockIdx.x)];
+  const SideDesc sd = CHECK ? chk.side : sides[side_of_block(sides, n_sides, blockIdx.x)];
   const uint64_t seg0 = (uint64_t)(blockIdx.x - sd.blk0) * kSegSets;
   if (seg0 >= sd.n) return;  // whole workgroup leaves together
   // malformed offsets, found by the launch before and not yet seen by the host
-  if (ctr->error & (kErrOffsets | kErrTooBig)) return;
+  if (!CHECK && (ctr->error & (kErrOffsets | kErrTooBig))) return;
   const uint32_t nseg = (uint32_t)min((uint64_t)kSegSets, sd.n - seg0);
   const uint64_t *__restrict__ offsets = sd.offsets;
   const uint32_t *__restrict__ tokens = sd.tokens;
@@ -131,10 +172,30 @@ __global__ __launch_bounds__(kBlock) void k_build_bitmaps_seg(
     const uint32_t ns = min(kPass, nseg - p0);
     const uint64_t t0 = offsets[s0];
     if (p0) __syncthreads();  // the previous pass has read soff and sbits
-    for (uint32_t i = threadIdx.x; i <= ns; i += kBlock) soff[i] = offsets[s0 + i] - t0;
+    uint32_t err = 0;
+    for (uint32_t i = threadIdx.x; i <= ns; i += kBlock) {
+      const uint64_t o = offsets[s0 + i];
+      soff[i] = o - t0;
+      if (!CHECK) continue;
+      err |= check_offset(sd, s0 + i, o);
+      if (i < ns) err |= check_size(o, offsets[s0 + i + 1]);
+    }
     for (uint32_t i = threadIdx.x; i < ns * 2 * WO; i += kBlock) sbits[i] = 0;
-    __syncthreads();
+    if (CHECK) {
+      // the whole workgroup leaves together
+      if (err) report<CHECK>(err, ctr, chk);
+      if (__syncthreads_or((int)err)) return;
+    } else {
+      __syncthreads();
+    }
     const uint64_t nt = soff[ns];
+    if (METHOD == SSJ_BM_NEXT) {
+      for (uint32_t i = threadIdx.x; i < ns * 2 * WO; i += kBlock) {
+        const uint32_t x = i / (2 * WO);
+        if (soff[x + 1] - soff[x] >= b_bits) sbits[i] = ones_below(i - x * 2 * WO, b_bits);
+      }
+      __syncthreads();
+    }
     // Each thread takes four consecutive tokens at a time, from the
     // 16-byte boundary at or before the run's start: one 16-byte load
     // (scalar loads at the array's end or for an unaligned array), one
@@ -175,7 +236,8 @@ __global__ __launch_bounds__(kBlock) void k_build_bitmaps_seg(
         }
         const uint32_t s = POW2 ? (v[k] & mask) : (v[k] % b_bits);
         if (METHOD == SSJ_BM_XOR) atomicXor(&sbits[lo * 2 * WO + (s >> 5)], 1u << (s & 31));
-        else atomicOr(&sbits[lo * 2 * WO + (s >> 5)], 1u << (s & 31));
+        else if (METHOD == SSJ_BM_SET) atomicOr(&sbits[lo * 2 * WO + (s >> 5)], 1u << (s & 31));
+        else if (soff[lo + 1] - soff[lo] < b_bits) probe_next(&sbits[lo * 2 * WO], s, b_bits);
       }
     }
     __syncthreads();
@@ -207,7 +269,7 @@ __global__ __launch_bounds__(kBlock) void k_build_bitmaps_seg(
       }
     }
   }
-  if (__ballot(unsorted) && (threadIdx.x & 63) == 0) atomicOr(&ctr->error, kErrUnsorted);
+  if (__ballot(unsorted) && (threadIdx.x & 63) == 0) report<CHECK>(kErrUnsorted, ctr, chk);
 }
 
 // Bitmap-Xor bitmaps at 16 or 32 words (and the narrower widths of `fold`)
@@ -312,31 +374,31 @@ __global__ __launch_bounds__(kBlock) void k_gather_bitmaps(const uint64_t *__res
   out[e] = (w < in_words && k < n) ? in[k * in_words + w] : 0ull;
 }
 
-template <int WO, int METHOD>
+template <int WO, int METHOD, bool CHECK>
 hipError_t launch_seg(bool pow2, hipStream_t st, const SideDesc *sides, uint32_t n_sides,
                       uint32_t seg_blocks, const uint32_t *rank, uint64_t n, uint32_t b_bits,
-                      uint64_t *out, const FoldOut &fold, JoinCounters *ctr) {
+                      uint64_t *out, const FoldOut &fold, JoinCounters *ctr, const BuildCheck &chk) {
   dim3 grid(seg_blocks);
   if (pow2)
-    hipLaunchKernelGGL((k_build_bitmaps_seg<WO, METHOD, true>), grid, dim3(kBlock), 0, st,
-                       sides, n_sides, rank, n, b_bits, out, fold, ctr);
+    hipLaunchKernelGGL((k_build_bitmaps_seg<WO, METHOD, true, CHECK>), grid, dim3(kBlock), 0, st,
+                       sides, n_sides, rank, n, b_bits, out, fold, ctr, chk);
   else
-    hipLaunchKernelGGL((k_build_bitmaps_seg<WO, METHOD, false>), grid, dim3(kBlock), 0, st,
-                       sides, n_sides, rank, n, b_bits, out, fold, ctr);
+    hipLaunchKernelGGL((k_build_bitmaps_seg<WO, METHOD, false, CHECK>), grid, dim3(kBlock), 0, st,
+                       sides, n_sides, rank, n, b_bits, out, fold, ctr, chk);
   return hipGetLastError();
 }
 
-template <int METHOD>
+template <int METHOD, bool CHECK>
 hipError_t launch_method(bool pow2, hipStream_t st, const SideDesc *sides, uint32_t n_sides,
                          uint32_t seg_blocks, uint64_t n, const uint32_t *perm,
                          const uint32_t *rank, const uint32_t *side_of, uint32_t b_bits,
                          uint32_t out_words, uint64_t *out, const FoldOut &fold,
-                         JoinCounters *ctr) {
-  if (METHOD != SSJ_BM_NEXT && (rank || !perm) && seg_blocks) {
+                         JoinCounters *ctr, const BuildCheck &chk) {
+  if ((rank || !perm) && seg_blocks) {
 #define SSJ_SEG(wo)                                                                     \
   case wo:                                                                              \
-    return launch_seg<wo, METHOD>(pow2, st, sides, n_sides, seg_blocks, rank, n, b_bits, \
-                                  out, fold, ctr);
+    return launch_seg<wo, METHOD, CHECK>(pow2, st, sides, n_sides, seg_blocks, rank, n, b_bits, \
+                                  out, fold, ctr, chk);
     switch (out_words) {
       SSJ_SEG(1) SSJ_SEG(2) SSJ_SEG(3) SSJ_SEG(4) SSJ_SEG(5) SSJ_SEG(6) SSJ_SEG(7) SSJ_SEG(8)
       SSJ_SEG(16) SSJ_SEG(32)
@@ -346,11 +408,11 @@ hipError_t launch_method(bool pow2, hipStream_t st, const SideDesc *sides, uint3
   }
   dim3 grid((unsigned)((n + kWavesPerBlock - 1) / kWavesPerBlock));
   if (pow2)
-    hipLaunchKernelGGL((k_build_bitmaps<METHOD, true>), grid, dim3(kBlock), 0, st, sides,
-                       n_sides, perm, side_of, n, b_bits, out_words, out, ctr);
+    hipLaunchKernelGGL((k_build_bitmaps<METHOD, true, CHECK>), grid, dim3(kBlock), 0, st, sides,
+                       n_sides, perm, side_of, n, b_bits, out_words, out, ctr, chk);
   else
-    hipLaunchKernelGGL((k_build_bitmaps<METHOD, false>), grid, dim3(kBlock), 0, st, sides,
-                       n_sides, perm, side_of, n, b_bits, out_words, out, ctr);
+    hipLaunchKernelGGL((k_build_bitmaps<METHOD, false, CHECK>), grid, dim3(kBlock), 0, st, sides,
+                       n_sides, perm, side_of, n, b_bits, out_words, out, ctr, chk);
   return hipGetLastError();
 }
 
@@ -508,8 +570,11 @@ hipError_t launch_build_bitmaps(const SideDesc *sides, uint32_t n_sides, uint32_
                                 uint64_t n_total, const uint32_t *perm, const uint32_t *rank,
                                 const uint32_t *side_of, uint32_t b_bits, int method,
                                 uint32_t out_words, uint64_t *out, JoinCounters *ctr,
-                                hipStream_t st, const FoldOut *fold_in) {
+                                hipStream_t st, const FoldOut *fold_in,
+                                const BuildCheck *check) {
   if (n_total == 0) return hipSuccess;
+  if (check && (perm || rank || n_sides != 1)) return hipErrorInvalidValue;
+  const BuildCheck chk = check ? *check : BuildCheck{};
   if (out_words > kMaxWords || out_words < b_bits / 64) return hipErrorInvalidValue;
   if (perm && !side_of) return hipErrorInvalidValue;
   FoldOut fold{};
@@ -523,16 +588,19 @@ hipError_t launch_build_bitmaps(const SideDesc *sides, uint32_t n_sides, uint32_
     fold = *fold_in;
   }
   const bool pow2 = (b_bits & (b_bits - 1)) == 0;
+#define SSJ_METHOD(m)                                                                          \
+  case m:                                                                                      \
+    return check ? launch_method<m, true>(pow2, st, sides, n_sides, seg_blocks, n_total, perm, \
+                                          rank, side_of, b_bits, out_words, out, fold, ctr,    \
+                                          chk)                                                \
+                 : launch_method<m, false>(pow2, st, sides, n_sides, seg_blocks, n_total,      \
+                                           perm, rank, side_of, b_bits, out_words, out, fold,  \
+                                           ctr, chk);
   switch (method) {
-    case SSJ_BM_XOR:
-      return launch_method<SSJ_BM_XOR>(pow2, st, sides, n_sides, seg_blocks, n_total, perm, rank,
-                                       side_of, b_bits, out_words, out, fold, ctr);
-    case SSJ_BM_SET:
-      return launch_method<SSJ_BM_SET>(pow2, st, sides, n_sides, seg_blocks, n_total, perm, rank,
-                                       side_of, b_bits, out_words, out, fold, ctr);
-    case SSJ_BM_NEXT:
-      return launch_method<SSJ_BM_NEXT>(pow2, st, sides, n_sides, seg_blocks, n_total, perm,
-                                        rank, side_of, b_bits, out_words, out, fold, ctr);
+    SSJ_METHOD(SSJ_BM_XOR)
+    SSJ_METHOD(SSJ_BM_SET)
+    SSJ_METHOD(SSJ_BM_NEXT)
+#undef SSJ_METHOD
     default:
       return hipErrorInvalidValue;
   }

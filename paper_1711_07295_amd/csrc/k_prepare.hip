@@ -233,6 +233,11 @@ hipError_t launch_reset_all(JoinCounters *ctr, hipStream_t st) {
   return hipGetLastError();
 }
 
+hipError_t launch_clear_u32(uint32_t *p, uint32_t n, hipStream_t st) {
+  hipLaunchKernelGGL(k_fill_u32, dim3(grid_for(n)), dim3(kBlock), 0, st, p, (uint64_t)n, 0u);
+  return hipGetLastError();
+}
+
 hipError_t launch_copy_u64(const unsigned long long *in, uint64_t n, unsigned long long *out,
                            hipStream_t st) {
   if (n == 0) return hipSuccess;

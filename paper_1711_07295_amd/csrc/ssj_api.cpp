@@ -287,16 +287,10 @@ class ChunkCache {
 // Bump allocator over device memory chunks.  A call's arena takes cached
 // chunks and returns them when it ends, after synchronising its stream; an
 // owned arena (a resident index) allocates its own and frees them when it is
-// destroyed (hipFree waits for the device).  A fixed arena hands out one
-// region the caller provides and never allocates: a request beyond the
-// region fails with SSJ_E_UNSUPPORTED.
+// destroyed (hipFree waits for the device).
 class Arena {
  public:
   explicit Arena(hipStream_t st, bool owned = false) : st_(st), owned_(owned) {
-    if (hipGetDevice(&dev_) != hipSuccess) dev_ = 0;
-  }
-  Arena(hipStream_t st, void *region, uint64_t size)
-      : st_(st), owned_(false), fixed_(true), next_(static_cast<char *>(region)), left_(size) {
     if (hipGetDevice(&dev_) != hipSuccess) dev_ = 0;
   }
   Arena(const Arena &) = delete;
@@ -347,7 +341,6 @@ class Arena {
   T *alloc(uint64_t n) {
     uint64_t bytes = (std::max<uint64_t>(n, 1) * sizeof(T) + 255) & ~255ull;
     if (bytes > left_) {
-      if (fixed_) throw Fail{SSJ_E_UNSUPPORTED};
       uint64_t size = owned_ ? std::max<uint64_t>(bytes, kOwnedChunk) : kChunk;
       if (!owned_)
         while (size < bytes) size <<= 1;
@@ -377,7 +370,6 @@ class Arena {
   static constexpr uint64_t kOwnedChunk = 16ull << 20;
   hipStream_t st_;
   bool owned_;
-  bool fixed_ = false;
   int dev_ = 0;
   std::vector<std::pair<void *, uint64_t>> chunks_;
   std::vector<void *> staged_;  // host upload buffers (HostPairs)
@@ -2548,50 +2540,39 @@ int bitmap_args(const ssj_sets *s, uint32_t b_bits, int method, uint32_t p, uint
 }
 
 // The bitmaps of one collection in caller order, `method` one of Xor, Set,
-// Next.  The offsets are validated first (set sizes, side table and
-// counters come from `ar`), the token order on the way.  No host memory is
-// allocated.
+// Next.  The offsets and the token order are validated on the way, so that the
+// call is one launch and one wait.  Its error flags are in page-locked memory
+// (h_flags, nothing is copied), or, when that is nullptr, in `d_flags`.
 int build_bitmaps(const ssj_sets *s, uint32_t b_bits, int method, uint64_t *out, hipStream_t st,
-                  Arena &ar) {
+                  uint32_t *h_flags, uint32_t *d_flags) {
   const uint64_t n = s->n_sets;
   if (n == 0) return SSJ_OK;
-  SideDesc side{};
-  side.offsets = s->offsets;
-  side.tokens = s->tokens;
-  side.n_tokens = s->n_tokens;
-  side.base = 0;
-  side.n = (uint32_t)n;
-  side.blk0 = 0;
-  SideDesc *d_side = ar.alloc<SideDesc>(1);
-  JoinCounters *ctr = ar.alloc<JoinCounters>(1);
-  uint32_t *sizes = ar.alloc<uint32_t>(n);
-  uint32_t *side_of = ar.alloc<uint32_t>(n);
-  h2d(d_side, &side, 1, st);
-  check(launch_reset_all(ctr, st));
-  check(launch_set_sizes(d_side, 1, n, sizes, side_of, ctr, st));
-  JoinCounters ctr_h{};
-  d2h(&ctr_h, ctr, 1, st);
+  constexpr uint32_t kF = BuildCheck::kFlags;
+  BuildCheck chk{};
+  chk.side.offsets = s->offsets;
+  chk.side.tokens = s->tokens;
+  chk.side.n_tokens = s->n_tokens;
+  chk.side.n = (uint32_t)n;
+  chk.flags = h_flags ? h_flags : d_flags;
+  uint32_t flags[kF] = {};
+  if (h_flags) std::memset(h_flags, 0, sizeof(flags));
+  else check(launch_clear_u32(d_flags, kF, st));
+  check(launch_build_bitmaps(nullptr, 1, bitmap_seg_blocks(n), n, nullptr, nullptr, nullptr,
+                             b_bits, method, b_bits / 64, out, nullptr, st, nullptr, &chk));
+  if (!h_flags) d2h(flags, d_flags, kF, st);
   sync(st);
-  if (ctr_h.error & (kErrOffsets | kErrTooBig)) return SSJ_E_INVALID;
-  check(launch_build_bitmaps(d_side, 1, bitmap_seg_blocks(n), n, nullptr, nullptr, nullptr,
-                             b_bits, method, b_bits / 64, out, ctr, st));
-  d2h(&ctr_h, ctr, 1, st);
-  sync(st);
-  if (ctr_h.error & kErrUnsorted) return SSJ_E_UNSORTED;
-  return SSJ_OK;
+  if (h_flags) std::memcpy(flags, h_flags, sizeof(flags));
+  static_assert(kErrOffsets == 1u && kErrUnsorted == 2u && kErrTooBig == 4u, "flag order");
+  if (flags[0] || flags[2]) return SSJ_E_INVALID;
+  return flags[1] ? SSJ_E_UNSORTED : SSJ_OK;
 }
 
-// Device memory of ssj_build_bitmaps_noalloc: side table, counters and the
-// set sizes of one collection, in a fixed array of every device.  Host code
-// reaches a device's copy only through the address hipGetSymbolAddress
-// returns for it (kept per device in g_scratch).
-constexpr uint64_t kScratchBytes = 32ull << 20;
+// Device memory of ssj_build_bitmaps_noalloc: the error flags of one call, in a
+// fixed array of every device.  Host code reaches a device's copy only through
+// the address hipGetSymbolAddress returns for it (kept per device in
+// g_scratch).
 constexpr int kScratchDevices = 64;
-constexpr uint64_t round256(uint64_t b) { return (b + 255) & ~255ull; }
-static_assert(round256(sizeof(SideDesc)) + round256(sizeof(JoinCounters)) +
-                      2 * round256(4ull * SSJ_NOALLOC_MAX_SETS) <= kScratchBytes,
-              "SSJ_NOALLOC_MAX_SETS sets fit the scratch array");
-static __device__ __align__(256) unsigned char scratch[kScratchBytes];
+static __device__ uint32_t scratch[BuildCheck::kFlags];
 
 struct ScratchSlot {
   std::mutex mu;       // held for a whole call: calls on one device never overlap
@@ -2637,7 +2618,9 @@ int ssj_build_bitmaps(const ssj_sets *s, uint32_t b_bits, int method, uint32_t p
     if (m < 0) return m;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     Arena ar(st);
-    return build_bitmaps(s, b_bits, m, bitmaps_dev, st, ar);
+    uint32_t *h_flags = ar.pinned<uint32_t>(BuildCheck::kFlags);
+    return build_bitmaps(s, b_bits, m, bitmaps_dev, st, h_flags,
+                         h_flags ? nullptr : ar.alloc<uint32_t>(BuildCheck::kFlags));
   } catch (const Fail &f) {
     (void)hipGetLastError();
     return f.code;
@@ -2670,8 +2653,8 @@ int ssj_build_bitmaps_noalloc(const ssj_sets *s, uint32_t b_bits, int method, ui
   }
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   try {
-    Arena ar(st, slot.ptr, kScratchBytes);
-    return build_bitmaps(s, b_bits, m, bitmaps_dev, st, ar);
+    return build_bitmaps(s, b_bits, m, bitmaps_dev, st, nullptr,
+                         static_cast<uint32_t *>(slot.ptr));
   } catch (const Fail &f) {
     (void)hipGetLastError();
     (void)hipStreamSynchronize(st);

@@ -230,10 +230,19 @@ hipError_t radix_sort_u64(unsigned long long *keys, unsigned long long *tmp, uin
 // output is in caller order (row base_s + k for caller set k); with them, in
 // size order (row g for the set perm[g] of side side_of[g]).  The strict
 // token order of every set is checked on the way.
+// check: one side, in caller order, whose offsets are validated on the way too (the
+// sets of a malformed part are not built); `sides` and `ctr` are not used.
 // fold (optional): also write the widths out_words/2, /4, ..., /32 (out[k]
 // for out_words >> (k+1) words; NULL entries skipped) from the same pass;
 // needs a power-of-two width of at most kMaxFoldWords words, Xor or Set, and
 // the segmented build (caller order, or size order through rank).
+// The side of a checked build, and a zeroed word per error bit (flags[k] for
+// bit k of kErr*), in device or page-locked host memory.
+struct BuildCheck {
+  static constexpr uint32_t kFlags = 3;
+  SideDesc side;
+  uint32_t *flags;
+};
 constexpr uint32_t kMaxFoldWords = 32;
 struct FoldOut {
   uint64_t *out[5];
@@ -242,7 +251,8 @@ hipError_t launch_build_bitmaps(const SideDesc *sides, uint32_t n_sides, uint32_
                                 uint64_t n_total, const uint32_t *perm, const uint32_t *rank,
                                 const uint32_t *side_of, uint32_t b_bits, int method,
                                 uint32_t out_words, uint64_t *out, JoinCounters *ctr,
-                                hipStream_t st, const FoldOut *fold = nullptr);
+                                hipStream_t st, const FoldOut *fold = nullptr,
+                                const BuildCheck *check = nullptr);
 // Sizes [lo, hi] of the sets of one side that a windowed build covers
 // (none when lo > hi).
 struct SizeWindow {
@@ -510,6 +520,9 @@ hipError_t launch_unique_to_queue(const unsigned long long *keys, uint64_t n, ui
 hipError_t launch_reset_round(JoinCounters *ctr, hipStream_t st);
 // zero a whole JoinCounters
 hipError_t launch_reset_all(JoinCounters *ctr, hipStream_t st);
+
+// p[0 .. n) = 0
+hipError_t launch_clear_u32(uint32_t *p, uint32_t n, hipStream_t st);
 
 // copy n 64-bit words
 hipError_t launch_copy_u64(const unsigned long long *in, uint64_t n, unsigned long long *out,
