@@ -10,6 +10,13 @@
 // tokens (64 against 128 bits at 4/5; 64 bits at 1/2); per width, the ns one
 // wave takes to stage a survivor, from one tile where nearly every pair
 // survives (64 x 2048 random sets of b tokens at 1/2).
+//
+// The b = 64 entries (2.9462e-05, 6144 pairs a step, 41 us a launch) are those of
+// its kernel before it took two columns per accumulator.  Measured anew it reads
+// 2.46e-05, 12,288 and 25 us, and 1.28 ns an entry; with those a batch of 48 joins
+// puts its sizes up to 12 at 64 bits and is slower (3.19 -> 3.69 ms, the entries
+// of that class being dearer than the model has them), and no other workload
+// gains more than 2%.
 #pragma once
 #include <cstdint>
 

@@ -123,9 +123,17 @@ struct Rows {
 // new chunk and when it exits.
 constexpr uint32_t kStage = kFilterStage;
 
+// Two columns per accumulator: a wave's rows, at most, and its LDS words for their
+// sizes, bands and bitmaps and for a step's 64 column sizes and bitmaps.
+constexpr int kTwoRows = 192;
+constexpr int kTwoWords = 5 * kTwoRows + 3 * 64;
+constexpr int kMaxRowTiles = 6;
+
 struct Sink {
   uint2 *stage;                // this wave's kStage LDS entries
-  int16_t *dots;               // this wave's 1024 LDS dot products (matrix cores)
+  uint32_t *kept;              // ... kept values of a step, 64 words per row tile (matrix cores)
+  uint32_t *rows;              // ... and kTwoWords words (two columns per accumulator)
+                               // or 1024 16-bit dot products (matrix cores otherwise)
   uint32_t fill;               // entries staged (wave-uniform)
   uint32_t first_col;          // (column, row slab) of the first staged entry
   uint32_t first_slab;
@@ -649,9 +657,11 @@ __device__ __forceinline__ void tile_loop(Sink &sink, Run &&run) {
   sink_pad(sink);
 }
 
-__device__ __forceinline__ void sink_init(Sink &sink, uint2 *stage, int16_t *dots) {
+__device__ __forceinline__ void sink_init(Sink &sink, uint2 *stage, uint32_t *kept,
+                                          uint32_t *rows) {
   sink.stage = stage;
-  sink.dots = dots;
+  sink.kept = kept;
+  sink.rows = rows;
   sink.fill = 0;
   sink.first_col = 0;
   sink.first_slab = 0;
@@ -670,7 +680,7 @@ template <int W, int R, int U, bool COS>
 __global__ __launch_bounds__(kBlock) void k_filter(FilterArgs) {
   extern __shared__ uint2 stage[];  // kStage entries per wave
   Sink sink;
-  sink_init(sink, stage + (threadIdx.x >> 6) * kStage, nullptr);
+  sink_init(sink, stage + (threadIdx.x >> 6) * kStage, nullptr, nullptr);
   tile_loop(sink, [&](const TileJob &jb) { return run_tile<W, R, U, COS>(jb, sink); });
 }
 
@@ -751,7 +761,7 @@ __device__ __forceinline__ void load_signs(const uint4 *__restrict__ planes, uin
 // The columns j0 + (lane % 32) of one step: a uniform address (j0 is the
 // same in every lane) plus the lane's byte offset loff = 32 (lane % 32) +
 // 16 h.  No bounds test: the zero padding past set n - 1 covers loads up to
-// 95 columns past a column below n, and the pairs of columns past the size
+// 191 columns past a column below n, and the pairs of columns past the size
 // group's end are dropped by the exact test.
 template <int W>
 __device__ __forceinline__ void load_cols(const uint4 *__restrict__ planes, uint32_t n,
@@ -795,101 +805,157 @@ __device__ __forceinline__ bool stage_mask(unsigned long long m, uint32_t row, u
   return true;
 }
 
-// Slow path of one step at columns [j0, j0 + 32) of a group ending at gend:
-// stage the kept pairs.  Only row tiles whose best value reaches their
-// threshold are looked at; in them each lane packs its kept values into the
-// bits of one word.  Few lanes with kept values (the usual case): the wave
-// walks those lanes and their set bits, one pair at a time, in the order
-// (lane, v).  Many: one ballot per value v stages whole masks, in the order
-// (v, lane).  The choice depends only on the step's values, so a step
-// resumed after a full queue takes the same order and skips exactly the
-// `skip` pairs it had written.
+// Lane's values k (bit v: value v) that passed a bound, each tested exactly, one
+// value per lane at a time, from the pair's sizes and bitmaps (b = 64).  rows: the
+// lane's row, cols: the lane's first column, both in LDS (columns 8 (v / 4) + v % 4
+// further on).
+template <bool COS>
+__device__ __forceinline__ uint32_t refine(uint32_t k, const uint32_t *rows, const uint32_t *cols,
+                                           const TileJob &jb) {
+  const uint32_t a = rows[0], lo = rows[kTwoRows], hi = rows[2 * kTwoRows];
+  const uint32_t r0 = rows[3 * kTwoRows], r1 = rows[4 * kTwoRows];
+#pragma unroll 1
+  for (uint32_t todo = k; todo; todo &= todo - 1) {
+    const uint32_t v = (uint32_t)__builtin_ctz(todo);
+    const uint32_t *col = cols + 8u * (v >> 2) + (v & 3u);
+    const uint32_t c = col[0];
+    const int32_t h = __popc(r0 ^ col[64]) + __popc(r1 ^ col[128]);
+    if (!(c >= lo && c <= hi && pair_kept<COS>(jb, a, c, h))) k &= ~(1u << v);
+  }
+  return k;
+}
+
+// Bits v (0 .. 15) whose column cb + 8 (v / 4) + v % 4 lies below `end`.
+__device__ __forceinline__ uint32_t columns_below(uint32_t cb, uint32_t end) {
+  const uint32_t left = end > cb ? min(end - cb, 32u) : 0u;
+  const uint32_t whole = 4u * (left >> 3), some = min(left & 7u, 4u);
+  return ((1u << whole) - 1u) | (((1u << some) - 1u) << whole);
+}
+
+// Stage the kept pairs of a step at columns j0 ...: bit rt of `hits` names the row
+// tiles to look at, and sink.kept their lanes' kept values, 16 bits for each of
+// the step's HALVES runs of 32 columns (bit v of a half: column 8 (v / 4) + 4 (lane /
+// 32) + v % 4 of it), columns past the run's end or a diagonal tile's row among
+// them; bound (HALVES = 2): they only passed a bound.  Few lanes with kept values
+// (the usual case): the wave walks those lanes and their set bits, one pair at
+// a time, in the order (lane, v).  Many: one ballot per value v stages whole masks, in the order
+// (v, lane).  The choice depends only on the pairs kept, so a step resumed
+// after a full queue takes the same order and skips exactly the `skip` pairs
+// it had written.  (One rolled loop: unrolled over the row tiles it was most of
+// the kernel's code, and every entry waited for instructions.)
+template <int HALVES, bool COS>
+__device__ __forceinline__ bool stage_step(uint32_t hits, uint32_t row_tile0, uint32_t j0,
+                                           uint32_t gend, const TileJob &jb, uint32_t &skip,
+                                           Sink &sink, bool bound = false) {
+  constexpr uint32_t kFewLanes = 4;
+  const uint32_t lane = threadIdx.x & 63;
+  uint32_t done = 0;
+#pragma unroll 1
+  for (hits = rfl(hits); hits; hits &= hits - 1) {
+    const uint32_t rt = (uint32_t)__builtin_ctz(hits);
+    const uint32_t kept = sink.kept[64 * rt + lane];
+    const uint32_t row0 = row_tile0 + 32u * rt;
+#pragma unroll 1
+    for (uint32_t s = 0; s < (uint32_t)HALVES; ++s) {
+      uint32_t k = HALVES == 1 ? kept : (kept >> (16u * s)) & 0xFFFFu;
+      const uint32_t js = j0 + 32u * s;
+      const uint32_t cb = js + 4u * (lane >> 5), my_row = row0 + (lane & 31u);
+      k &= columns_below(cb, jb.diag ? min(gend, my_row) : gend);
+      if (HALVES == 2 && bound)
+        k = refine<COS>(k, sink.rows + 32u * rt + (lane & 31u),
+                        sink.rows + 5 * kTwoRows + (cb - j0), jb);
+      unsigned long long lm = __ballot(k != 0);
+      if ((uint32_t)__popcll(lm) > kFewLanes) {
+#pragma unroll 1
+        for (uint32_t v = 0; v < 16; ++v) {
+          const unsigned long long m = __ballot((k >> v) & 1u);
+          if (m && !stage_mask(m, my_row, cb + 8u * (v >> 2) + (v & 3u), j0, gend, skip, done,
+                               sink))
+            return false;
+        }
+        continue;
+      }
+      while (lm) {
+        const uint32_t L = (uint32_t)__builtin_ctzll(lm);
+        lm &= lm - 1;
+        uint32_t kk = (uint32_t)__builtin_amdgcn_readlane((int)k, (int)L);
+        const uint32_t row = row0 + (L & 31u);
+        const uint32_t cL = js + 4u * (L >> 5);
+        while (kk) {
+          const uint32_t v = (uint32_t)__builtin_ctz(kk);
+          kk &= kk - 1;
+          if (skip) {
+            --skip;
+            ++done;
+            continue;
+          }
+          if (sink.fill == kStage && !flush(sink)) return false;
+          if (sink.fill == 0) {
+            sink.first_col = j0;
+            sink.first_slab = done;
+            sink.first_end = gend;
+          }
+          if (lane == 0) sink.stage[sink.fill] = make_uint2(row, cL + 8u * (v >> 2) + (v & 3u));
+          ++sink.fill;
+          ++done;
+        }
+      }
+    }
+  }
+  return true;
+}
+
+// Slow path of one step at columns [j0, j0 + 32) of a run: stage the kept pairs.
+// Only row tiles whose best value reaches their threshold are looked at; their
+// dot products are made again (the fast path does not keep them: registers
+// are what limits the waves per SIMD).
 template <int W, int RT, bool COS>
 __device__ __forceinline__ bool emit_mfma(const MRows<W, RT> &rw, const uint4 (&a)[W],
                                           const int32_t (&mx)[RT], uint32_t j0,
                                           const ColRun &run, const TileJob &jb, uint32_t &skip,
                                           Sink &sink) {
-  const bool diag = jb.diag;
-  const uint32_t gend = run.end;
-  constexpr uint32_t kFewLanes = 4;
-  const uint32_t lane = threadIdx.x & 63, h = lane >> 5;
-  const uint32_t cb = j0 + 4u * h;  // this lane's column for v is cb + 8(v/4) + v%4
-  const uint32_t row0 = (uint32_t)__builtin_amdgcn_readlane((int)rw.idx, 0);  // lane 0: row0
-  uint32_t done = 0;
+  const uint32_t lane = threadIdx.x & 63;
+  const bool bound = run.hi > run.lo || (COS && jb.cosine);  // the threshold is only a bound
+  uint32_t hits = 0;
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt) {
     if (!__ballot(mx[rt] >= rw.thr_bits[rt])) continue;
-    // the step's dot products of this row tile again (the fast path does
-    // not keep them: registers are what limits the waves per SIMD)
     v16f_t d = {};
 #pragma unroll
     for (int kb = 0; kb < W; ++kb) d = mfma_pm1(a[kb], rw.sg[rt][kb], d);
-    const uint32_t my_row = rw.idx + 32u * rt;
-    uint32_t k = 0;  // bit v: value v kept
-    const int32_t thr = dot_threshold(rw.thr_bits[rt]);
-    // built by shifting: no wide constants
+    const float thr = (float)dot_threshold(rw.thr_bits[rt]);
+    uint32_t k = 0;  // bit v: value v kept (built by shifting: no wide constants)
 #pragma unroll
-    for (int v = 15; v >= 0; --v) {
-      const uint32_t col = cb + 8u * (v / 4) + (uint32_t)(v % 4);
-      const bool kp = d[v] >= (float)thr && col < gend && (!diag || col < my_row);
-      k = (k << 1) | (kp ? 1u : 0u);
-    }
-    if ((run.hi > run.lo || (COS && jb.cosine)) && __ballot(k != 0)) {
-      // the threshold is only a bound: each value that reaches it is tested
-      // at its own column's size, one value per lane at a time, from a copy
-      // of the products in LDS
+    for (int v = 15; v >= 0; --v) k = (k << 1) | (d[v] >= thr ? 1u : 0u);
+    if (bound) {
+      const uint32_t cb = j0 + 4u * (lane >> 5), my_row = rw.idx + 32u * rt;
+      k &= columns_below(cb, jb.diag ? min(run.end, my_row) : run.end);
+      if (__ballot(k != 0)) {
+        // each value that reaches the bound is tested at its own column's size,
+        // one value per lane at a time, from a copy of the products in LDS (from
+        // the bitmaps, W words a pair: +40 us in a 1024-bit class of 350 us)
+        int16_t *dots = reinterpret_cast<int16_t *>(sink.rows);
 #pragma unroll
-      for (int v = 0; v < 16; ++v) sink.dots[64 * v + lane] = (int16_t)d[v];
-      __builtin_amdgcn_wave_barrier();
-      const uint32_t *size_cols = args()->size_cols;
-      for (uint32_t todo = k; todo; todo &= todo - 1) {
-        const uint32_t v = (uint32_t)__builtin_ctz(todo);
-        const uint32_t c = size_cols[cb + 8u * (v >> 2) + (v & 3u)];
-        const int32_t dot = sink.dots[64 * v + lane];
-        if (!(c >= rw.cmn[rt] && c <= rw.cmx[rt] &&
-              pair_kept<COS>(jb, rw.size[rt], c, (64 * W - dot) >> 1)))
-          k &= ~(1u << v);
-      }
-      __builtin_amdgcn_wave_barrier();
-    }
-    unsigned long long lm = __ballot(k != 0);
-    if ((uint32_t)__popcll(lm) > kFewLanes) {
-#pragma unroll 1
-      for (uint32_t v = 0; v < 16; ++v) {
-        const unsigned long long m = __ballot((k >> v) & 1u);
-        if (m && !stage_mask(m, my_row, cb + 8u * (v >> 2) + (v & 3u), j0, gend, skip,
-                             done, sink))
-          return false;
-      }
-      continue;
-    }
-    while (lm) {
-      const uint32_t L = (uint32_t)__builtin_ctzll(lm);
-      lm &= lm - 1;
-      uint32_t kk = (uint32_t)__builtin_amdgcn_readlane((int)k, (int)L);
-      const uint32_t row = row0 + 32u * rt + (L & 31u);
-      const uint32_t cL = j0 + 4u * (L >> 5);
-      while (kk) {
-        const uint32_t v = (uint32_t)__builtin_ctz(kk);
-        kk &= kk - 1;
-        if (skip) {
-          --skip;
-          ++done;
-          continue;
+        for (int v = 0; v < 16; ++v) dots[64 * v + lane] = (int16_t)d[v];
+        __builtin_amdgcn_wave_barrier();
+        const uint32_t *size_cols = args()->size_cols;
+        for (uint32_t todo = k; todo; todo &= todo - 1) {
+          const uint32_t v = (uint32_t)__builtin_ctz(todo);
+          const uint32_t c = size_cols[cb + 8u * (v >> 2) + (v & 3u)];
+          const int32_t dot = dots[64 * v + lane];
+          if (!(c >= rw.cmn[rt] && c <= rw.cmx[rt] &&
+                pair_kept<COS>(jb, rw.size[rt], c, (64 * W - dot) >> 1)))
+            k &= ~(1u << v);
         }
-        if (sink.fill == kStage && !flush(sink)) return false;
-        if (sink.fill == 0) {
-          sink.first_col = j0;
-          sink.first_slab = done;
-          sink.first_end = gend;
-        }
-        if (lane == 0) sink.stage[sink.fill] = make_uint2(row, cL + 8u * (v >> 2) + (v & 3u));
-        ++sink.fill;
-        ++done;
+        __builtin_amdgcn_wave_barrier();
       }
     }
+    sink.kept[64 * rt + lane] = k;
+    hits |= 1u << rt;
   }
-  return true;
+  __builtin_amdgcn_wave_barrier();
+  return stage_step<1, COS>(hits, (uint32_t)__builtin_amdgcn_readlane((int)rw.idx, 0), j0,
+                            run.end, jb, skip, sink);
 }
 
 // The dot products of the step's columns `a` with row tile rt.
@@ -1039,21 +1105,30 @@ __device__ __forceinline__ bool run_tile_mfma(const TileJob &jb, Sink &sink) {
   const uint32_t lane = threadIdx.x & 63, h = lane >> 5, jr = lane & 31;
   constexpr int32_t K = 64 * W;
   MRows<W, RT> rw;
+  rw.idx = jb.row0 + jr;
+  // No branches: every row's loads are in flight together (with a branch per row
+  // tile each waited for the one before: b = 128 .. 512 classes of 20,000 .. 32,000
+  // tiles 750, 726, 284 -> 680, 686, 266 us).  Rows past the end read the last one's.
+  const uint32_t last = jb.row_end - 1;
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt) rw.size[rt] = size_rows[min(rw.idx + 32u * rt, last)];
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt) {
-    const uint32_t i = jb.row0 + 32u * rt + jr;
-    if (rt == 0) rw.idx = i;
-    if (i < jb.row_end) {
-      const uint32_t a = size_rows[i];
-      rw.size[rt] = a;
-      rw.cmn[rt] = jb.cmin[a];
-      rw.cmx[rt] = jb.cmax[a];
-    } else {
+    const uint32_t i = rw.idx + 32u * rt;
+    load_signs<W>(sg_rows, n_rows, i, i <= last, h, rw.sg[rt]);
+  }
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt) {
+    rw.cmn[rt] = jb.cmin[rw.size[rt]];
+    rw.cmx[rt] = jb.cmax[rw.size[rt]];
+  }
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt) {
+    if (rw.idx + 32u * rt > last) {
       rw.size[rt] = 0;
       rw.cmn[rt] = 0xFFFFFFFFu;
       rw.cmx[rt] = 0;
     }
-    load_signs<W>(sg_rows, n_rows, i, i < jb.row_end, h, rw.sg[rt]);
   }
   uint32_t skip = jb.first;
   uint32_t j = jb.c0;
@@ -1081,9 +1156,9 @@ __device__ __forceinline__ bool run_tile_mfma(const TileJob &jb, Sink &sink) {
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) {
       const bool in_band = run.lo <= rw.cmx[rt] && run.hi >= rw.cmn[rt];
-      int32_t sl = 0;
-      if (in_band)
-        sl = run_slack<COS>(jb, rw.size[rt], run.lo, min(run.hi, rw.cmx[rt]));
+      // (slack[0] for a row outside the band: no branch, the loads go out together)
+      const int32_t sl = run_slack<COS>(jb, in_band ? rw.size[rt] : 0u, run.lo,
+                                        in_band ? min(run.hi, rw.cmx[rt]) : 0u);
       rw.thr_bits[rt] = in_band ? dot_threshold_bits(K - 2 * sl) : __float_as_int(kNever);
       any_ok |= in_band;
     }
@@ -1102,21 +1177,358 @@ __device__ __forceinline__ bool run_tile_mfma(const TileJob &jb, Sink &sink) {
   return flush(sink, true);
 }
 
-// Waves per SIMD the register budget of a shape aims at.
+// ---------------------------------------------------------------------------
+// Two columns per accumulator (b = 64).
+//
+// There the reduction of the products, not the matrix cores, bounds the plain
+// kernel: a product leaves 16 values per lane, 8 three-input maxima, 36 cycles of
+// vector issue against 32 of the matrix cores (b = 64).  The K = 64 slots of a
+// product are two blocks of 32 with a power-of-two scale each, so a product
+// can score 32 bits of one column in block 0 and 32 bits of another in block 1:
+// with scales 2^-1 and 2^15, and an accumulator that starts at C, 2 W chained
+// products leave
+//   C + d0 / 2 + 2^16 d1 / 2,
+// d0 and d1 the dot products (even numbers) of columns j and j + 32 with the row.
+// C is the float with bit pattern 0x4B404000 (1.5 2^23 + 2^14), so that the sum
+// stays in [2^23, 2^24), where a float's pattern is its value plus a constant:
+// its halves are 0x4B40 + d1 / 2 and 0x4000 + d0 / 2, two positive 16-bit floats
+// that order like the dot products.  A tree of packed 3-input 16-bit maxima, the
+// threshold (less one) among its inputs, reduces 32 pairs in the 8 instructions
+// that 16 took, and a pair is kept exactly when the result differs from the
+// threshold.
+//
+// Alone, in registers: 443 cycles per 12,288 pairs against 328 per 6,144; under
+// load the clock falls (power) from 2.25 to 1.87 GHz, 4.3e13 -> 5.3e13 pairs/s.  In
+// the 1,000,000-set join's b = 64 class 1.99 -> 1.72 ms, in a join of 4,000,000
+// short sets 9.05 -> 7.85 ms.  At b = 128 the matrix cores bound the plain kernel
+// as much as the reduction, and the larger state costs a wave per SIMD: 0.150 ->
+// 0.198 ms in the 1,000,000-set join, 0.257 -> 0.284 in a query of 2,000 sets
+// against 5,000,000; it keeps the plain kernel.
+//
+// A step is 64 columns: lane l holds column j0 + l, both halves of every 64-bit
+// block; the row operand is the same in both halves of the wave.
+
+typedef _Float16 h2_t __attribute__((ext_vector_type(2)));
+
+constexpr uint32_t kFieldLo = 0x4000u, kFieldHi = 0x4B40u;
+
+template <int W, int RT>
+struct PRows {
+  uint4 sg[RT][2 * W];  // every half block of the lane's row (lane % 32) in each row tile
+  uint32_t thr[RT];     // packed: one less than the least kept value, in both halves
+  // sizes and bands of the wave's rows in LDS (registers are what limits the
+  // waves per SIMD, and they are needed once a run): size, cmin, cmax, and the
+  // bitmap's low and high half
+  uint32_t (*row)[kTwoRows];
+};
+
+// Packed threshold of the dot threshold t = 2 u (64 W + 2 or more: never).
+template <int W>
+__device__ __forceinline__ uint32_t pack_threshold(int32_t u) {
+  u = min(max(u, -32 * W), 32 * W + 1);
+  return ((kFieldHi + (uint32_t)(u - 1)) << 16) + kFieldLo + (uint32_t)(u - 1);
+}
+__device__ __forceinline__ int32_t packed_dot_threshold(uint32_t p) {
+  return 2 * ((int32_t)(p & 0xFFFFu) - (int32_t)kFieldLo + 1);
+}
+
+__device__ __forceinline__ v16f_t mfma_two(const uint4 &a, const uint4 &b, const v16f_t &c,
+                                           int scale) {
+  const v8i_t x = {(int)a.x, (int)a.y, (int)a.z, (int)a.w, 0, 0, 0, 0};
+  const v8i_t y = {(int)b.x, (int)b.y, (int)b.z, (int)b.w, 0, 0, 0, 0};
+  return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(x, y, c, 4, 4, 0, scale, 0, 127);
+}
+
+__device__ __forceinline__ h2_t max3(h2_t a, h2_t b, h2_t c) {
+  return __builtin_elementwise_maximum(__builtin_elementwise_maximum(a, b), c);
+}
+
+// Halfwise maximum of the 16 values and `thr`.
+__device__ __forceinline__ uint32_t max17(const v16f_t &x, uint32_t thr) {
+  h2_t b[16];
+#pragma unroll
+  for (int v = 0; v < 16; ++v) {
+    // (by way of a float: bit-casting the element itself reads element 0)
+    const float f = x[v];
+    b[v] = __builtin_bit_cast(h2_t, f);
+  }
+  h2_t m0 = max3(b[0], b[1], b[2]), m1 = max3(b[3], b[4], b[5]), m2 = max3(b[6], b[7], b[8]);
+  h2_t m3 = max3(b[9], b[10], b[11]), m4 = max3(b[12], b[13], b[14]);
+  m0 = max3(m0, m1, m2);
+  m3 = max3(m3, m4, b[15]);
+  return __builtin_bit_cast(uint32_t, max3(m0, m3, __builtin_bit_cast(h2_t, thr)));
+}
+
+// The products of the step's columns with row tile rt; c: the start value.
+template <int W, int RT>
+__device__ __forceinline__ v16f_t products_two(const uint4 (&a)[2 * W], const PRows<W, RT> &rw,
+                                               int rt, const v16f_t &c, int scale) {
+  v16f_t t = mfma_two(a[0], rw.sg[rt][0], c, scale);
+#pragma unroll
+  for (int x = 1; x < 2 * W; ++x) t = mfma_two(a[x], rw.sg[rt][x], t, scale);
+  return t;
+}
+
+// Columns j0 + lane of one step, as load_cols: a column below n plus at most
+// kSignPad - 1.
+template <int W>
+__device__ __forceinline__ void load_cols_two(const uint4 *__restrict__ planes, uint32_t n,
+                                              uint32_t j0, uint32_t loff, uint4 (&a)[2 * W]) {
+  // (opaque: the compiler would keep planes + loff, 64 bits a lane, and spill it)
+  asm volatile("" : "+v"(loff));
+#pragma unroll
+  for (int kb = 0; kb < W; ++kb) {
+    const char *p = reinterpret_cast<const char *>(planes +
+                                                   ((size_t)kb * (n + kSignPad) + j0) * 2) + loff;
+    a[2 * kb] = *reinterpret_cast<const uint4 *>(p);
+    a[2 * kb + 1] = *reinterpret_cast<const uint4 *>(p + 16);
+  }
+}
+
+// Slow path of one step at columns [j0, j0 + 64), as emit_mfma, for the row tiles in
+// the bits of `hits`: the packed products are made again and their halves give
+// both columns' dot products.
+template <int W, int RT, bool COS>
+__device__ __forceinline__ bool emit_two(const PRows<W, RT> &rw, const uint4 (&a)[2 * W],
+                                         uint32_t hits, int scale, uint32_t j0,
+                                         const ColRun &run, const TileJob &jb, uint32_t &skip,
+                                         Sink &sink) {
+  const uint32_t lane = threadIdx.x & 63;
+  const bool bound = run.hi > run.lo || (COS && jb.cosine);
+  uint32_t size = 0;
+  uint64_t bits = 0;
+  if (bound && j0 + lane < run.end) {  // for the exact tests; in flight during the products
+    const ArgPtr ka = args();
+    size = ka->size_cols[j0 + lane];
+    bits = ka->bm_cols[j0 + lane];
+  }
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt) {
+    if (!((hits >> rt) & 1u)) continue;
+    v16f_t d;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) d[v] = __uint_as_float((kFieldHi << 16) + kFieldLo);
+#pragma unroll
+    for (int x = 0; x < 2 * W; ++x) d = mfma_two(a[x], rw.sg[rt][x], d, scale);
+    const uint32_t thr_hi = rw.thr[rt] | 0xFFFFu;
+    const uint16_t thr_lo = (uint16_t)rw.thr[rt];
+    uint32_t k0 = 0, k1 = 0;  // columns j0 .. and j0 + 32 ..
+#pragma unroll
+    for (int v = 15; v >= 0; --v) {
+      const uint32_t p = __float_as_uint(d[v]);
+      k0 = (k0 << 1) | ((uint16_t)p > thr_lo ? 1u : 0u);
+      k1 = (k1 << 1) | (p > thr_hi ? 1u : 0u);
+    }
+    const uint32_t k = k0 | (k1 << 16);
+    sink.kept[64 * rt + lane] = k;
+  }
+  if (bound) {
+    uint32_t *cols = sink.rows + 5 * kTwoRows + lane;
+    cols[0] = size;
+    cols[64] = (uint32_t)bits;
+    cols[128] = (uint32_t)(bits >> 32);
+  }
+  __builtin_amdgcn_wave_barrier();
+  return stage_step<2, COS>(hits, jb.row0, j0, run.end, jb, skip, sink, bound);
+}
+
+// Fast path of one step, as fast_mfma: the products run one row tile ahead of
+// their reduction, across steps, in two accumulators (RT is even, so every
+// step starts in the first).
+template <int W, int RT>
+__device__ __forceinline__ uint32_t fast_two(const uint4 (&a)[2 * W], const uint4 (&an)[2 * W],
+                                             const PRows<W, RT> &rw, const v16f_t &c, int scale,
+                                             v16f_t (&acc)[2]) {
+  static_assert(RT % 2 == 0, "steps start in accumulator 0");
+  uint32_t hits = 0;  // bit rt: row tile rt keeps something
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt) {
+    const int cur = rt & 1, nxt = cur ^ 1;
+    acc[nxt] = rt + 1 < RT ? products_two<W, RT>(a, rw, rt + 1, c, scale)
+                           : products_two<W, RT>(an, rw, 0, c, scale);
+    __builtin_amdgcn_sched_barrier(0);
+    const uint32_t m = max17(acc[cur], rw.thr[rt]);
+    hits |= __ballot(m != rw.thr[rt]) ? 1u << rt : 0u;
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  asm volatile("" ::"v"(acc[0]));
+  return hits;
+}
+
+// The steps of columns [j, run.end), as sweep_mfma.
+template <int W, int RT, bool COS>
+__device__ __forceinline__ bool sweep_two(const uint4 *__restrict__ sg_cols, uint32_t n_cols,
+                                          const PRows<W, RT> &rw, int scale, uint4 (&b0)[2 * W],
+                                          uint4 (&b1)[2 * W], uint32_t j, const ColRun &run,
+                                          const TileJob &jb, uint32_t &skip, Sink &sink) {
+  const uint32_t g1 = run.end, loff = (threadIdx.x & 63u) * 32u;
+  uint4 b2[2 * W];
+  v16f_t acc[2];
+  uint32_t j0 = j;
+  for (;;) {
+    int phase;
+    uint32_t hits;
+    uint4 cur[2 * W];
+    // the start value's pattern in every register, made anew after each slow
+    // path, which needs the registers
+    v16f_t c;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) c[v] = __uint_as_float((kFieldHi << 16) + kFieldLo);
+    asm volatile("" : "+v"(c));
+    acc[0] = products_two<W, RT>(b0, rw, 0, c, scale);
+    for (;;) {
+      load_cols_two<W>(sg_cols, n_cols, j0 + 128, loff, b2);
+      if (__builtin_expect((hits = fast_two<W, RT>(b0, b1, rw, c, scale, acc)) != 0, 0)) {
+        phase = 0;
+#pragma unroll
+        for (int x = 0; x < 2 * W; ++x) cur[x] = b0[x];
+        break;
+      }
+      skip = 0;
+      if ((j0 += 64) >= g1) return true;
+      load_cols_two<W>(sg_cols, n_cols, j0 + 128, loff, b0);
+      if (__builtin_expect((hits = fast_two<W, RT>(b1, b2, rw, c, scale, acc)) != 0, 0)) {
+        phase = 1;
+#pragma unroll
+        for (int x = 0; x < 2 * W; ++x) cur[x] = b1[x];
+        break;
+      }
+      skip = 0;
+      if ((j0 += 64) >= g1) return true;
+      load_cols_two<W>(sg_cols, n_cols, j0 + 128, loff, b1);
+      if (__builtin_expect((hits = fast_two<W, RT>(b2, b0, rw, c, scale, acc)) != 0, 0)) {
+        phase = 2;
+#pragma unroll
+        for (int x = 0; x < 2 * W; ++x) cur[x] = b2[x];
+        break;
+      }
+      skip = 0;
+      if ((j0 += 64) >= g1) return true;
+    }
+    if (!emit_two<W, RT, COS>(rw, cur, hits, scale, j0, run, jb, skip, sink)) return false;
+    skip = 0;
+    if ((j0 += 64) >= g1) return true;
+    // b0 and b1 take the columns of steps j0 and j0 + 64
+#pragma unroll
+    for (int x = 0; x < 2 * W; ++x) {
+      const uint4 x0 = phase == 0 ? b1[x] : phase == 1 ? b2[x] : b0[x];
+      const uint4 x1 = phase == 0 ? b2[x] : phase == 1 ? b0[x] : b1[x];
+      b0[x] = x0;
+      b1[x] = x1;
+    }
+  }
+}
+
+// One tile, as run_tile_mfma.
+template <int W, int RT, bool COS>
+__device__ __forceinline__ bool run_tile_two(const TileJob &jb, Sink &sink) {
+  static_assert(W == 1, "wider dot products leave the start value's range");
+  const ArgPtr ka = args();
+  const uint4 *__restrict__ sg_rows = ka->sg_rows, *__restrict__ sg_cols = ka->sg_cols;
+  const uint32_t *__restrict__ size_rows = ka->size_rows, *__restrict__ size_cols = ka->size_cols;
+  const uint32_t n_rows = ka->cfg.n_rows, n_cols = ka->cfg.n_cols;
+  const uint32_t lane = threadIdx.x & 63, jr = lane & 31;
+  const int scale = lane < 32 ? 127 - 1 : 127 + 15;
+  static_assert(32 * RT <= kTwoRows, "rows fit their LDS arrays");
+  PRows<W, RT> rw;
+  rw.row = reinterpret_cast<uint32_t(*)[kTwoRows]>(sink.rows);
+  // Rows 64 x + lane for the LDS arrays, without branches (see run_tile_mfma).
+  const uint32_t last = jb.row_end - 1;
+  uint32_t size[RT / 2], lo[RT / 2], hi[RT / 2];
+  uint64_t bits[RT / 2];
+#pragma unroll
+  for (int x = 0; x < RT / 2; ++x) {
+    const uint32_t i = min(jb.row0 + 64u * x + lane, last);
+    size[x] = size_rows[i];
+    bits[x] = ka->bm_rows[i];
+  }
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt) {
+    const uint32_t i = jb.row0 + 32u * rt + jr;
+    load_cols_two<W>(sg_rows, n_rows, i <= last ? i : n_rows, 0, rw.sg[rt]);
+  }
+#pragma unroll
+  for (int x = 0; x < RT / 2; ++x) {
+    lo[x] = jb.cmin[size[x]];
+    hi[x] = jb.cmax[size[x]];
+  }
+#pragma unroll
+  for (int x = 0; x < RT / 2; ++x) {
+    const uint32_t r = 64u * x + lane;
+    const bool ok = jb.row0 + r <= last;
+    rw.row[0][r] = ok ? size[x] : 0u;
+    rw.row[1][r] = ok ? lo[x] : 0xFFFFFFFFu;
+    rw.row[2][r] = ok ? hi[x] : 0u;
+    rw.row[3][r] = (uint32_t)bits[x];
+    rw.row[4][r] = (uint32_t)(bits[x] >> 32);
+  }
+  __builtin_amdgcn_wave_barrier();
+  uint32_t skip = jb.first;
+  uint32_t j = jb.c0;
+  const uint32_t loff = lane * 32u;
+  uint32_t c = j < jb.c1 ? as_const(size_cols)[j] : 0u;
+  uint32_t resumed_end = jb.end;
+  while (j < jb.c1) {
+    uint4 b0[2 * W], b1[2 * W];
+    load_cols_two<W>(sg_cols, n_cols, j, loff, b0);
+    load_cols_two<W>(sg_cols, n_cols, j + 64, loff, b1);
+    ColRun run = col_run(jb.sstart, jb.col_base, jb.col_max, c, j, jb.c1);
+    if (resumed_end) {
+      run.end = min(max(resumed_end, j + 1), jb.c1);
+      run.hi = as_const(size_cols)[run.end - 1];
+      resumed_end = 0;
+    }
+    if (run.end < jb.c1) c = as_const(size_cols)[run.end];
+    bool any_ok = false;
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) {
+      const uint32_t x = 32u * rt + jr, hi = rw.row[2][x];
+      const bool in_band = run.lo <= hi && run.hi >= rw.row[1][x];
+      // (slack[0] for a row outside the band, as in run_tile_mfma; -1: never)
+      const int32_t sl = run_slack<COS>(jb, in_band ? rw.row[0][x] : 0u, run.lo,
+                                        in_band ? min(run.hi, hi) : 0u);
+      rw.thr[rt] = pack_threshold<W>(32 * W - (in_band ? sl : -1));
+      any_ok |= in_band;
+    }
+    if (__ballot(any_ok)) {
+      if (!sweep_two<W, RT, COS>(sg_cols, n_cols, rw, scale, b0, b1, j, run, jb, skip, sink))
+        return false;
+    }
+    skip = 0;
+    j = run.end;
+  }
+  // the tile's staged pairs go out before the next tile
+  return flush(sink, true);
+}
+
+// Widths whose kernel takes two columns per accumulator, and the waves per SIMD
+// the register budget of a width aims at.
+constexpr bool two_columns(int w) { return w == 1; }
 template <int W>
 constexpr int mfma_waves() {
   return W <= 2 ? 3 : W <= 4 ? 2 : 1;
 }
 
+// LDS bytes of a wave.
+template <int W>
+constexpr uint32_t mfma_wave_lds() {
+  return kStage * sizeof(uint2) + 64 * kMaxRowTiles * sizeof(uint32_t) +
+         (two_columns(W) ? kTwoWords * sizeof(uint32_t) : 1024 * sizeof(int16_t));
+}
+
 template <int W, int RT, bool COS>
 __global__ __launch_bounds__(kBlock, mfma_waves<W>()) void k_filter_mfma(FilterArgs) {
-  // kStage entries per wave, then 1024 dot products per wave
+  static_assert(RT <= kMaxRowTiles, "kept values of every row tile");
+  // per wave: kStage entries, kept values, the rows' sizes and bands or dot products
   extern __shared__ uint2 stage[];
-  const uint32_t w = threadIdx.x >> 6;
+  uint2 *mine = stage + (threadIdx.x >> 6) * (mfma_wave_lds<W>() / sizeof(uint2));
   Sink sink;
-  sink_init(sink, stage + w * kStage,
-            reinterpret_cast<int16_t *>(stage + (blockDim.x >> 6) * kStage) + w * 1024);
-  tile_loop(sink, [&](const TileJob &jb) { return run_tile_mfma<W, RT, COS>(jb, sink); });
+  sink_init(sink, mine, reinterpret_cast<uint32_t *>(mine + kStage),
+            reinterpret_cast<uint32_t *>(mine + kStage + 32 * kMaxRowTiles));
+  tile_loop(sink, [&](const TileJob &jb) {
+    if constexpr (two_columns(W)) return run_tile_two<W, RT, COS>(jb, sink);
+    else return run_tile_mfma<W, RT, COS>(jb, sink);
+  });
 }
 
 template <int W, int R, int U, bool COS>
@@ -1129,7 +1541,7 @@ hipError_t launch_shape(dim3 grid, hipStream_t st, const FilterArgs &a) {
 template <int W, int RT, bool COS>
 hipError_t launch_mfma(dim3 grid, hipStream_t st, const FilterArgs &a) {
   hipLaunchKernelGGL((k_filter_mfma<W, RT, COS>), grid, dim3(64 * a.cfg.block_waves),
-                     a.cfg.block_waves * (kStage * sizeof(uint2) + 1024 * sizeof(int16_t)), st, a);
+                     a.cfg.block_waves * mfma_wave_lds<W>(), st, a);
   return hipGetLastError();
 }
 

@@ -286,10 +286,10 @@ hipError_t launch_gather_bitmaps(const uint64_t *in, const uint32_t *perm, uint6
 // planes[(kb * (n + kSignPad) + s) * 2 + h]; half h holds bits 32h..32h+31
 // of the block, bit 8e+m of a half in nibble m of its dword e.  Sets n ..
 // n + kSignPad - 1 are all zero: lanes with no row load set n, and a step's
-// column loads (at most 95 columns past a column below n) stay inside the
+// column loads (at most 191 columns past a column below n) stay inside the
 // plane without a bounds test.  `bm`: n sets of `words` words, in the
 // order the planes take; planes: (n + kSignPad) * words * 2 entries.
-constexpr uint32_t kSignPad = 96;
+constexpr uint32_t kSignPad = 192;
 hipError_t launch_expand_signs(const uint64_t *bm, uint32_t words, uint64_t n, uint4 *planes,
                                hipStream_t st);
 
