@@ -1525,8 +1525,21 @@ struct RoundTimes {
   }
 };
 
-// Whether the tiles of width slot k get a wave each (kDirectTiles).
+// Whether the tiles of width slot k get a wave each (kDirectTiles).  From 256 bits
+// on only in a class of little work: its columns' planes outgrow an XCD's L2, which
+// then wants one region of the tiles per XCD, as the cursors have it, and that is
+// worth more than the 45 us they cost.  In a batch of 256 joins the 512-, 1024- and
+// 2048-bit classes take 6.5, 6.8 and 2.0 ms with a wave per tile and 4.4, 4.4 and
+// 1.6 with cursors; smaller classes are faster with a wave per tile (a join of long
+// sets: 512 bits 248 us against 348, 1024 bits 318 against 408).
+constexpr double kDirectWideNs = 700000.0;
 bool direct_slot(const Plan &pl, uint32_t k) {
+  const uint32_t words = pl.slot_words[k];
+  if (words >= 4) {
+    int a = 0;  // the automatic width that costs what this one does, or more
+    while (a + 1 < kNumAuto && kAutoWords[a] < words) ++a;
+    if ((double)pl.ops[k] / (4.0 * words + 1.0) * kFilterNsPerPair[a] > kDirectWideNs) return false;
+  }
   return pl.tile_hi[k] - pl.tile_lo[k] <= kDirectTiles;
 }
 
