@@ -38,6 +38,8 @@ namespace {
 
 __device__ __forceinline__ uint32_t rfl(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
 
+__device__ __forceinline__ float rfl(float v) { return __uint_as_float(rfl(__float_as_uint(v))); }
+
 __device__ __forceinline__ unsigned long long rfl64(unsigned long long v) {
   uint32_t lo = rfl((uint32_t)v), hi = rfl((uint32_t)(v >> 32));
   return ((unsigned long long)hi << 32) | lo;
@@ -620,7 +622,7 @@ __device__ __forceinline__ void tile_loop(Sink &sink, Run &&run) {
     job.cosine = rfl(td->sim) == SSJ_SIM_COSINE;
     job.p = rfl(td->p);
     job.q = rfl(td->q);
-    job.t = (float)job.p / (float)job.q;
+    job.t = rfl((float)job.p / (float)job.q);
     uint32_t c0, c1;
     job.diag = false;
     if (self) {
@@ -680,7 +682,7 @@ template <int W, int R, int U, bool COS>
 __global__ __launch_bounds__(kBlock) void k_filter(FilterArgs) {
   extern __shared__ uint2 stage[];  // kStage entries per wave
   Sink sink;
-  sink_init(sink, stage + (threadIdx.x >> 6) * kStage, nullptr, nullptr);
+  sink_init(sink, stage + rfl(threadIdx.x >> 6) * kStage, nullptr, nullptr);
   tile_loop(sink, [&](const TileJob &jb) { return run_tile<W, R, U, COS>(jb, sink); });
 }
 
@@ -766,6 +768,12 @@ __device__ __forceinline__ void load_signs(const uint4 *__restrict__ planes, uin
 template <int W>
 __device__ __forceinline__ void load_cols(const uint4 *__restrict__ planes, uint32_t n,
                                           uint32_t j0, uint32_t loff, uint4 (&a)[W]) {
+  // Opaque at 1024 bits: the compiler keeps loff widened to 64 bits, and the kernel has no
+  // registers for it.  With this and the uniform values below in scalar registers
+  // it uses no scratch memory: a reload in every step waited for all loads in
+  // flight, the ring's among them (the 1024-bit class of a batch of 256 joins:
+  // 4.31 -> 3.62 ms).
+  if (W >= 16) asm volatile("" : "+v"(loff));
 #pragma unroll
   for (int kb = 0; kb < W; ++kb) {
     const uint4 *p = planes + ((size_t)kb * (n + kSignPad) + j0) * 2;
@@ -1521,7 +1529,9 @@ __global__ __launch_bounds__(kBlock, mfma_waves<W>()) void k_filter_mfma(FilterA
   static_assert(RT <= kMaxRowTiles, "kept values of every row tile");
   // per wave: kStage entries, kept values, the rows' sizes and bands or dot products
   extern __shared__ uint2 stage[];
-  uint2 *mine = stage + (threadIdx.x >> 6) * (mfma_wave_lds<W>() / sizeof(uint2));
+  // (the wave's number is uniform: left to the compiler the three addresses take vector
+  // registers, which the kernel of 1024 bits has none of to spare)
+  uint2 *mine = stage + rfl(threadIdx.x >> 6) * (mfma_wave_lds<W>() / sizeof(uint2));
   Sink sink;
   sink_init(sink, mine, reinterpret_cast<uint32_t *>(mine + kStage),
             reinterpret_cast<uint32_t *>(mine + kStage + 32 * kMaxRowTiles));
