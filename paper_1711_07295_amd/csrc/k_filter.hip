@@ -495,12 +495,13 @@ __device__ __forceinline__ bool run_tile(const TileJob &jb, Sink &sink) {
 // direct launch (cfg.direct), each wave takes one tile and ends: no cursor
 // is read, and the workgroup dispatch balances the tiles of an XCD, which
 // gets every eighth run of kDirectDeal tiles (regions as the cursors have
-// them would leave XCDs idle: nobody takes their neighbours' tiles).  The cursors cost a launch about 45 us that does not grow with
-// its work: a wave that finds its own cursor dry reads the other 63 one
-// after the other, a memory round trip each.  In a direct launch every
-// tile a full queue keeps a wave from starting goes to the resume list (a
-// round that resumes has no fresh tiles there: the first round had them
-// all).
+// them would leave XCDs idle: nobody takes their neighbours' tiles).  The
+// cursors cost a launch about 45 us that does not grow with its work: a wave
+// that finds its own cursor dry reads the other 63 one after the other, a
+// memory round trip each.  In a direct launch every tile a full queue keeps a
+// wave from starting goes to the resume list (a round that resumes has no
+// fresh tiles there: the first round had them all), and a round that
+// resumes starts the waves the GPU holds, each with its share of the list.
 constexpr uint32_t kDirectDeal = 8;
 
 template <class Run>
@@ -511,19 +512,7 @@ __device__ __forceinline__ void tile_loop(Sink &sink, Run &&run) {
   uint32_t entry = wave;
   bool fresh = true;     // direct: the wave's tile is still to take
   bool stopped = false;  // this wave found the queue full
-  // the tile stays to be done from (c, s) on, a step of a run that ends at e
-  auto record = [&](uint32_t tile, uint32_t c, uint32_t s, uint32_t e) {
-    const ArgPtr a = args();
-    if (lane == 0) {
-      const uint32_t q = atomicAdd(&a->ctr->n_resume, 1u);
-      Resume rs;
-      rs.tile = tile;
-      rs.col = c;
-      rs.slab = s;
-      rs.end = e;
-      if (q < a->cfg.resume_cap) a->resume_out[q] = rs;
-    }
-  };
+  bool undone = false;   // ... and left tile t to be done from (col, slab) on
   // Each XCD owns one contiguous region of the tile range, so that its
   // waves sweep neighbouring row blocks whose columns stay in its L2.
   // Inside a region the tiles are dealt to kSub sub-cursors in blocks of
@@ -541,6 +530,34 @@ __device__ __forceinline__ void tile_loop(Sink &sink, Run &&run) {
     const uint32_t tile_lo = a->cfg.tile_lo, tile_hi = a->cfg.tile_hi;
     const uint32_t n_tiles = tile_hi - tile_lo;
     const uint32_t n_resume = min(a->cfg.n_resume_in, a->cfg.resume_cap);
+    const bool full =
+        stopped ||
+        rfl(__hip_atomic_load(&ctr->overflow, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) != 0;
+    if (full) {
+      // The tile, and what the wave has left of the resume entries (entry, entry + waves,
+      // ...), stay to be done: one reservation for 64 of them.  One each, on one
+      // address, took most of a round of a small queue over many tiles: a 40,000-slot
+      // queue over 25,000 tiles 0.62 ms a round, so 0.22.
+      do {
+        const uint64_t e = entry + (uint64_t)lane * a->cfg.waves;
+        uint32_t rt = t, rc = col, rs = slab, re = end;  // lane 63: the tile
+        bool left = undone && lane == 63;
+        if (lane < 63 && e < n_resume) {
+          const Resume *in = a->resume_in + e;
+          rt = in->tile, rc = in->col, rs = in->slab, re = in->end;
+          left = rt >= tile_lo && rt < tile_hi;
+        }
+        const unsigned long long m = __ballot(left);
+        if (m) {
+          uint32_t at = 0;
+          if (lane == 0) at = atomicAdd(&ctr->n_resume, (uint32_t)__popcll(m));
+          at = rfl(at) + (uint32_t)__popcll(m & __lanemask_lt());
+          if (left && at < a->cfg.resume_cap) a->resume_out[at] = Resume{rt, rc, rs, re};
+        }
+        undone = false;
+        entry = (uint32_t)min(entry + (uint64_t)63 * a->cfg.waves, (uint64_t)n_resume);
+      } while (entry < n_resume);
+    }
     bool resumed = false;
     while (entry < n_resume && !resumed) {
       const auto *in = as_const(a->resume_in) + entry;
@@ -551,13 +568,6 @@ __device__ __forceinline__ void tile_loop(Sink &sink, Run &&run) {
       resumed = t >= tile_lo && t < tile_hi;
       entry += a->cfg.waves;
     }
-    const bool full =
-        stopped ||
-        rfl(__hip_atomic_load(&ctr->overflow, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) != 0;
-    if (resumed && full) {
-      record(t, col, slab, end);
-      continue;
-    }
     if (!resumed && a->cfg.direct) {
       if (!fresh || a->cfg.n_resume_in) break;
       fresh = false;
@@ -567,8 +577,10 @@ __device__ __forceinline__ void tile_loop(Sink &sink, Run &&run) {
       if (k >= n_tiles) break;
       t = tile_lo + k;
       if (full) {
-        record(t, kTileStart, 0, 0);
-        break;
+        col = kTileStart;
+        slab = end = 0;
+        undone = true;
+        continue;
       }
     } else if (!resumed) {
       if (full) break;
@@ -649,11 +661,13 @@ __device__ __forceinline__ void tile_loop(Sink &sink, Run &&run) {
     job.c0 = c0;
     job.c1 = min(c1, a->cfg.n_cols);
     if (!run(job)) {
-      // the queue is full: record where this tile resumes, and take no more
-      // (the loop records what is left of the wave's resume entries)
-      if (lane == 0) atomicOr(&ctr->overflow, 1u);
-      stopped = true;
-      record(t, rfl(sink.fail_col), rfl(sink.fail_slab), rfl(sink.fail_end));
+      // the queue is full: the tile resumes at the sink's point, and the wave takes no more
+      if (lane == 0)
+        __hip_atomic_store(&ctr->overflow, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      stopped = undone = true;
+      col = rfl(sink.fail_col);
+      slab = rfl(sink.fail_slab);
+      end = rfl(sink.fail_end);
     }
   }
   sink_pad(sink);
@@ -1512,10 +1526,7 @@ __device__ __forceinline__ bool run_tile_two(const TileJob &jb, Sink &sink) {
 // Widths whose kernel takes two columns per accumulator, and the waves per SIMD
 // the register budget of a width aims at.
 constexpr bool two_columns(int w) { return w == 1; }
-template <int W>
-constexpr int mfma_waves() {
-  return W <= 2 ? 3 : W <= 4 ? 2 : 1;
-}
+constexpr int mfma_waves(int w) { return w <= 2 ? 3 : w <= 4 ? 2 : 1; }
 
 // LDS bytes of a wave.
 template <int W>
@@ -1525,7 +1536,7 @@ constexpr uint32_t mfma_wave_lds() {
 }
 
 template <int W, int RT, bool COS>
-__global__ __launch_bounds__(kBlock, mfma_waves<W>()) void k_filter_mfma(FilterArgs) {
+__global__ __launch_bounds__(kBlock, mfma_waves(W)) void k_filter_mfma(FilterArgs) {
   static_assert(RT <= kMaxRowTiles, "kept values of every row tile");
   // per wave: kStage entries, kept values, the rows' sizes and bands or dot products
   extern __shared__ uint2 stage[];
@@ -1633,6 +1644,10 @@ int filter_grid_blocks() {
   return cus * 8;  // 32 waves per CU
 }
 
+uint32_t mfma_resident_waves(uint32_t words) {
+  return (uint32_t)filter_grid_blocks() / 8 * 4 * (uint32_t)mfma_waves((int)words);
+}
+
 hipError_t launch_filter(uint32_t padded_words, bool cosine, const FilterArgs &args_in,
                          hipStream_t st) {
   FilterArgs a = args_in;
@@ -1650,9 +1665,14 @@ hipError_t launch_filter(uint32_t padded_words, bool cosine, const FilterArgs &a
     constexpr uint64_t kTurn = kXcds * kDirectDeal;
     grid = dim3((unsigned)(kTurn * ((n_tiles + kTurn - 1) / kTurn)));
   } else {
+    // (A direct launch of the matrix-core kernel that resumes: no more waves than the GPU
+    // holds.  Each costs a round that fills the queue two atomics on one address,
+    // a slot reservation that fails and one of resume entries.)
+    const uint64_t most = a.cfg.direct && a.sg_rows ? mfma_resident_waves(padded_words)
+                                                    : (uint64_t)filter_grid_blocks() * (kBlock / 64);
     const uint64_t need = std::max<uint64_t>(
         a.cfg.direct ? a.cfg.n_resume_in : std::max<uint64_t>(n_tiles, a.cfg.n_resume_in), 1);
-    grid = dim3((unsigned)std::min<uint64_t>((uint64_t)filter_grid_blocks() * 4 / waves_per_block,
+    grid = dim3((unsigned)std::min<uint64_t>(most / waves_per_block,
                                              (need + waves_per_block - 1) / waves_per_block));
   }
   a.cfg.block_waves = (uint32_t)waves_per_block;

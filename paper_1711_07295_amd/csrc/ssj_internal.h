@@ -355,6 +355,8 @@ uint32_t filter_padded_words(uint32_t words);
 // mfma: prefer the matrix-core kernel where it exists for the width
 FilterShape filter_shape(uint32_t padded_words, bool mfma);
 int filter_grid_blocks();
+// Waves of the matrix-core kernel of `words` words that the current device holds at once.
+uint32_t mfma_resident_waves(uint32_t words);
 
 struct FilterArgs {
   const uint64_t *bm_rows;
