@@ -216,10 +216,28 @@ struct TileJob {
   const uint32_t *cmin, *cmax;
   const_u32_ptr sstart;
   uint32_t col_base, col_max;  // first column and largest size of the column space
+  uint32_t task;
   bool cosine;
   uint32_t p, q;
   float t;         // p / q
 };
+
+// A task's exact test.  With Cosine among the call's functions it is read where it is
+// used: kept across the vector-ALU sweeps, its fields took scalar registers from the
+// columns' buffers (1024 bits: 105 instructions a column against 96).
+struct PairTest {
+  const int32_t *slack;
+  bool cosine;
+  uint32_t p, q;
+};
+template <bool COS>
+__device__ __forceinline__ PairTest pair_test(const TileJob &jb) {
+  if constexpr (!COS) return PairTest{jb.slack, false, 0, 0};
+  const ArgPtr a = args();
+  const auto *td = as_const(a->tasks) + jb.task;
+  return PairTest{reinterpret_cast<const int32_t *>(a->tables + td->slack_off),
+                  td->sim == SSJ_SIM_COSINE, td->p, td->q};
+}
 
 // Largest slack a + c' - 2 omin(a, c') a row of size a can have with a column of
 // size c' in [lo, hi], all inside the band: exact for lo == hi, else at most
@@ -241,8 +259,8 @@ __device__ __forceinline__ int32_t run_slack(const TileJob &jb, uint32_t a, uint
 // Whether a pair of sizes a and c inside the band, h differing bits, is kept:
 // h <= a + c - 2 omin(a, c).  For Cosine: half of a + c - h, the overlap
 // bound, reaches the threshold.
-template <bool COS>
-__device__ __forceinline__ bool pair_kept(const TileJob &jb, uint32_t a, uint32_t c, int32_t h) {
+template <bool COS, class Test>
+__device__ __forceinline__ bool pair_kept(const Test &jb, uint32_t a, uint32_t c, int32_t h) {
   if (COS && jb.cosine) {
     const int32_t s = (int32_t)(a + c) - h;
     return s >= 0 && cosine_reaches((uint32_t)s >> 1, a, c, jb.p, jb.q);
@@ -255,7 +273,6 @@ template <int R>
 struct Exact {
   bool bound;
   const uint32_t (&bias)[R];
-  const uint32_t *size_cols;
   const TileJob *job;
 };
 
@@ -299,13 +316,14 @@ __device__ __forceinline__ bool emit(const Rows<W, R> &rw, const uint32_t (&d)[U
   if (ex.bound) {
     // each kept pair at its own sizes.  The
     // biased distance is bias + h, so h = d - bias.
+    const PairTest test = pair_test<COS>(*ex.job);
 #pragma unroll
     for (int x = 0; x < U * R; ++x) {
-      const uint32_t c = as_const(ex.size_cols)[j + x / R];
+      const uint32_t c = as_const(args()->size_cols)[j + x / R];
       const uint32_t h = d[x / R][x % R] - ex.bias[x % R];
       if (((kb >> x) & 1u) &&
           !(c >= rw.cmn[x % R] && c <= rw.cmx[x % R] &&
-            pair_kept<COS>(*ex.job, rw.size[x % R], c, (int32_t)h)))
+            pair_kept<COS>(test, rw.size[x % R], c, (int32_t)h)))
         kb &= ~(1u << x);
     }
   }
@@ -368,7 +386,11 @@ __device__ __forceinline__ bool step(const Rows<W, R> &rw, const Exact<R> &ex,
       d[u][r] = h;
       acc |= h;
     }
-  if (__ballot((int32_t)acc < 0)) return emit<W, R, U, COS>(rw, d, j, ex, sink);
+  // (the expectation and the sweep's loop of one exit keep what the slow path needs out of
+  // the fast one: without them a 2048-bit class of 150,000 long sets took 34.5 ms,
+  // with them 30.1, one of 300,000 short sets at 512 bits 6.35 and 6.00)
+  if (__builtin_expect(__ballot((int32_t)acc < 0) != 0, 0))
+    return emit<W, R, U, COS>(rw, d, j, ex, sink);
   return true;
 }
 
@@ -376,12 +398,11 @@ __device__ __forceinline__ bool step(const Rows<W, R> &rw, const Exact<R> &ex,
 template <int W, int R, int U, bool DIAG, bool COS>
 __device__ __forceinline__ bool sweep(const uint64_t *__restrict__ bm_cols, const Rows<W, R> &rw,
                                       const int32_t (&thr)[R], uint32_t j, uint32_t g1,
-                                      bool bound, const uint32_t *size_cols,
-                                      const TileJob &jb, Sink &sink) {
+                                      bool bound, const TileJob &jb, Sink &sink) {
   uint32_t bias[R];
 #pragma unroll
   for (int r = 0; r < R; ++r) bias[r] = (uint32_t)(-thr[r] - 1);
-  const Exact<R> ex{bound, bias, size_cols, &jb};
+  const Exact<R> ex{bound, bias, &jb};
   // Scalar loads may return out of order, so a wave can only wait for all
   // of them.  Two register buffers alternate: the wait for the current
   // step's columns comes before the next step's load is issued (the next
@@ -390,18 +411,20 @@ __device__ __forceinline__ bool sweep(const uint64_t *__restrict__ bm_cols, cons
   // copied between steps.
   uint32_t ba[U][2 * W], bb[U][2 * W];
   if (j + U <= g1) load_cols<W, U>(bm_cols, j, ba);
-  for (;;) {
-    if (j + U > g1) break;
+  bool ok = true;
+  while (j + U <= g1) {
     const uint32_t jb = after(j + U);
     if (jb + U <= g1) load_cols<W, U>(bm_cols, jb, bb);
-    if (!step<W, R, U, DIAG, COS>(rw, ex, ba, j, sink)) return false;
+    ok = step<W, R, U, DIAG, COS>(rw, ex, ba, j, sink);
     j += U;
-    if (j + U > g1) break;
+    if (!ok || j + U > g1) break;
     const uint32_t ja = after(j + U);
     if (ja + U <= g1) load_cols<W, U>(bm_cols, ja, ba);
-    if (!step<W, R, U, DIAG, COS>(rw, ex, bb, j, sink)) return false;
+    ok = step<W, R, U, DIAG, COS>(rw, ex, bb, j, sink);
+    if (!ok) break;
     j += U;
   }
+  if (!ok) return false;
   for (; j < g1; ++j) {
     uint32_t cb[1][2 * W];
     load_cols<W, 1>(bm_cols, j, cb);
@@ -472,10 +495,8 @@ __device__ __forceinline__ bool run_tile(const TileJob &jb, Sink &sink) {
       if ((uint32_t)r < first_slab) thr[r] = -1;
     first_slab = 0;
     if (__ballot(any_ok)) {
-      const bool ok = diag ? sweep<W, R, U, true, COS>(bm_cols, rw, thr, j, gend, bound,
-                                                       size_cols, jb, sink)
-                           : sweep<W, R, U, false, COS>(bm_cols, rw, thr, j, gend, bound,
-                                                        size_cols, jb, sink);
+      const bool ok = diag ? sweep<W, R, U, true, COS>(bm_cols, rw, thr, j, gend, bound, jb, sink)
+                           : sweep<W, R, U, false, COS>(bm_cols, rw, thr, j, gend, bound, jb, sink);
       if (!ok) return false;
     }
     j = gend;
@@ -625,6 +646,7 @@ __device__ __forceinline__ void tile_loop(Sink &sink, Run &&run) {
     const uint32_t task = rfl(blocks[b].task);
     const bool self = rfl(blocks[b].self) != 0;
     const auto *td = as_const(a->tasks) + task;
+    job.task = task;
     job.slack = reinterpret_cast<const int32_t *>(tables + rfl(td->slack_off));
     job.cmin = tables + rfl(td->cmin_off);
     job.cmax = tables + rfl(td->cmax_off);
