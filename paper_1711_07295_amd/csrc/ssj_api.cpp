@@ -52,18 +52,32 @@ constexpr uint32_t kDefaultTileCols = 2048;
 // few columns, and the launch lasts as long as its slowest tile.  (The
 // matrix-core kernel measured no gain below 64: it takes 32 columns a step.)
 //
-// Eight tiles for every wave the GPU holds at the kernel's registers (three,
-// two or one waves per SIMD at up to 128, 256 and more bits; the vector-ALU
-// classes as the last): with fewer the last round of tiles leaves much of
-// the GPU idle, with more the tiles' starts weigh.  Measured at 4,096 /
-// 8,192 / 16,384 / 32,768 tiles: b = 128 in a batch of 48 collections
-// 1272 / 1273 / 996 / 650 us, in a query of 2,000 sets 353 / 291 / 268 / 265;
-// b = 256 in the batch 927 / 930 / 741 / 768, in a 3,000-set R-S join 201 /
-// 133 / 121 / 124; b = 512 in the batch 274 / 292 / 324 / 408.
+// On the matrix cores eight tiles for every wave the GPU holds at the kernel's
+// registers (three, two or one waves per SIMD at up to 128, 256 and more
+// bits): with fewer the last round of tiles leaves much of the GPU idle, with
+// more the tiles' starts weigh.  Measured at 4,096 / 8,192 / 16,384 / 32,768
+// tiles: b = 128 in a batch of 48 collections 1272 / 1273 / 996 / 650 us, in a
+// query of 2,000 sets 353 / 291 / 268 / 265; b = 256 in the batch 927 / 930 /
+// 741 / 768, in a 3,000-set R-S join 201 / 133 / 121 / 124; b = 512 in the
+// batch 274 / 292 / 324 / 408.
+//
+// On the vector ALUs eight tiles for every SIMD below 512 bits and 24 from there
+// on.  At 8,192 / 16,384 / 24,576 / 32,768 tiles: b = 2048 in a batch of 256
+// collections 1568 / 1455 / 1386 / 1379 us, in a join of 60,000 sets 2056 / 1870
+// / 1811 / 1786; b = 512 in a join of 20,000 long sets 206 / 163 / 151 / 152;
+// b = 256 in the same join, where most pairs survive, 578 / 823 / 836 / 849, and
+// in the join of 60,000 sets 173 / 165 / 171 / 177.
 uint64_t min_slot_tiles(const FilterShape &shape) {
-  if (!shape.mfma || shape.words > 4) return 8 * 1024;
-  return shape.words > 2 ? 8 * 2048 : 8 * 3072;
+  const uint64_t simds = (uint64_t)filter_grid_blocks() / 8 * 4;
+  if (shape.mfma) return 8ull * mfma_resident_waves(shape.words);
+  return (shape.words < 8 ? 8 : 24) * simds;
 }
+// Widest tiles of a vector-ALU class below 512 bits.  These kernels hold many waves, and
+// a large class would have three or four tiles for each: the launch then waits
+// for the last ones.  300,000 sets at 2048 / 512 columns: b = 64 4.37 / 1.98 ms,
+// b = 128 2.55 / 1.97, b = 256 3.27 / 3.12.
+constexpr uint32_t kMaxTileColsValu = 512;
+
 // Host threads that plan the width classes of a call's tasks (16 tasks or
 // more per thread), when the tasks' largest sizes sum to kPlanThreadSizes
 // or more.
@@ -1753,6 +1767,7 @@ void join_begin(Space &R, Space &C, const std::vector<TaskIn> &tasks, const Join
       const FilterShape shape = filter_shape(pl.slot_words[k], pl.slot_mfma[k]);
       const uint64_t want = slot_band[k] / ((uint64_t)shape.rows * min_slot_tiles(shape));
       const uint32_t floor_cols = shape.mfma ? kMinTileCols : kMinTileColsValu;
+      if (!shape.mfma && shape.words < 8) tile_cols = std::min(tile_cols, kMaxTileColsValu);
       tile_cols = (uint32_t)std::max<uint64_t>(floor_cols, std::min<uint64_t>(tile_cols, want));
     }
     pl.slot_tile_cols[k] = tile_cols;

@@ -82,3 +82,14 @@ def test_steps_of_several_sizes(sparse, sim, p, q, b, flags):
                                     flags=flags | ssj.SSJ_FLAG_SURVIVORS_ONLY)
         assert st["survivors"] == cnt and st["band_pairs"] == band
         assert np.array_equal(got, want)
+
+
+@pytest.mark.parametrize("n,b,least", [(60_000, 2048, 20_000), (60_000, 512, 20_000),
+                                       (200_000, 64, 20_000), (200_000, 192, 40_000)])
+def test_vector_alu_classes_are_cut_into_enough_tiles(n, b, least):
+    c = gen.generate(n_sets=n, universe=n, zipf_s=1.0, size_dist=gen.SIZE_LOGNORMAL, size_a=20.0,
+                     size_b=0.8, size_lo=2, size_hi=500, planted_frac=0.05, seed=81)
+    d = ssj.to_device(c.offsets, c.tokens)
+    got, st = ssj.ssj_self_join(d, 4, 5, b_bits=b, flags=ssj.SSJ_FLAG_VALU)
+    want, _ = ssj.ssj_self_join(d, 4, 5, b_bits=256, flags=ssj.SSJ_FLAG_MFMA)
+    assert st["class_tiles"][0] > least and np.array_equal(got, want)
