@@ -394,7 +394,14 @@ hipError_t launch_method(bool pow2, hipStream_t st, const SideDesc *sides, uint3
                          const uint32_t *rank, const uint32_t *side_of, uint32_t b_bits,
                          uint32_t out_words, uint64_t *out, const FoldOut &fold,
                          JoinCounters *ctr, const BuildCheck &chk) {
-  if ((rank || !perm) && seg_blocks) {
+  // Bitmap-Next of a collection of few segments takes a wave per set: probes in one set
+  // wait for each other, a workgroup per 256 sets leaves most of the GPU idle
+  // then, and there is no fold to share.  At 64 bits, segments / waves: 4,000 sets of 550
+  // tokens 246 / 32 us, 20,000 of 200 128 / 32, 65,000 of 12 34 / 32; 100,000 of
+  // 19 40.5 / 40.4, 200,000 of 12 36 / 59, 1,000,000 of 12 63 / 228.
+  constexpr uint64_t kFewSegments = 256;
+  const bool by_set = METHOD == SSJ_BM_NEXT && n <= kFewSegments * kSegSets;
+  if ((rank || !perm) && seg_blocks && !by_set) {
 #define SSJ_SEG(wo)                                                                     \
   case wo:                                                                              \
     return launch_seg<wo, METHOD, CHECK>(pow2, st, sides, n_sides, seg_blocks, rank, n, b_bits, \
