@@ -2083,7 +2083,8 @@ void join_end(const JoinRun &jr, Arena &ar, hipStream_t st, RoundTimes &tm, Time
   uint64_t results_n = 0, queue_slots = 0;
   JoinCounters ctr_h{};
   // A round ends with the counters on the host, and with them the sorted
-  // pairs when there are few and no later step adds to them.
+  // pairs when there are few and no later step adds to them.  With no
+  // page-locked block to be had a copy brings the counters.
   constexpr size_t kCtrBytes = offsetof(JoinCounters, queue_next);
   FinishArgs fin{};
   fin.ctr = ctr;
@@ -2092,18 +2093,22 @@ void join_end(const JoinRun &jr, Arena &ar, hipStream_t st, RoundTimes &tm, Time
   fin.jb = jb;
   fin.bits = tb + ib + jb;
   fin.h_ctr = ar.pinned<uint32_t>(kCtrBytes / 4);
-  if (!fin.h_ctr) throw Fail{SSJ_E_NOMEM};
   fin.h_start = ar.pinned<uint64_t>((uint64_t)n_tasks + 1);
   fin.h_pairs = ar.pinned<ssj_pair>(kSmallResults);
-  fin.max_results = n_probe || !fin.h_start || !fin.h_pairs ? 0 : kSmallResults;
+  fin.max_results =
+      n_probe || !fin.h_ctr || !fin.h_start || !fin.h_pairs ? 0 : kSmallResults;
   if (pl.n_tiles) {
     for (;;) {
-      fin.keys = results;
-      if (tm.marks.empty()) tm.mark(RoundTimes::kStart, st);
-      check(launch_finish(fin, st));
-      tm.mark(RoundTimes::kFinish, st);
+      if (fin.h_ctr) {
+        fin.keys = results;
+        if (tm.marks.empty()) tm.mark(RoundTimes::kStart, st);
+        check(launch_finish(fin, st));
+        tm.mark(RoundTimes::kFinish, st);
+      } else {
+        d2h(&ctr_h, ctr, 1, st);
+      }
       sync(st);
-      std::memcpy(static_cast<void *>(&ctr_h), fin.h_ctr, kCtrBytes);
+      if (fin.h_ctr) std::memcpy(static_cast<void *>(&ctr_h), fin.h_ctr, kCtrBytes);
       if (ctr_h.error & kErrUnsorted) throw Fail{SSJ_E_UNSORTED};
       queue_slots += std::min<uint64_t>(ctr_h.queue_count, qcap);
       results_n = ctr_h.results;
