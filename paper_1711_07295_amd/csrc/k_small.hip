@@ -53,12 +53,15 @@ __device__ __forceinline__ void block_sort(uint32_t n, int bits, SortScratch &s,
         const unsigned long long set = __ballot((d >> b) & 1u);
         peers &= ((d >> b) & 1u) ? set : ~set;
       }
+      // the wave's count of the digit: every peer reads it before the highest of them
+      // advances it, and the next 64 keys read it after that
       const uint32_t prior = s.cnt[w][d];
+      __builtin_amdgcn_wave_barrier();
       dig[it] = d;
       rank[it] = prior + (uint32_t)__popcll(peers & below);
-      // the highest lane of each peer group advances the wave's count
       if (valid && (peers >> lane) == 1ull)
         s.cnt[w][d] = (uint16_t)(prior + (uint32_t)__popcll(peers));
+      __builtin_amdgcn_wave_barrier();
     }
     __syncthreads();
     // digit totals, the waves' offsets inside a digit, and the digits' bases

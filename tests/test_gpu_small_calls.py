@@ -37,6 +37,20 @@ def test_result_counts(extra):
     assert np.array_equal(got, oracle.self_join(c.offsets, c.tokens, 9, 10))
 
 
+@pytest.mark.parametrize("step", [1, 2, 256])
+def test_keys_that_share_their_digits(step):
+    """8,192 sets of one size, so that all have one sort key; 64 (32) equal ones, `step` apart, whose
+    pairs share none, half or all of the two low digits of their result keys."""
+    rng = np.random.default_rng(step)
+    sets = [np.sort(rng.choice(4000, 8, replace=False)) for _ in range(8192)]
+    for k in range(64):
+        sets[k * step if step < 256 else k % 32 * step] = np.arange(5000, 5008)
+    c = gen.from_lists(sets)
+    got, _ = ssj.ssj_self_join(_dev(c), 9, 10)
+    want = oracle.self_join(c.offsets, c.tokens, 9, 10)
+    assert len(want) >= (2016 if step < 256 else 496) and np.array_equal(got, want)
+
+
 @pytest.mark.parametrize("n_sides", [1, 2, 1024, 1025])
 def test_side_counts(n_sides):
     """Many sides, empty ones and empty sets among them."""
