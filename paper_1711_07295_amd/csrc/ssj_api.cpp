@@ -580,12 +580,17 @@ void space_begin(Space &sp, Arena &ar, hipStream_t st) {
   d2h(reinterpret_cast<uint32_t *>(sp.h_head), &sp.ctr->error, 2, st);
 }
 
+// The preparation's checks of the offsets; the stream has been waited for.
+void space_checked(const Space &sp) {
+  if (sp.h_head->error & (kErrOffsets | kErrTooBig)) throw Fail{SSJ_E_INVALID};
+}
+
 // Stable sort by (side, size), group starts of every side (copied to the
 // host; the caller synchronises before space_finish), and the inverse
 // permutation when bitmaps are to be built.
 // Arrays the space keeps come from `ar`, the sort's temporaries from `tmp_ar`.
 void space_sort(Space &sp, bool need_rank, Arena &ar, Arena &tmp_ar, hipStream_t st) {
-  if (sp.h_head->error & (kErrOffsets | kErrTooBig)) throw Fail{SSJ_E_INVALID};
+  space_checked(sp);
   sp.max_size = sp.h_head->max_size;
   if ((uint64_t)sp.max_size * 2 + 2 > kMaxTable) throw Fail{SSJ_E_UNSUPPORTED};
   sp.stride = sp.max_size + 2;
@@ -620,7 +625,7 @@ void space_sort(Space &sp, bool need_rank, Arena &ar, Arena &tmp_ar, hipStream_t
 // The group starts and with them the largest size of every side; the stream
 // has been waited for.
 void space_finish(Space &sp) {
-  if (sp.h_head->error & (kErrOffsets | kErrTooBig)) throw Fail{SSJ_E_INVALID};
+  space_checked(sp);
   sp.max_size = sp.h_head->max_size;
   sp.stride = sp.max_size + 2;
   sp.sstart_h.assign(sp.h_sstart, sp.h_sstart + (size_t)sp.n_sides * sp.stride);
@@ -2412,6 +2417,7 @@ int join_one(const ssj_sets *R, const uint64_t *r_bm, const ssj_sets *S, const u
     }
     if (!self) space_begin(B, ar, st);
     if (!small || !self) sync(st);
+    if (small && !self) space_checked(A);  // R's errors come before S's
     if (!small) space_sort(A, r_bm == nullptr, ar, ar, st);
     if (!self) space_sort(B, s_bm == nullptr, ar, ar, st);
     Event sorted;

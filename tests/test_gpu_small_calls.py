@@ -2,6 +2,7 @@
 with few results, at the sizes where the general kernels take over."""
 import numpy as np
 import pytest
+import torch
 
 import gen
 import oracle
@@ -84,3 +85,20 @@ def test_bad_offsets_leave_the_small_path_with_their_error():
             with pytest.raises(ssj.SsjError) as e:
                 ssj.ssj_self_join(ssj.to_device(off, c.tokens), 4, 5, b_bits=b)
             assert e.value.status == ssj.SSJ_E_INVALID
+
+
+def test_rs_join_reports_the_first_collection_s_error():
+    """R malformed, S with a set larger than is handled: invalid, whether R is prepared in one
+    launch or not; S alone: unsupported."""
+    n = 1 << 25
+    big = ssj.DeviceSets(torch.tensor([0, n], dtype=torch.int64, device="cuda"),
+                         torch.arange(n, dtype=torch.int32, device="cuda"))
+    for k, status in ((100, ssj.SSJ_E_INVALID), (9000, ssj.SSJ_E_INVALID),
+                      (0, ssj.SSJ_E_UNSUPPORTED)):
+        off = np.arange(max(k, 5) + 1, dtype=np.uint64)
+        if k:
+            off[k // 2] = 1 << 40
+        r = ssj.to_device(off, np.zeros(max(k, 5), dtype=np.uint32))
+        with pytest.raises(ssj.SsjError) as e:
+            ssj.ssj_rs_join(r, big, 4, 5)
+        assert e.value.status == status
