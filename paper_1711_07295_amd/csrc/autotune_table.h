@@ -11,12 +11,8 @@
 // wave takes to stage a survivor, from one tile where nearly every pair
 // survives (64 x 2048 random sets of b tokens at 1/2).
 //
-// The b = 64 entries (2.9462e-05, 6144 pairs a step, 41 us a launch) are those of
-// its kernel before it took two columns per accumulator.  Measured anew it reads
-// 2.46e-05, 12,288 and 25 us, and 1.28 ns an entry; with those a batch of 48 joins
-// puts its sizes up to 12 at 64 bits and is slower (3.19 -> 3.69 ms, the entries
-// of that class being dearer than the model has them), and no other workload
-// gains more than 2%.
+// b = 64: kept, not measured (calibrate.py says why).  The measured values are
+// 2.4600e-05 ns per pair, 12288 pairs a step and 2.5000e+04 ns a launch.
 #pragma once
 #include <cstdint>
 
