@@ -93,3 +93,53 @@ def test_vector_alu_classes_are_cut_into_enough_tiles(n, b, least):
     got, st = ssj.ssj_self_join(d, 4, 5, b_bits=b, flags=ssj.SSJ_FLAG_VALU)
     want, _ = ssj.ssj_self_join(d, 4, 5, b_bits=256, flags=ssj.SSJ_FLAG_MFMA)
     assert st["class_tiles"][0] > least and np.array_equal(got, want)
+
+
+@pytest.fixture(scope="module")
+def even():
+    """5,000 sets of 20 .. 24 tokens: at 1/3 every pair is in the band, and many survive."""
+    c = gen.generate(n_sets=5000, universe=50, zipf_s=0.5, size_dist=gen.SIZE_UNIFORM, size_lo=20,
+                     size_hi=24, planted_frac=0.2, seed=82)
+    return c, ssj.to_device(c.offsets, c.tokens)
+
+
+# in tiles of one column every width has more tiles than get a wave each
+@pytest.mark.parametrize("flags", [ssj.SSJ_FLAG_MFMA, ssj.SSJ_FLAG_VALU])
+@pytest.mark.parametrize("b", [128, 256, 512, 1024])
+def test_cursors_at_every_width(even, b, flags):
+    c, d = even
+    bm = oracle.bitmaps(c.offsets, c.tokens, b, oracle.BM_XOR)
+    cnt, _, want = oracle.survivors(c.offsets, bm, b, 1, 3, listing=True)
+    for cap in (0, 40_000):
+        got, st = ssj.ssj_self_join(d, 1, 3, b_bits=b, tile_cols=1, queue_capacity=cap,
+                                    flags=flags | ssj.SSJ_FLAG_SURVIVORS_ONLY)
+        assert st["class_tiles"][0] > 65536 and (cap == 0 or st["filter_launches"] > 1)
+        assert st["survivors"] == cnt > 100_000 and np.array_equal(got, want)
+
+
+def test_large_wide_class_takes_the_cursors():
+    """20,000 sets of one size at 2048 bits: fewer tiles than get a wave each, but more than
+    0.7 ms of work; a queue that fills."""
+    c = gen.generate(n_sets=20_000, universe=400, zipf_s=0.5, size_dist=gen.SIZE_UNIFORM,
+                     size_lo=40, size_hi=40, planted_frac=0.3, seed=83)
+    d = ssj.to_device(c.offsets, c.tokens)
+    want = oracle.self_join(c.offsets, c.tokens, 4, 5)
+    for cap in (0, 4096):
+        got, st = ssj.ssj_self_join(d, 4, 5, b_bits=2048, queue_capacity=cap)
+        assert st["class_tiles"][0] <= 65536 and (st["filter_launches"] > 1) == (cap > 0)
+        assert st["survivors"] > 4096 and np.array_equal(got, want)
+
+
+# the cursors' class first or last, one wave per tile in the others
+@pytest.mark.parametrize("short,long", [(14_000, 1500), (2000, 9000)])
+def test_full_queue_over_cursors_and_single_tiles(short, long):
+    cols = [gen.generate(n_sets=n, universe=2000, zipf_s=1.0, size_dist=gen.SIZE_LOGNORMAL,
+                         size_a=m, size_b=0.4, size_lo=2, size_hi=600, planted_frac=0.3, seed=s)
+            for n, m, s in ((short, 8.0, 84), (long, 150.0, 85))]
+    devs = [ssj.to_device(c.offsets, c.tokens) for c in cols]
+    p, q = [4, 1], [5, 2]
+    got, st = ssj.ssj_self_join_batch(devs, p, q, tile_cols=1, queue_capacity=4096)
+    tiles = st["class_tiles"][:st["n_classes"]]
+    assert max(tiles) > 65536 and min(tiles) <= 65536 and st["filter_launches"] > len(tiles)
+    for c, a, x, y in zip(cols, got, p, q):
+        assert np.array_equal(a, oracle.self_join(c.offsets, c.tokens, x, y))
