@@ -14,9 +14,11 @@
 //   - the wave walks the tile's columns in order; every column's bitmap is
 //     wave-uniform and is read with scalar loads, one step of U columns
 //     ahead, into two alternating register buffers;
-//   - columns of equal size form a group; at a group start each lane
-//     derives its threshold from the row and column sizes, folding the
-//     length filter in (threshold -1 = never kept);
+//   - columns are swept in runs of one size, or, where the sizes are sparse,
+//     of a few (ColRun); at a run's start each lane derives its threshold
+//     from the row and column sizes, folding the length filter in (threshold
+//     -1 = never kept), and in a run of several sizes the pairs that reach
+//     the bound are tested at their own;
 //   - the compare is folded into the popcount: the chain starts at
 //     -(slack + 1), so a kept pair has a negative sum; the sums of a step's
 //     U*R pairs are ORed and one ballot of the sign bit decides whether the
@@ -24,10 +26,11 @@
 //     their ballot ranks in its LDS buffer, which goes to the queue with one
 //     reservation when full and at the end of every tile;
 //   - self-join diagonal tiles add the triangle condition j < i.
-// Waves are persistent and take tiles from cursors split per XCD.  When the
-// survivor queue is full the wave marks its reserved slots as sentinels,
-// records (tile, column, row slab) of its first staged pair to resume from,
-// sets the overflow flag and stops; the host verifies the queue and
+// A launch starts one wave per tile, or, where it has very many tiles or a lot
+// of wide work, persistent waves that take tiles from cursors split per XCD
+// (tile_loop).  When the survivor queue is full the wave marks its reserved slots
+// as sentinels, records (tile, column, row slab) of its first staged pair to resume
+// from, sets the overflow flag and stops; the host verifies the queue and
 // relaunches with the resume list.
 #include <algorithm>
 
@@ -738,10 +741,12 @@ __global__ __launch_bounds__(kBlock) void k_filter(FilterArgs) {
 //   - MFMA columns (B) are 32 of the wave's rows, RT such row tiles, held in
 //     registers for the whole tile;
 //   - lane l holds row l%32 of every row tile and 16 of the step's columns,
-//     8(v/4) + 4(l/32) + v%4 for v = 0..15.  Steps never cross a size group
-//     (a group's last step is partial; lanes past its end load zeros), so
-//     one threshold per lane and row tile covers all 16 values: the max of
-//     the 16 dot products against T is the whole fast-path test.
+//     8(v/4) + 4(l/32) + v%4 for v = 0..15.  Steps never cross a run's end (a
+//     run's last step is partial, and the pairs of the columns past its end
+//     are dropped), so one threshold per lane and row tile covers all 16
+//     values: the max of the 16 dot products against T is the whole fast-path
+//     test.  In a run of several sizes T is a bound, and the slow path tests
+//     each pair that reaches it at its own sizes.
 // The slow path stages the kept pairs in a fixed order (row tile, then v,
 // then lane), so a step resumed after a full queue skips exactly the pairs
 // it had written.
@@ -784,10 +789,9 @@ __device__ __forceinline__ v16f_t mfma_pm1(const uint4 &a, const uint4 &b, const
   return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(x, y, c, 4, 4, 0, 127, 0, 127);
 }
 
-// This lane's half of every block of column `col`, or zeros when !ok: the
-// planes hold n + 1 columns, column n all zero, so every lane loads and no
-// load sits behind a branch.
-// This lane's half of set `col`'s sign planes (set n, all zero, when !ok).
+// This lane's half of set `col`'s sign planes, every block, or of set n's when !ok: the
+// planes end in kSignPad sets of zeros, so every lane loads and no load sits
+// behind a branch.
 template <int W>
 __device__ __forceinline__ void load_signs(const uint4 *__restrict__ planes, uint32_t n,
                                            uint32_t col, bool ok, uint32_t h, uint4 (&a)[W]) {
@@ -1151,8 +1155,9 @@ __device__ __forceinline__ bool run_tile_mfma(const TileJob &jb, Sink &sink) {
   MRows<W, RT> rw;
   rw.idx = jb.row0 + jr;
   // No branches: every row's loads are in flight together (with a branch per row
-  // tile each waited for the one before: b = 128 .. 512 classes of 20,000 .. 32,000
-  // tiles 750, 726, 284 -> 680, 686, 266 us).  Rows past the end read the last one's.
+  // tile each waited for the one before: b = 128, 256 and 512 classes of 20,000 ..
+  // 32,000 tiles 750, 726, 284 -> 680, 686, 266 us; not measured by itself at b =
+  // 1024, where the loads take the kernel's last registers).  Rows past the end read the last one's.
   const uint32_t last = jb.row_end - 1;
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt) rw.size[rt] = size_rows[min(rw.idx + 32u * rt, last)];
@@ -1234,8 +1239,10 @@ __device__ __forceinline__ bool run_tile_mfma(const TileJob &jb, Sink &sink) {
 //   C + d0 / 2 + 2^16 d1 / 2,
 // d0 and d1 the dot products (even numbers) of columns j and j + 32 with the row.
 // C is the float with bit pattern 0x4B404000 (1.5 2^23 + 2^14), so that the sum
-// stays in [2^23, 2^24), where a float's pattern is its value plus a constant:
-// its halves are 0x4B40 + d1 / 2 and 0x4000 + d0 / 2, two positive 16-bit floats
+// stays in [2^23, 2^24), where a float's pattern is its value plus a constant.
+// (A single +-1/2 has no place there: that a block's sum arrives whole rests on how
+// the matrix cores add, and on the test that checks every pair of dot products.)
+// Its halves are 0x4B40 + d1 / 2 and 0x4000 + d0 / 2, two positive 16-bit floats
 // that order like the dot products.  A tree of packed 3-input 16-bit maxima, the
 // threshold (less one) among its inputs, reduces 32 pairs in the 8 instructions
 // that 16 took, and a pair is kept exactly when the result differs from the
@@ -1271,9 +1278,6 @@ template <int W>
 __device__ __forceinline__ uint32_t pack_threshold(int32_t u) {
   u = min(max(u, -32 * W), 32 * W + 1);
   return ((kFieldHi + (uint32_t)(u - 1)) << 16) + kFieldLo + (uint32_t)(u - 1);
-}
-__device__ __forceinline__ int32_t packed_dot_threshold(uint32_t p) {
-  return 2 * ((int32_t)(p & 0xFFFFu) - (int32_t)kFieldLo + 1);
 }
 
 __device__ __forceinline__ v16f_t mfma_two(const uint4 &a, const uint4 &b, const v16f_t &c,
@@ -1562,9 +1566,12 @@ __global__ __launch_bounds__(kBlock, mfma_waves(W)) void k_filter_mfma(FilterArg
   static_assert(RT <= kMaxRowTiles, "kept values of every row tile");
   // per wave: kStage entries, kept values, the rows' sizes and bands or dot products
   extern __shared__ uint2 stage[];
-  // (the wave's number is uniform: left to the compiler the three addresses take vector
-  // registers, which the kernel of 1024 bits has none of to spare)
-  uint2 *mine = stage + rfl(threadIdx.x >> 6) * (mfma_wave_lds<W>() / sizeof(uint2));
+  // The wave's number is uniform: left to the compiler the three addresses take vector
+  // registers, which the kernel of 1024 bits has none of to spare.  (At 128 bits scalar
+  // ones, moved to vector registers where they are used, cost a batch's class 4%.)
+  uint32_t wave = threadIdx.x >> 6;
+  if (W >= 16) wave = rfl(wave);
+  uint2 *mine = stage + wave * (mfma_wave_lds<W>() / sizeof(uint2));
   Sink sink;
   sink_init(sink, mine, reinterpret_cast<uint32_t *>(mine + kStage),
             reinterpret_cast<uint32_t *>(mine + kStage + 32 * kMaxRowTiles));

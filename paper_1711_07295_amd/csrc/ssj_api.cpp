@@ -61,16 +61,18 @@ constexpr uint32_t kDefaultTileCols = 2048;
 // 741 / 768, in a 3,000-set R-S join 201 / 133 / 121 / 124; b = 512 in the
 // batch 274 / 292 / 324 / 408.
 //
-// On the vector ALUs eight tiles for every SIMD below 512 bits and 24 from there
+// On the vector ALUs eight tiles for every SIMD below 2048 bits and 24 from there
 // on.  At 8,192 / 16,384 / 24,576 / 32,768 tiles: b = 2048 in a batch of 256
 // collections 1568 / 1455 / 1386 / 1379 us, in a join of 60,000 sets 2056 / 1870
-// / 1811 / 1786; b = 512 in a join of 20,000 long sets 206 / 163 / 151 / 152;
-// b = 256 in the same join, where most pairs survive, 578 / 823 / 836 / 849, and
-// in the join of 60,000 sets 173 / 165 / 171 / 177.
+// / 1811 / 1786; b = 512 in a query of 2,000 sets against 5,000,000 70 / 114 /
+// 115 (tiles of the least width from 12,288 on), in 8 queries of 100 against
+// 300,000 199 / 203 / 281, in a join of 20,000 long sets 211 / 156 / 141; b = 256
+// in the same join, where most pairs survive, 578 / 823 / 836 / 849, and in the
+// join of 60,000 sets 173 / 165 / 171 / 177.
 uint64_t min_slot_tiles(const FilterShape &shape) {
   const uint64_t simds = (uint64_t)filter_grid_blocks() / 8 * 4;
   if (shape.mfma) return 8ull * mfma_resident_waves(shape.words);
-  return (shape.words < 8 ? 8 : 24) * simds;
+  return (shape.words < 32 ? 8 : 24) * simds;
 }
 // Widest tiles of a vector-ALU class below 512 bits.  These kernels hold many waves, and
 // a large class would have three or four tiles for each: the launch then waits
@@ -1548,9 +1550,9 @@ struct RoundTimes {
 // on only in a class of little work: its columns' planes outgrow an XCD's L2, which
 // then wants one region of the tiles per XCD, as the cursors have it, and that is
 // worth more than the 45 us they cost.  In a batch of 256 joins the 512-, 1024- and
-// 2048-bit classes take 6.5, 6.8 and 2.0 ms with a wave per tile and 4.4, 4.4 and
-// 1.6 with cursors; smaller classes are faster with a wave per tile (a join of long
-// sets: 512 bits 248 us against 348, 1024 bits 318 against 408).
+// 2048-bit classes take 7.7, 7.0 and 2.4 ms with a wave per tile and 4.4, 3.7 and
+// 1.3 with cursors; smaller classes are faster with a wave per tile (a join of long
+// sets: 512 bits 256 us against 346, 1024 bits 256 against 342).
 constexpr double kDirectWideNs = 700000.0;
 bool direct_slot(const Plan &pl, uint32_t k) {
   const uint32_t words = pl.slot_words[k];
@@ -2585,9 +2587,10 @@ int bitmap_args(const ssj_sets *s, uint32_t b_bits, int method, uint32_t p, uint
 }
 
 // The bitmaps of one collection in caller order, `method` one of Xor, Set,
-// Next.  The offsets and the token order are validated on the way, so that the
-// call is one launch and one wait.  Its error flags are in page-locked memory
-// (h_flags, nothing is copied), or, when that is nullptr, in `d_flags`.
+// Next.  The offsets and the token order are validated on the way.  With error
+// flags in page-locked memory (h_flags) the call is one launch and one wait; when
+// that is nullptr they are in `d_flags`, cleared by a launch before and copied
+// to the host after.
 int build_bitmaps(const ssj_sets *s, uint32_t b_bits, int method, uint64_t *out, hipStream_t st,
                   uint32_t *h_flags, uint32_t *d_flags) {
   const uint64_t n = s->n_sets;

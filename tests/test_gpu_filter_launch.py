@@ -84,7 +84,7 @@ def test_steps_of_several_sizes(sparse, sim, p, q, b, flags):
         assert np.array_equal(got, want)
 
 
-@pytest.mark.parametrize("n,b,least", [(60_000, 2048, 20_000), (60_000, 512, 20_000),
+@pytest.mark.parametrize("n,b,least", [(60_000, 2048, 20_000), (60_000, 4096, 20_000),
                                        (200_000, 64, 20_000), (200_000, 192, 40_000)])
 def test_vector_alu_classes_are_cut_into_enough_tiles(n, b, least):
     c = gen.generate(n_sets=n, universe=n, zipf_s=1.0, size_dist=gen.SIZE_LOGNORMAL, size_a=20.0,
