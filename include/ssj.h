@@ -188,7 +188,10 @@ typedef struct {
  *                Jaccard threshold with the same normalized value,
  *                t'/(2 - t'); ssj_cutoff resolves Combined per function.)
  *   bitmaps_dev  caller-owned device buffer of n_sets * b_bits / 64 uint64,
- *                written in caller order
+ *                written in caller order; offsets and token order are
+ *                checked while the bitmaps are built, so that after
+ *                SSJ_E_INVALID for bad offsets, SSJ_E_UNSORTED or
+ *                SSJ_E_DEVICE it may be partly written
  *   hip_stream   stream for the work; the call returns after the stream
  *                is synchronised (validation result is needed)
  * Errors: SSJ_E_INVALID (null pointer, bad b, bad offsets, Combined with a
@@ -206,10 +209,12 @@ int ssj_build_bitmaps(const ssj_sets *s, uint32_t b_bits, int method, uint32_t p
  *   Working memory (error flags) is a fixed device array of a few bytes
  *   inside the library, one copy per device, held from the library's load
  *   until the process ends and cleared by every call.  Calls on one device
- *   share that array: the library runs them
- *   one at a time (a call holds the device's array until its stream is
- *   synchronised), so concurrent calls from several threads wait for each
- *   other instead of racing.  No host memory is allocated either.
+ *   share that array: the library runs them one at a time (a call holds the
+ *   device's array until its stream is synchronised), so concurrent calls
+ *   from several threads wait for each other instead of racing.  No host
+ *   memory is allocated either.  The array would serve any number of sets;
+ *   the limit of SSJ_NOALLOC_MAX_SETS, from a time when it held every set's
+ *   size, stays so that programs which rely on the refusal keep it.
  *   The call synchronises hip_stream, so it cannot be captured into a graph.
  * Errors: as ssj_build_bitmaps; SSJ_E_UNSUPPORTED also when n_sets exceeds
  *         SSJ_NOALLOC_MAX_SETS (nothing is written then); SSJ_E_DEVICE when

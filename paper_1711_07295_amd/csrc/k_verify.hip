@@ -20,8 +20,8 @@
 //
 // Each wave packs the real entries of its windows of the queue (the
 // filter's chunks end in sentinels) so that every lane verifies a survivor;
-// results are appended with one atomic per wave and round (ballot + lane
-// rank).
+// results and deferred pairs are staged per wave and appended with one atomic
+// per workgroup at the end, or per wave when a wave's list fills.
 #include <atomic>
 
 #include "ssj_internal.h"

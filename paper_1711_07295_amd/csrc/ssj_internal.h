@@ -15,7 +15,8 @@ constexpr uint32_t kSentinel = 0xFFFFFFFFu;
 // Widest bitmap in 64-bit words (b = 4096 bits).
 constexpr uint32_t kMaxWords = 64;
 
-// Threads per workgroup for every kernel of the library (4 wave64s).
+// Threads per workgroup of the library's kernels (4 wave64s), but for those that name
+// their own (verification, the one-workgroup kernels, one-wave filter launches).
 constexpr int kBlock = 256;
 
 // Partitions of a tile range (one per XCD of the MI355X).
@@ -115,11 +116,6 @@ __host__ __device__ inline uint32_t cosine_omin(uint32_t a, uint32_t c, uint32_t
   return (uint32_t)o;
 }
 
-// slack = |r| + |s| - 2 omin of a Cosine task (negative: never similar)
-__host__ __device__ inline int32_t cosine_slack(uint32_t a, uint32_t c, uint32_t p, uint32_t q) {
-  return (int32_t)((int64_t)a + c - 2 * (int64_t)cosine_omin(a, c, p, q));
-}
-
 // One row block of the filter's tile plan: up to 64*R consecutive rows
 // [row0, row_end) of one row side, all of one bitmap width, and the column
 // range (global column indices) they are compared with.
@@ -174,9 +170,10 @@ struct FilterConfig {
 };
 
 // A launch of at most this many tiles starts one wave per tile and leaves
-// their balance to the workgroup dispatch (FilterConfig::direct).  It saves
-// the cursors' fixed cost; a launch of more tiles takes long enough not to
-// notice it, and keeps an XCD's waves on neighbouring tiles.
+// their balance to the workgroup dispatch (FilterConfig::direct), unless it has a
+// lot of wide work (direct_slot).  It saves the cursors' fixed cost; a launch
+// of more tiles takes long enough not to notice it, and keeps an XCD's waves
+// on neighbouring tiles.
 constexpr uint32_t kDirectTiles = 65536;
 
 // ---------------------------------------------------------------- launchers
