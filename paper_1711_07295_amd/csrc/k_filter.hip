@@ -554,14 +554,17 @@ __device__ __forceinline__ void tile_loop(Sink &sink, Run &&run) {
     const uint32_t tile_lo = a->cfg.tile_lo, tile_hi = a->cfg.tile_hi;
     const uint32_t n_tiles = tile_hi - tile_lo;
     const uint32_t n_resume = min(a->cfg.n_resume_in, a->cfg.resume_cap);
+    // the queue is full once a wave has left something to be done
     const bool full =
         stopped ||
-        rfl(__hip_atomic_load(&ctr->overflow, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) != 0;
+        rfl(__hip_atomic_load(&ctr->n_resume, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) != 0;
     if (full) {
       // The tile, and what the wave has left of the resume entries (entry, entry + waves,
       // ...), stay to be done: one reservation for 64 of them.  One each, on one
       // address, took most of a round of a small queue over many tiles: a 40,000-slot
-      // queue over 25,000 tiles 0.62 ms a round, so 0.22.
+      // queue over 25,000 tiles 0.62 ms a round, so 0.10.  The count of what was left
+      // is also the sign that the queue is full: a flag of its own, stored by every
+      // wave that finds it so, took 0.12 ms of such a round.
       do {
         const uint64_t e = entry + (uint64_t)lane * a->cfg.waves;
         uint32_t rt = t, rc = col, rs = slab, re = end;  // lane 63: the tile
@@ -575,7 +578,9 @@ __device__ __forceinline__ void tile_loop(Sink &sink, Run &&run) {
         if (m) {
           uint32_t at = 0;
           if (lane == 0) at = atomicAdd(&ctr->n_resume, (uint32_t)__popcll(m));
-          at = rfl(at) + (uint32_t)__popcll(m & __lanemask_lt());
+          at = rfl(at);
+          if (at == 0 && lane == 0) ctr->overflow = 1;  // for the host
+          at += (uint32_t)__popcll(m & __lanemask_lt());
           if (left && at < a->cfg.resume_cap) a->resume_out[at] = Resume{rt, rc, rs, re};
         }
         undone = false;
@@ -687,8 +692,6 @@ __device__ __forceinline__ void tile_loop(Sink &sink, Run &&run) {
     job.c1 = min(c1, a->cfg.n_cols);
     if (!run(job)) {
       // the queue is full: the tile resumes at the sink's point, and the wave takes no more
-      if (lane == 0)
-        __hip_atomic_store(&ctr->overflow, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       stopped = undone = true;
       col = rfl(sink.fail_col);
       slab = rfl(sink.fail_slab);

@@ -37,7 +37,7 @@ def test_waves_with_many_entries_left(tiles, cap, flags):
 
 
 def test_a_round_over_many_tiles_is_short():
-    """25,000 tiles over a 40,000-slot queue: 0.2 ms a round (0.6 with an atomic a tile)."""
+    """25,000 tiles over a 40,000-slot queue: 0.1 ms a round (0.6 with an atomic a tile)."""
     c = gen.generate(n_sets=40_000, universe=40_000, zipf_s=1.0, size_dist=gen.SIZE_LOGNORMAL,
                      size_a=30.0, size_b=0.8, size_lo=2, size_hi=500, planted_frac=0.05, seed=3)
     d = ssj.to_device(c.offsets, c.tokens)
