@@ -21,6 +21,10 @@ FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
          # matrix-core results in VGPRs: the filter reads every one of them
          # with vector ALU ops, and AGPR results would each cost a copy
          "-mllvm", "-amdgpu-mfma-vgpr-form",
+         # the filter's step loops are short and run millions of times: a loop of 1,596
+         # bytes (b = 128) that began 4 bytes before a line of the instruction cache
+         # took 0.711 ms of a batch, on a 32-byte boundary 0.689
+         "-falign-loops=32",
          "-Wall", "-Wno-unused-function", "-Wno-unused-command-line-argument",
          "-I", os.path.join(ROOT, "include"), "-I", CSRC]
 
