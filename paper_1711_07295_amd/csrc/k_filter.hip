@@ -225,17 +225,18 @@ struct TileJob {
   float t;         // p / q
 };
 
-// A task's exact test.  With Cosine among the call's functions it is read where it is
-// used: kept across the vector-ALU sweeps, its fields took scalar registers from the
-// columns' buffers (1024 bits: 105 instructions a column against 96).
+// A task's exact test.  With Cosine among the call's functions it is read again where it
+// is used at 2048 bits and more (AGAIN): kept across the vector-ALU sweeps, its fields
+// take scalar registers from the columns' buffers there (231 instructions a column
+// against 217).  A class of 640 bits takes 0.25 ms with them kept and 0.27 without.
 struct PairTest {
   const int32_t *slack;
   bool cosine;
   uint32_t p, q;
 };
-template <bool COS>
+template <bool AGAIN>
 __device__ __forceinline__ PairTest pair_test(const TileJob &jb) {
-  if constexpr (!COS) return PairTest{jb.slack, false, 0, 0};
+  if constexpr (!AGAIN) return PairTest{jb.slack, jb.cosine, jb.p, jb.q};
   const ArgPtr a = args();
   const auto *td = as_const(a->tasks) + jb.task;
   return PairTest{reinterpret_cast<const int32_t *>(a->tables + td->slack_off),
@@ -319,7 +320,7 @@ __device__ __forceinline__ bool emit(const Rows<W, R> &rw, const uint32_t (&d)[U
   if (ex.bound) {
     // each kept pair at its own sizes.  The
     // biased distance is bias + h, so h = d - bias.
-    const PairTest test = pair_test<COS>(*ex.job);
+    const PairTest test = pair_test<COS && W >= 32>(*ex.job);
 #pragma unroll
     for (int x = 0; x < U * R; ++x) {
       const uint32_t c = as_const(args()->size_cols)[j + x / R];
@@ -389,10 +390,13 @@ __device__ __forceinline__ bool step(const Rows<W, R> &rw, const Exact<R> &ex,
       d[u][r] = h;
       acc |= h;
     }
+  const bool any = __ballot((int32_t)acc < 0) != 0;
   // (the expectation and the sweep's loop of one exit keep what the slow path needs out of
   // the fast one: without them a 2048-bit class of 150,000 long sets took 34.5 ms,
-  // with them 30.1, one of 300,000 short sets at 512 bits 6.35 and 6.00)
-  if (__builtin_expect(__ballot((int32_t)acc < 0) != 0, 0))
+  // with them 30.1, one of 300,000 short sets at 512 bits 6.35 and 6.00; a class of
+  // 60,000 at 64 bits, where most steps keep a pair, 0.35 ms without the
+  // expectation and 0.36 with it)
+  if (W >= 8 ? __builtin_expect(any, 0) : any)
     return emit<W, R, U, COS>(rw, d, j, ex, sink);
   return true;
 }
